@@ -4,8 +4,8 @@ tokens to one of 131072.
 
 ``listed()`` names the cases, ``draw(rng)`` gives more of the same ranges, ``prepare`` makes what a training
 program holds before the call (inputs on the GPU, the pack's plan, its buffers), ``run`` is one pass,
-``work`` what a pass cannot do without and ``tolerance`` how far another correct implementation at the same
-precision may be off.
+``work`` what a pass cannot do without, ``tolerance`` how far another correct implementation at the same
+precision may be off and ``exact`` the same outputs in 64 bits.
 """
 import math
 
@@ -197,3 +197,88 @@ def tolerance(case):
         return {"rel": 1e-2}
     # gradients stored in bf16 are 9.6e-4 off the same path in 64 bits; losses alone are 32-bit sums (4e-8)
     return {"rel": 4e-3} if case["grad"] else {"rel": 1e-5}
+
+
+# ------------------------------------------------------------------------------------ the same in 64 bits
+
+
+def _exact_attention(case, seed):
+    if work(case)["flops"] > 2e14:
+        return None  # the 131072-token pack: too long in 64 bits
+    state = prepare(case, seed)
+    pa, h, kv = state["pa"], case["heads"], case["kv_heads"]
+    g, d, e, scale = h // kv, case["d_qk"], case["d_v"], 1.0 / math.sqrt(case["d_qk"])
+    f64, dev = torch.float64, pa.device
+
+    def out(heads, dim):
+        return torch.empty((case["tokens"], heads, dim), dtype=f64, device=dev)
+
+    o, lse = out(h, e), torch.empty((h, case["tokens"]), dtype=f64, device=dev)
+    dq, dk, dv = (out(h, d), out(kv, d), out(kv, e)) if case["backward"] else (None, None, None)
+    start = 0
+    for n in _lengths(case):
+        k = state["k"][start:start + n].transpose(0, 1).to(f64).contiguous()  # [kv, n, d]
+        v = state["v"][start:start + n].transpose(0, 1).to(f64).contiguous()
+        kt, vt = k.transpose(1, 2).contiguous(), v.transpose(1, 2).contiguous()
+        gk, gv = torch.zeros_like(k), torch.zeros_like(v)
+        step = max(1, min(n, (1 << 27) // (h * n)))  # scores of `step` rows of every head: at most 1 GiB
+        for a in range(0, n, step):
+            b = min(a + step, n)
+            rows = slice(start + a, start + b)
+
+            def by_kv_head(t):  # [rows, h, dim] -> [kv, g * rows, dim]
+                return t.transpose(0, 1).reshape(kv, g * (b - a), -1).to(f64)
+
+            def by_row(t):
+                return t.reshape(h, b - a, -1).transpose(0, 1)
+
+            q = by_kv_head(state["q"][rows])
+            s = torch.matmul(q, kt[:, :, :b].contiguous()).mul_(scale)
+            later = torch.arange(b, device=dev)[None, :] > torch.arange(a, b, device=dev)[:, None]
+            s.view(h, b - a, b).masked_fill_(later, -math.inf)
+            log_sum = torch.logsumexp(s, dim=-1, keepdim=True)
+            p = s.sub_(log_sum).exp_()
+            po = torch.matmul(p, v[:, :b].contiguous())
+            o[rows], lse[:, rows] = by_row(po), log_sum.view(h, b - a)
+            if case["backward"]:
+                go = by_kv_head(state["d_o"][rows])
+                gv[:, :b] += torch.matmul(p.transpose(1, 2).contiguous(), go)
+                ds = torch.matmul(go, vt[:, :, :b].contiguous()).sub_((go * po).sum(-1, keepdim=True)).mul_(p)
+                dq[rows] = by_row(torch.matmul(ds, k[:, :b].contiguous()).mul_(scale))
+                gk[:, :b] += torch.matmul(ds.transpose(1, 2).contiguous(), q).mul_(scale)
+        if case["backward"]:
+            dk[start:start + n], dv[start:start + n] = gk.transpose(0, 1), gv.transpose(0, 1)
+        start += n
+    return (o, lse, dq, dk, dv) if case["backward"] else (o, lse)
+
+
+def _exact_loss(case, seed):
+    s = prepare(case, seed)
+    labels, T, n = s["labels"].long(), s["T"], s["n"]
+    has = (labels >= 0) & (labels < s["V"])
+    sample = torch.bucketize(torch.arange(T, device=labels.device), s["cu"][1:].long(), right=True)
+    count = torch.zeros(n, dtype=torch.float64, device=labels.device).index_add_(0, sample, has.double())
+    if case["normalizer"] == "token_mean":
+        w = (1.0 / count.sum().clamp(min=1.0)).expand(T)
+    elif case["normalizer"] == "sample_mean":
+        w = (1.0 / (count.clamp(min=1.0) * n))[sample]
+    else:
+        w = torch.full((T,), 1.0 / (n * s["t_ave"]), dtype=torch.float64, device=labels.device)
+    w = torch.where(has, w, torch.zeros_like(w))
+    token_loss = torch.zeros(T, dtype=torch.float64, device=labels.device)
+    grad = torch.empty(s["logits"].shape, dtype=torch.float64, device=labels.device) if case["grad"] else None
+    for a in range(0, T, 512):
+        rows = slice(a, min(a + 512, T))
+        z = s["logits"][rows].double()
+        lse, at = torch.logsumexp(z, dim=-1), labels[rows].clamp(0, s["V"] - 1)[:, None]
+        token_loss[rows] = torch.where(has[rows], lse - z.gather(1, at)[:, 0], 0.0)
+        if grad is not None:
+            z.sub_(lse[:, None]).exp_().scatter_add_(1, at, torch.full_like(at, -1, dtype=torch.float64))
+            grad[rows] = z.mul_(w[rows, None])
+    loss = (w * token_loss).sum().reshape(1)
+    return [loss, token_loss] + ([grad] if grad is not None else [])
+
+
+def exact(case, seed):
+    """What `run` gives for these inputs, in 64 bits and plain torch; None where that takes too long."""
+    return (_exact_attention if case["kind"] == "attention" else _exact_loss)(case, seed)
