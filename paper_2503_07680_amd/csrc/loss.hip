@@ -6,10 +6,10 @@
 //                   1 / (T_i B_l) for the row's sample i, stable 1 / (B_l T_ave)
 //   d loss / d z_r  w_r (softmax(z_r) - onehot(label_r))
 //
-// HBM-bound: every logit is read once and every gradient written once.  One workgroup of 1024 threads
-// owns a row at a time and holds the whole row in registers as packed bf16 (up to 163840 entries:
-// 20 loads of 16 bytes per thread, each load instruction of the workgroup covering 16 KiB of
-// consecutive addresses), so the row maximum, the sum of exponentials and the gradient are all
+// HBM-bound: every logit is read once and every gradient written once.  One workgroup of 256, 512 or
+// 1024 threads owns a row at a time and holds the whole row in registers as packed bf16 (up to 163840
+// entries: 20 loads of 16 bytes per thread, each load instruction of the workgroup covering 16 bytes per
+// thread of consecutive addresses), so the row maximum, the sum of exponentials and the gradient are all
 // computed from that one read; the registers of a chunk are refilled with the next row while the
 // gradient of this one is still being written.  Longer rows are streamed twice (running maximum and
 // rescaled sum in the first pass; the second read mostly hits L2/MALL).
@@ -19,8 +19,7 @@
 
 namespace hbp {
 
-constexpr int kCeThreads = 1024;
-constexpr int kCeChunk = kCeThreads * 8;  // logits covered by one load instruction of the workgroup
+constexpr int kCeThreads = 1024;  // of the kernels with one workgroup, and the most of a row's workgroup
 constexpr float kLog2eF = 1.4426950408889634f;
 constexpr float kLn2F = 0.6931471805599453f;
 
@@ -120,6 +119,136 @@ __global__ __launch_bounds__(kCeThreads) void ce_partition_kernel(const CeParams
   }
 }
 
+// ---- what a workgroup of the main kernel works out for itself -----------------------------------
+// Every workgroup needs its range of rows and the weights of the samples in it, and both follow from which
+// rows have a loss.  Up to kCePlanRows rows each workgroup reads all labels itself (from L2; 4 bytes a row
+// against the row's 2 V), keeps them as one bit a row with a running count per 64 rows, and finds its range
+// and any sample's number of loss tokens in that.  The three kernels that did this before the main one
+// (count, weight, partition) each cost a launch: 22 us of 757 at T = 8192, V = 128256, and 12 us of 40 at
+// T = 1000, V = 32000.  They stay for longer packs, whose bits and counts would not fit beside the others'.
+constexpr int kCePlanRows = 1 << 17;
+constexpr int kCePlanCu = 1024;  // samples whose bounds are kept in LDS too
+
+struct CeRows {
+  uint64_t* live;  // bit i of word w: row 64 w + i has a loss; one word of zeros behind the last
+  int32_t* before; // loss rows in front of word w; one entry behind the last
+  int32_t* cu;     // bounds of the samples, null: too many, read them from global memory
+};
+__host__ __device__ inline int ce_plan_words(int T) { return (T + 63) / 64; }
+inline int ce_plan_lds(int T, int n) {
+  return (ce_plan_words(T) + 1) * (int)(sizeof(uint64_t) + sizeof(int32_t)) + (n <= kCePlanCu ? (n + 1) * (int)sizeof(int32_t) : 0);
+}
+// loss rows in front of row x; x is clamped to the pack (a malformed list of samples stays in bounds)
+__device__ __forceinline__ int ce_live_before(const CeRows& c, int x, int T) {
+  x = min(max(x, 0), T);
+  return c.before[x >> 6] + __popcll(c.live[x >> 6] & ((1ull << (x & 63)) - 1));
+}
+__device__ __forceinline__ int ce_sample_count(const CeRows& c, int a, int b, int T) {
+  return max(ce_live_before(c, b, T) - ce_live_before(c, a, T), 0);
+}
+// Fills c, range[0..1] = this workgroup's rows (the cut of ce_partition_kernel: the first row whose preceding
+// rows cost at least k / n_ranges of the total) and slots[NW] = loss tokens in all samples.
+template <int NT>
+__device__ __forceinline__ void ce_plan_rows(const CeParams& p, const CeRows& c, int tid, int* range, int* slots) {
+  constexpr int NW = NT / 64, kBatch = 4;
+  const int wave = tid >> 6, lane = tid & 63, nw = ce_plan_words(p.T);
+  const bool with_grad = p.dlogits != nullptr;
+  for (int w0 = wave; w0 < nw; w0 += NW * kBatch) {
+    int lab[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int r = (w0 + NW * j) * 64 + lane;
+      lab[j] = r < p.T ? p.labels[r] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const uint64_t bits = __builtin_amdgcn_ballot_w64(lab[j] >= 0 && lab[j] < p.V);
+      if (lane == 0 && w0 + NW * j < nw) c.live[w0 + NW * j] = bits;
+    }
+  }
+  if (c.cu)
+    for (int i = tid; i <= p.n_samples; i += NT) c.cu[i] = p.cu[i];
+  __syncthreads();
+  // running counts: `per` consecutive words a thread
+  const int per = (nw + NT - 1) / NT;
+  const int w_begin = min(tid * per, nw), w_end = min(w_begin + per, nw);
+  int mine = 0;
+  for (int w = w_begin; w < w_end; ++w) mine += __popcll(c.live[w]);
+  int incl = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int up = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += up;
+  }
+  if (lane == 63) slots[wave] = incl;
+  __syncthreads();
+  int base = incl - mine, all = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    if (i < wave) base += slots[i];
+    all += slots[i];
+  }
+  const uint64_t row_c = (with_grad ? 8 : 0) + 1;  // row_cost(): 8 more for a row with a loss
+  const uint64_t total = row_c * p.T + 8ull * all, n = gridDim.x;
+  for (int w = w_begin; w < w_end; ++w) {
+    c.before[w] = base;
+    const uint64_t bits = c.live[w];
+    const uint64_t in_front = row_c * (64ull * w) + 8ull * base;
+    base += __popcll(bits);
+    const uint64_t behind = row_c * min(64 * (w + 1), p.T) + 8ull * base;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint64_t target = (blockIdx.x + j) * total;
+      if (in_front * n < target && target <= behind * n) {
+        int i = 0;  // first row of the word with the rows up to and including it costing >= target / n
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1) {
+          const int k = i + step;  // rows 0 .. k - 1 of the word
+          if ((in_front + row_c * k + 8ull * __popcll(bits & ((1ull << k) - 1))) * n < target) i = k;
+        }
+        range[j] = 64 * w + i + 1;
+      }
+    }
+  }
+  if (tid == 0) {
+    c.live[nw] = 0;
+    c.before[nw] = all;
+    if (blockIdx.x == 0) range[0] = 0;
+  }
+  __syncthreads();
+  int in_samples = 0;
+  if (p.normalizer == HBP_LOSS_TOKEN_MEAN) {
+    for (int i = tid; i < p.n_samples; i += NT)
+      in_samples += ce_sample_count(c, c.cu ? c.cu[i] : p.cu[i], c.cu ? c.cu[i + 1] : p.cu[i + 1], p.T);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) in_samples += __shfl_xor(in_samples, m, 64);
+    if (lane == 0) slots[wave] = in_samples;  // the counts in it were read before the barrier
+    __syncthreads();
+    in_samples = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) in_samples += slots[i];
+    __syncthreads();
+    if (tid == 0) slots[0] = in_samples;
+    __syncthreads();
+  }
+}
+// the weight of row r's cross-entropy; 0 for a row that belongs to no sample.  tokens: ce_plan_rows' slots[0].
+__device__ __forceinline__ float ce_row_weight(const CeParams& p, const CeRows& c, int r, int tokens) {
+  auto cu = [&](int i) { return c.cu ? c.cu[i] : p.cu[i]; };
+  int lo = 0, hi = p.n_samples;  // the last sample that begins at or in front of the row
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (cu(mid) <= r) lo = mid;
+    else hi = mid;
+  }
+  const int a = cu(lo), b = cu(lo + 1);
+  if (r < a || r >= b) return 0.f;
+  if (p.normalizer == HBP_LOSS_TOKEN_MEAN) return tokens > 0 ? 1.0f / (float)tokens : 0.f;
+  if (p.normalizer == HBP_LOSS_STABLE) return 1.0f / ((float)p.n_samples * p.t_ave);
+  const float n = (float)ce_sample_count(c, a, b, p.T);
+  return n > 0.f ? 1.0f / (n * (float)p.n_samples) : 0.f;
+}
+
 // NCH: 16-byte loads per thread that cover a row when HOLD (row kept in registers); with !HOLD the
 // row is streamed in kCeChunk pieces, twice.
 //
@@ -139,9 +268,12 @@ __global__ __launch_bounds__(kCeThreads) void ce_partition_kernel(const CeParams
 constexpr int kLag = HBP_CE_LAG;
 constexpr int kRowBatch = 256;  // rows whose scalars are staged in LDS at a time
 
-template <int NCH, bool HOLD, bool WITH_GRAD>
-__global__ __launch_bounds__(kCeThreads) void ce_main_kernel(const CeParams p) {
-  __shared__ float slot_m[2][kCeThreads / 64], slot_s[2][kCeThreads / 64];
+// NT threads, by the length of a row (see launch_packed_ce).
+template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
+__global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
+  constexpr int kCeChunk = NT * 8;  // logits covered by one load instruction of the workgroup
+  constexpr int NW = NT / 64;
+  __shared__ float slot_m[2][NW], slot_s[2][NW];
   const int tid = threadIdx.x;
   const u32x4 kNegInf = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};  // bf16 -inf pairs
   u32x4 held[HOLD ? NCH : 1];
@@ -200,7 +332,14 @@ __global__ __launch_bounds__(kCeThreads) void ce_main_kernel(const CeParams p) {
   // waited for with every outstanding store and load of the chunk pipeline (the counter is in order).
   __shared__ int row_label[kRowBatch];
   __shared__ float row_weight[kRowBatch], row_zlabel[kRowBatch];
-  const int row_end = p.row_start[blockIdx.x + 1];
+  extern __shared__ uint64_t plan_lds[];
+  __shared__ int plan_range[2], plan_slots[NW];
+  CeRows rows;
+  rows.live = plan_lds;
+  rows.before = (int32_t*)(plan_lds + ce_plan_words(p.T) + 1);
+  rows.cu = p.n_samples <= kCePlanCu ? rows.before + ce_plan_words(p.T) + 1 : nullptr;
+  if (!p.row_start) ce_plan_rows<NT>(p, rows, tid, plan_range, plan_slots);
+  const int row_end = p.row_start ? p.row_start[blockIdx.x + 1] : plan_range[1];
   auto stage_rows = [&](int first_row) {  // rows first_row + i, i < kRowBatch
     __syncthreads();                       // the entries of the batch before have all been read
     if (tid < kRowBatch) {
@@ -210,7 +349,8 @@ __global__ __launch_bounds__(kCeThreads) void ce_main_kernel(const CeParams p) {
       if (rr < row_end) {
         lab = p.labels[rr];
         if (has_loss(lab)) {
-          wt = p.weighted[rr];  // the row's weight, put there by ce_weight_kernel
+          wt = p.row_start ? p.weighted[rr]  // the row's weight, put there by ce_weight_kernel
+                           : ce_row_weight(p, rows, (int)rr, plan_slots[0]);
           zl = __uint_as_float((uint32_t)p.logits[rr * p.stride_t + lab] << 16);
         } else {
           lab = -1;
@@ -222,7 +362,7 @@ __global__ __launch_bounds__(kCeThreads) void ce_main_kernel(const CeParams p) {
     }
     __syncthreads();
   };
-  int r = p.row_start[blockIdx.x];
+  int r = p.row_start ? p.row_start[blockIdx.x] : plan_range[0];
   if (r >= row_end) return;
   stage_rows(r);
   int label = row_label[0];  // -1: no loss
@@ -262,11 +402,11 @@ __global__ __launch_bounds__(kCeThreads) void ce_main_kernel(const CeParams p) {
       __syncthreads();
       float m_row = slot_m[parity][0];
 #pragma unroll
-      for (int i = 1; i < kCeThreads / 64; ++i) m_row = fmaxf(m_row, slot_m[parity][i]);
+      for (int i = 1; i < NW; ++i) m_row = fmaxf(m_row, slot_m[parity][i]);
       const float m_row0 = finite_or_zero(m_row);
       float s_row = 0.f;
 #pragma unroll
-      for (int i = 0; i < kCeThreads / 64; ++i)
+      for (int i = 0; i < NW; ++i)
         s_row += slot_s[parity][i] * __builtin_amdgcn_exp2f((finite_or_zero(slot_m[parity][i]) - m_row0) * kLog2eF);
       const float lse2 = m_row0 * kLog2eF + __builtin_amdgcn_logf(s_row);  // log2-sum-exp2 of the row
       const float ce = lse2 * kLn2F - z_label;
@@ -349,48 +489,72 @@ __global__ __launch_bounds__(kCeThreads) void ce_reduce_kernel(const CeParams p)
 
 // Workgroups resident at once per compute unit.  The main kernel's grid is that times the compute
 // units: a persistent loop over rows; a second batch of workgroups would start with an empty pipeline.
-template <int NCH, bool HOLD, bool WITH_GRAD>
-static int main_per_cu() {
-  static int per_cu = 0;  // same on every device of this part
+template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
+static int main_per_cu(int lds) {
+  static int per_cu = 0;  // by registers; same on every device of this part
   if (per_cu == 0) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ce_main_kernel<NCH, HOLD, WITH_GRAD>, kCeThreads, 0) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ce_main_kernel<NT, NCH, HOLD, WITH_GRAD>, NT, 0) != hipSuccess || n < 1) n = 1;
     per_cu = n;
   }
-  return per_cu;
+  constexpr int kLds = 160 * 1024, kStatic = 4 * 1024;  // LDS of a compute unit; the kernel's own arrays
+  const int by_lds = kLds / (lds + kStatic);
+  return per_cu < by_lds ? per_cu : by_lds;
 }
-template <int NCH, bool HOLD, bool WITH_GRAD>
-static void launch_main_g(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  int64_t grid = (int64_t)main_per_cu<NCH, HOLD, WITH_GRAD>() * n_cu;
+template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
+static void launch_main_g(CeParams p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const bool planned = p.T > kCePlanRows;
+  const int lds = planned ? 0 : ce_plan_lds(p.T, p.n_samples);
+  int64_t grid = (int64_t)main_per_cu<NT, NCH, HOLD, WITH_GRAD>(lds) * n_cu;
   if (grid > kCeMaxWorkgroups) grid = kCeMaxWorkgroups;
   if (grid > p.T) grid = p.T;
-  hipLaunchKernelGGL(ce_partition_kernel, dim3(1), dim3(kCeThreads), 0, s, p, (int)grid);
-  if (ev0) (void)hipEventRecord(ev0, s);
-  hipLaunchKernelGGL((ce_main_kernel<NCH, HOLD, WITH_GRAD>), dim3((unsigned)grid), dim3(kCeThreads), 0, s, p);
-  if (ev1) (void)hipEventRecord(ev1, s);
-}
-template <int NCH, bool HOLD>
-static void launch_main(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (p.dlogits) launch_main_g<NCH, HOLD, true>(p, n_cu, s, ev0, ev1);
-  else launch_main_g<NCH, HOLD, false>(p, n_cu, s, ev0, ev1);
-}
-
-int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (p.n_samples > 0) {
+  if (planned) {
     hipLaunchKernelGGL(ce_count_kernel, dim3(p.n_samples), dim3(256), 0, s, p);
     hipLaunchKernelGGL(ce_weight_kernel, dim3(p.n_samples), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(ce_partition_kernel, dim3(1), dim3(kCeThreads), 0, s, p, (int)grid);
+  } else {
+    p.row_start = nullptr;
   }
-  if (p.T > 0) {
-    const int chunks = (p.V + kCeChunk - 1) / kCeChunk;
-    switch (chunks) {
-#define HBP_CE_HELD(N) case N: launch_main<N, true>(p, n_cu, s, ev0, ev1); break;
-      HBP_CE_HELD(1) HBP_CE_HELD(2) HBP_CE_HELD(3) HBP_CE_HELD(4) HBP_CE_HELD(5)
-      HBP_CE_HELD(6) HBP_CE_HELD(7) HBP_CE_HELD(8) HBP_CE_HELD(9) HBP_CE_HELD(10)
-      HBP_CE_HELD(11) HBP_CE_HELD(12) HBP_CE_HELD(13) HBP_CE_HELD(14) HBP_CE_HELD(15)
-      HBP_CE_HELD(16) HBP_CE_HELD(17) HBP_CE_HELD(18) HBP_CE_HELD(19) HBP_CE_HELD(20)
+  if (ev0) (void)hipEventRecord(ev0, s);
+  hipLaunchKernelGGL((ce_main_kernel<NT, NCH, HOLD, WITH_GRAD>), dim3((unsigned)grid), dim3(NT), lds, s, p);
+  if (ev1) (void)hipEventRecord(ev1, s);
+}
+template <int NT, int NCH, bool HOLD>
+static void launch_main(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (p.dlogits) launch_main_g<NT, NCH, HOLD, true>(p, n_cu, s, ev0, ev1);
+  else launch_main_g<NT, NCH, HOLD, false>(p, n_cu, s, ev0, ev1);
+}
+// rows of LO to HI chunks of NT * 8 entries
+template <int NT, int LO, int HI>
+static bool launch_held(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  switch ((p.V + NT * 8 - 1) / (NT * 8)) {
+#define HBP_CE_HELD(N) case N: if constexpr (N >= LO && N <= HI) { launch_main<NT, N, true>(p, n_cu, s, ev0, ev1); return true; } return false;
+    HBP_CE_HELD(1) HBP_CE_HELD(2) HBP_CE_HELD(3) HBP_CE_HELD(4) HBP_CE_HELD(5)
+    HBP_CE_HELD(6) HBP_CE_HELD(7) HBP_CE_HELD(8) HBP_CE_HELD(9) HBP_CE_HELD(10)
+    HBP_CE_HELD(11) HBP_CE_HELD(12) HBP_CE_HELD(13) HBP_CE_HELD(14) HBP_CE_HELD(15)
+    HBP_CE_HELD(16) HBP_CE_HELD(17) HBP_CE_HELD(18) HBP_CE_HELD(19) HBP_CE_HELD(20)
 #undef HBP_CE_HELD
-      default: launch_main<1, false>(p, n_cu, s, ev0, ev1);
-    }
+    default: return false;
+  }
+}
+
+// Threads a row.  A row costs its workgroup one reduction and one barrier whatever its length, with nothing
+// else to run on the compute unit if the workgroup fills it; several smaller workgroups overlap theirs.  A
+// longer row has to be spread over more threads to be held.  us at T = 8192 with the gradient / without:
+//   V        1024 threads   512          256
+//   4096      65 /  41       41 /  29     37 /  28
+//   16384    111 /  56      104 /  46    104 /  46
+//   32000    192 / 104      192 /  74    195 /  84
+//   65536    381 / 164      375 / 146
+//   81920    476 / 194      473 / 178
+// (with few rows a workgroup, T = 1000, the three are within 10 % from V = 32000 on.)
+constexpr int kCeRow256 = 16384, kCeRow512 = 81920;
+
+int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (p.T > 0) {
+    if (p.V <= kCeRow256) (void)launch_held<256, 1, kCeRow256 / 2048>(p, n_cu, s, ev0, ev1);
+    else if (p.V <= kCeRow512) (void)launch_held<512, kCeRow256 / 4096 + 1, kCeRow512 / 4096>(p, n_cu, s, ev0, ev1);
+    else if (!launch_held<1024, kCeRow512 / 8192 + 1, 20>(p, n_cu, s, ev0, ev1)) launch_main<1024, 1, false>(p, n_cu, s, ev0, ev1);
   }
   hipLaunchKernelGGL(ce_reduce_kernel, dim3(1), dim3(kCeThreads), 0, s, p);
   return (int)hipGetLastError();

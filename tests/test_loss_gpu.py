@@ -85,6 +85,31 @@ def test_large_vocabularies_held_in_registers_and_a_longer_row_streamed_twice():
     check(bits, y, cu, 2, t_ave=2.0)
 
 
+@pytest.mark.parametrize("V", [16376, 16384, 16392, 81920, 81928])
+def test_vocab_sizes_around_the_limits_of_the_workgroup_sizes(V):
+    bits, y, cu = make_case([5, 8], V, V % 89)
+    check(bits, y, cu, 1)
+
+
+@pytest.mark.parametrize("lens", [[63], [64], [40, 25], [1] * 1100 + [60], [70000, 61072], [70000, 61073]])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_rows_and_weights_found_from_the_label_bits(lens, mode):
+    # around a word of 64 rows; more samples than are kept on chip; the longest pack planned in the main kernel
+    # and the first one that has kernels of its own for that
+    bits, y, cu = make_case(lens, 8, len(lens) + lens[0])
+    check(bits, y, cu, mode)
+
+
+def test_rows_outside_every_sample_have_no_weight():
+    bits, y, cu = make_case([30, 50, 20], 64, 9, p_mask=0.0)
+    cu = np.array([10, 30, 30, 85], dtype=np.int32)                 # rows 0..9 and 85..99 are in no sample
+    _, _, dz = run_gpu(bits, y, cu, 0)
+    want, _, dz_in = run_gpu(bits[10:85], y[10:85], (cu - 10).astype(np.int32), 0)
+    loss, tl, _ = run_gpu(bits, y, cu, 0)
+    assert loss == pytest.approx(want, rel=LOSS_REL) and tl.all()
+    assert not dz[:10].any() and not dz[85:].any() and np.array_equal(dz[10:85], dz_in)
+
+
 def test_row_stride_and_more_rows_than_workgroups():
     bits, y, cu = make_case([700, 300, 200], 512, 3)
     check(bits, y, cu, 0, stride=520)
