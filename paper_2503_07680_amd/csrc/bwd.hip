@@ -810,9 +810,12 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   prof_write(pa, p.prof, tid);
 }
 
-// dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  One workgroup
-// per key tile of the worklist (only rows covered by a tile are written, as without parts); a thread
-// handles four consecutive dims of one (key, kv head).
+// dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  Workgroups (x, y):
+// share y of key tile x of the worklist (only rows covered by a tile are written, as without parts); a thread
+// handles four consecutive dims of one (key, kv head) at a time.  HBM-bound: every partial sum is read once.
+// With one workgroup a tile there were too few loads under way (T = 32768, 8 query heads on one kv head, 269
+// tiles: 125 us, 2.3 TB/s); kReduceUnits units a thread and four loads of each under way: 53 us, 5.4 TB/s.
+constexpr int kReduceUnits = 2;
 template <int DQK, int DV>
 __global__ __launch_bounds__(kThreads) void bwd_reduce_parts_kernel(const BwdParams p) {
   const hbp_tile tl = p.tiles[blockIdx.x];
@@ -821,23 +824,26 @@ __global__ __launch_bounds__(kThreads) void bwd_reduce_parts_kernel(const BwdPar
   if (!(s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end && tl.row_end <= s1 &&
         tl.row_end - tl.row_begin <= 128))
     return;
-  constexpr int QK4 = DQK / 4, V4 = DV / 4;
-  const int n_rows = tl.row_end - tl.row_begin;
-  const int64_t n_units = (int64_t)n_rows * p.Hkv * (QK4 + V4);
-  for (int64_t u = threadIdx.x; u < n_units; u += kThreads) {
-    const int c = (int)(u % (QK4 + V4));
-    const int64_t rk = u / (QK4 + V4);
-    const int kh = (int)(rk % p.Hkv);
-    const int64_t key = tl.row_begin + rk / p.Hkv;
+  constexpr uint32_t QK4 = DQK / 4, V4 = DV / 4;
+  const uint32_t n_heads = p.Hkv, n_units = (uint32_t)(tl.row_end - tl.row_begin) * n_heads * (QK4 + V4);
+  for (uint32_t u = blockIdx.y * kThreads + threadIdx.x; u < n_units; u += gridDim.y * kThreads) {
+    const uint32_t c = u % (QK4 + V4), rk = u / (QK4 + V4);
+    const uint32_t row = rk / n_heads, kh = rk - row * n_heads;
+    const int64_t key = tl.row_begin + row;
     const bool is_k = c < QK4;
     const int dim = is_k ? DQK : DV, x = 4 * (is_k ? c : c - QK4);
     const float* src = (is_k ? p.dk_part : p.dv_part) + (key * p.Hkv + kh) * dim + x;
     const int64_t part_stride = (int64_t)p.T * p.Hkv * dim;
     f32x4 acc = *(const f32x4*)src;
-    for (int part = 1; part < p.n_split; ++part) {
-      const f32x4 v = *(const f32x4*)(src + part * part_stride);
-      acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
+    int part = 1;
+    for (; part + 4 <= p.n_split; part += 4) {  // four loads under way
+      f32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = *(const f32x4*)(src + (part + i) * part_stride);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc += v[i];
     }
+    for (; part < p.n_split; ++part) acc += *(const f32x4*)(src + part * part_stride);
     uint16_t* dst = is_k ? p.dk + key * p.k_st + (int64_t)kh * p.k_sh + x : p.dv + key * p.v_st + (int64_t)kh * p.v_sh + x;
     *(u32x2*)dst = u32x2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])};
   }
@@ -905,7 +911,9 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
     if (p.n_split > 1) {
-      hipLaunchKernelGGL((bwd_reduce_parts_kernel<DQK, DV>), dim3(p.n_tiles), dim3(kThreads), 0, s, p);
+      const int units = 128 * p.Hkv * ((DQK + DV) / 4);  // of a full tile; fewer than 8 kv heads here
+      hipLaunchKernelGGL((bwd_reduce_parts_kernel<DQK, DV>), dim3(p.n_tiles, units / (kThreads * kReduceUnits)),
+                         dim3(kThreads), 0, s, p);
       e = hipGetLastError();
       if (e != hipSuccess) return (int)e;
     }
