@@ -292,7 +292,6 @@ extern "C" hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void*
   p.n_split = hbp::heads_split(p.Hkv, p.g % 2 == 0 ? p.g / 2 : p.g);  // even groups: items are pairs of heads
 
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  if (hbp::launch_zero_counters(p.counter, hs) != 0) return HBP_ERR_DEVICE;
   if (hbp::launch_fwd(desc->d_qk, desc->d_v, p, desc->fwd_tile_rows ? desc->fwd_tile_rows : kTileRows, kNumCU, hs, g_events[HBP_FWD][0], g_events[HBP_FWD][1]) != 0) return HBP_ERR_DEVICE;
   return HBP_OK;
 }
@@ -389,8 +388,11 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   p.dk_part = reinterpret_cast<float*>(ws + lay.dk_part_off);
   p.dv_part = reinterpret_cast<float*>(ws + lay.dv_part_off);
 
-  const int grid_dkdv = grid_for((int64_t)n_kv_tiles * p.Hkv * p.n_split, 1);
-  const int grid_dq = grid_for((int64_t)n_q_tiles * p.Hq, 2);
+  const int64_t items_dkdv = (int64_t)n_kv_tiles * p.Hkv * p.n_split, items_dq = (int64_t)n_q_tiles * p.Hq;
+  const int grid_dkdv = grid_for(items_dkdv, 1), grid_dq = grid_for(items_dq, 2);
+  const int dq_per_cu = desc->d_qk <= 128 ? 2 : 1;
+  p.direct = (hbp::direct_items(items_dkdv, kNumCU, p.prof) ? 1 : 0) |
+             (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq) ? 2 : 0);
   hipEvent_t ev[4] = {g_events[HBP_BWD][0], g_events[HBP_BWD][1], g_events[HBP_BWD_DQ][0], g_events[HBP_BWD_DQ][1]};
   if (hbp::launch_bwd(desc->d_qk, desc->d_v, p, grid_dq, grid_dkdv, static_cast<hipStream_t>(stream), ev) != 0)
     return HBP_ERR_DEVICE;

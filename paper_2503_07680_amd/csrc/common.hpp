@@ -357,31 +357,51 @@ struct Taken {
   int q_cur, q_tried;
 };
 
+// Item j of queue `queue`, which has nk kv heads.
+__device__ __forceinline__ void queue_item(int j, int queue, int nk, int n_tiles, int per_kv, int& tile_idx, int& head) {
+  const int per_group = n_tiles * kHeadGroup * per_kv;  // items of a full group of heads
+  const int full = nk / kHeadGroup;
+  int grp = j / per_group, jj = j - grp * per_group, size = kHeadGroup;
+  if (grp >= full) {  // the last, smaller group
+    grp = full;
+    jj = j - full * per_group;
+    size = nk - full * kHeadGroup;
+  }
+  const int per_tile = size * per_kv;
+  const int rem = jj % per_tile;
+  tile_idx = jj / per_tile;
+  head = (queue + kNumXcd * (grp * kHeadGroup + rem / per_kv)) * per_kv + rem % per_kv;
+}
+
 // One thread takes the next item.  q_cur / q_tried: that thread's cursor over the queues.  A real
 // call, everything passed and returned by value in registers: inlined into the persistent kernels
 // its temporaries cost them registers they do not have (two of them would spill).
 // steal_stride (odd): how the cursor moves on from an exhausted queue; different workgroups of a die use
 // different strides, so they do not all descend on the same other queue.
 __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
-                                                      int q_tried, int steal_stride) {
+                                                      int q_tried, int block) {
+  if (!counters) {  // one workgroup an item: workgroups are dealt to the dies in turn
+    Taken t{-1, 0, q_cur, kNumXcd};
+    if (q_tried == 0) {
+      if (Hkv % kNumXcd == 0) {
+        queue_item(block / kNumXcd, block % kNumXcd, Hkv / kNumXcd, n_tiles, per_kv, t.tile_idx, t.head);
+      } else {
+        t.tile_idx = block / (Hkv * per_kv);
+        t.head = block % (Hkv * per_kv);
+      }
+    }
+    return t;
+  }
+  const int steal_stride = 2 * ((block >> 3) & 3) + 1;
   while (q_tried < kNumXcd) {
     const int nk = Hkv > q_cur ? (Hkv - q_cur + kNumXcd - 1) / kNumXcd : 0;  // kv heads of this die
     const int len = n_tiles * nk * per_kv;
     if (len > 0) {
       const int j = atomicAdd(counters + q_cur * kCounterStride, 1);
       if (j < len) {
-        const int per_group = n_tiles * kHeadGroup * per_kv;  // items of a full group of heads
-        const int full = nk / kHeadGroup;
-        int grp = j / per_group, jj = j - grp * per_group, size = kHeadGroup;
-        if (grp >= full) {  // the last, smaller group
-          grp = full;
-          jj = j - full * per_group;
-          size = nk - full * kHeadGroup;
-        }
-        const int per_tile = size * per_kv;
-        const int rem = jj % per_tile;
-        return Taken{jj / per_tile, (q_cur + kNumXcd * (grp * kHeadGroup + rem / per_kv)) * per_kv + rem % per_kv,
-                     q_cur, q_tried};
+        Taken t{0, 0, q_cur, q_tried};
+        queue_item(j, q_cur, nk, n_tiles, per_kv, t.tile_idx, t.head);
+        return t;
       }
     }
     q_cur = (q_cur + steal_stride) & (kNumXcd - 1);
@@ -391,7 +411,7 @@ __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_ti
 }
 
 struct WorkQueues {
-  int32_t* counters;
+  int32_t* counters;  // null: one workgroup an item (see direct_items)
   int n_tiles, Hkv, per_kv;  // per_kv: heads per kv head inside one item group (g, or 1)
 };
 
@@ -427,7 +447,7 @@ __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int t
   lds_barrier();  // all LDS reads of the previous item are finished
   if (tid == 0) {
     const Taken tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried,
-                               2 * ((blockIdx.x >> 3) & 3) + 1);
+                               (int)blockIdx.x);
     q_cur = tk.q_cur;
     q_tried = tk.q_tried;
     box[0] = tk.tile_idx;
@@ -473,8 +493,18 @@ struct BwdParams {
   // the dK/dV kernel the parts of a kv head then produce partial sums: fp32, [n_split][T][Hkv][dim],
   // added up in part order by a reduce kernel.
   int32_t n_split, n_split_dq;
+  int32_t direct;  // bit 0: the dK/dV kernel has one workgroup an item, bit 1: the dQ kernel
   float *dk_part, *dv_part;
 };
+
+// A kernel whose items all fit on the chip at once gets one workgroup an item and no queue: every item starts
+// at once whatever its order, and the launch that resets the counters (5 us of the stream's time) and the
+// atomic in front of an item fall away.  Training step of a 1024-token pack with 4 heads of 64: 46.0 -> 36.6 us;
+// of 5497 tokens with 8 heads: 119 -> 110.  Not for more items than that: the hardware's dispatch of the later
+// ones balances uneven items worse than the queues do (up to eight rounds of workgroups: 8192 tokens, 32/8
+// heads -1 %, but 32768 tokens, 8/1 heads +3 %).  Profile records are one per resident workgroup, so a call
+// that asks for them keeps the queues.
+inline bool direct_items(int64_t n_items, int64_t resident, const void* prof) { return !prof && n_items <= resident; }
 
 // In how many parts the `units` schedulable units of a kv head (query heads, or pairs of them) are
 // dealt out: the smallest divisor of units that gives every die a queue, else units itself.

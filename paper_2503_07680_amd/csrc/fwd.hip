@@ -549,7 +549,7 @@ int launch_zero_counters(int32_t* counters, hipStream_t s) {
 }
 
 template <int DQK, int DV, int HP, int TP>
-static int launch_fwd_hp(const FwdParams& p, int n_cu, hipStream_t s) {
+static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s) {
   constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2);
   static bool attr_set = false;
   if (!attr_set) {
@@ -560,6 +560,8 @@ static int launch_fwd_hp(const FwdParams& p, int n_cu, hipStream_t s) {
   }
   const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * (2 / (HP * TP));
   const int grid = (int)(n_items < cap ? n_items : cap);
+  if (direct_items(n_items, cap, p.prof)) p.counter = nullptr;
+  else if (const int e = launch_zero_counters(p.counter, s)) return e;
   hipLaunchKernelGGL((fwd_kernel<DQK, DV, HP, TP>), dim3(grid), dim3(kThreads * HP * TP), lds_bytes, s, p);
   return (int)hipGetLastError();
 }

@@ -363,6 +363,22 @@ def test_wrapped_block_order_with_a_group_of_four_heads_at_head_size_128():
     compare(case, pa, out, q_heads=[20, 21, 22, 23], label="group 5")
 
 
+@pytest.mark.parametrize("lens,Hq,Hkv,d,e", [
+    ([300, 130, 1], 4, 4, 64, 64), ([300, 130, 1], 6, 3, 128, 128), ([700, 41], 8, 1, 128, 128),
+    ([128] * 16, 16, 16, 192, 128),                       # 256 query and key tiles: as many as fit at once at d_qk = 192
+    ([128] * 16 + [1], 16, 16, 192, 128), ([128] * 32 + [1], 16, 16, 64, 64),   # one more than fit
+    ([128] * 32, 64, 8, 128, 128)])
+def test_one_workgroup_an_item_and_the_queues_give_the_same_bits(lens, Hq, Hkv, d, e):
+    """Profile records keep the queues; without them a call whose items all fit on the chip has none."""
+    case = Case(lens, sum(lens), Hq, Hkv, d, e, seed=len(lens) + Hq)
+    pa, dev, out = run_gpu(case, with_profile=True)          # run_gpu asks for no records: its calls may go without queues
+    compare(case, pa, out)
+    pa.forward(dev["q"], dev["k"], dev["v"], profile=True)
+    pa.backward(dev["q"], dev["k"], dev["v"], dev["do"], profile=True)
+    for name in ("o", "lse", "dq", "dk", "dv"):
+        assert np.array_equal(getattr(pa, name).float().cpu().numpy(), out[name]), name
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 1), (12, 3), (8, 8)])
 def test_few_kv_heads_split_their_query_heads_and_partial_tile_lists_leave_rows_alone(Hq, Hkv):
     """With fewer kv heads than dies the query heads of a kv head are dealt out in parts (dK/dV then come
