@@ -114,8 +114,9 @@ hbp_status hbp_tile_rows(int32_t d_qk, int32_t d_v, int32_t which, int32_t* rows
 hbp_status hbp_fwd_tile_rows(const hbp_attn_desc* desc, int32_t* rows_out);
 
 /* Bytes of device workspace a call needs (256-byte aligned base required).
- * which = HBP_FWD or HBP_BWD.  Forward: the scheduler's per-die queue counters.  Backward: two
- * sets of counters, the per-row D = rowsum(dO*O) and LSE*log2(e), both [Hq,T] fp32; and, with
+ * which = HBP_FWD or HBP_BWD.  Forward: the scheduler's per-die queue counters and the order in which
+ * the tiles are taken.  Backward: two
+ * sets of counters, that order, the per-row D = rowsum(dO*O) and LSE*log2(e), both [Hq,T] fp32; and, with
  * fewer than 8 kv heads, fp32 partial sums of dK and dV, [parts][T][Hkv][d_qk + d_v]: the query
  * heads of a kv head are then dealt out in `parts` runs (the smallest divisor of Hq/Hkv with
  * Hkv * parts >= 8, else Hq/Hkv) that are separate work items, and a reduce kernel adds the parts
@@ -151,7 +152,7 @@ hbp_status hbp_profile_capacity(const hbp_attn_desc* desc, int32_t which, int32_
  * q,k,v,o,lse,cu_seqlens,q_tiles,workspace,profile: DEVICE.  desc: HOST.
  * q_tiles: the HBP_TILES_QUERY list of hbp_pack_plan made with hbp_tile_rows(..., HBP_FWD), or
  * with desc->fwd_tile_rows rows when that is set;
- * items are served longest first by a persistent grid.  Tiles that are malformed (outside
+ * items are served longest first (most key tiles) by a persistent grid.  Tiles that are malformed (outside
  * their sample, longer than the tile size) are skipped, never dereferenced.
  * Rows of O/LSE not covered by any tile are left untouched.  n_q_tiles == 0 or T == 0: no-op.
  * Errors: INVALID_ARG (null pointers, negative counts, n_q_tiles * n_q_heads above INT32_MAX, a

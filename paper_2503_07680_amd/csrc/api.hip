@@ -9,7 +9,9 @@
 namespace {
 
 constexpr int kNumCU = 256;          // MI355X: 8 accelerator dies x 32 compute units
-constexpr size_t kCounterBytes = 2048;  // two sets of 8 per-die counters, 128 bytes apart
+constexpr size_t kCounterBytes = 2048;  // two sets of 8 per-die counters, 64 bytes apart, and a tile order
+constexpr size_t kSetBytes = hbp::kNumXcd * hbp::kCounterStride * sizeof(int32_t);
+static_assert(2 * kSetBytes + hbp::kOrderTiles * sizeof(uint16_t) <= kCounterBytes, "counters and order fit");
 constexpr int64_t kMaxTokenStride = int64_t{1} << 22;  // elements; see check_desc
 constexpr int kTileRows = 128;       // rows per query / key tile of every kernel (the forward also takes 256)
 
@@ -288,6 +290,7 @@ extern "C" hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void*
   p.v_st = st.v_st; p.v_sh = st.v_sh; p.o_st = st.o_st; p.o_sh = st.o_sh;
   p.scale_log2 = resolve_scale(desc) * 1.4426950408889634f;
   p.counter = static_cast<int32_t*>(workspace);
+  p.order = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + 2 * kSetBytes);
   p.prof = profile;
   p.n_split = hbp::heads_split(p.Hkv, p.g % 2 == 0 ? p.g / 2 : p.g);  // even groups: items are pairs of heads
 
@@ -364,7 +367,7 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   }
   char* ws = static_cast<char*>(workspace);
   p.counter = reinterpret_cast<int32_t*>(ws);
-  p.counter_dq = reinterpret_cast<int32_t*>(ws + 1024);
+  p.counter_dq = reinterpret_cast<int32_t*>(ws + kSetBytes);
   p.D = reinterpret_cast<float*>(ws + lay.d_off);
   p.lse2 = reinterpret_cast<float*>(ws + lay.lse2_off);
   p.cu = cu_seqlens;
@@ -393,6 +396,8 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   const int dq_per_cu = desc->d_qk <= 128 ? 2 : 1;
   p.direct = (hbp::direct_items(items_dkdv, kNumCU, p.prof) ? 1 : 0) |
              (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq) ? 2 : 0);
+  if (!(p.direct & 2) && n_q_tiles <= hbp::kOrderTiles)
+    p.order_dq = reinterpret_cast<uint16_t*>(ws + 2 * kSetBytes);
   hipEvent_t ev[4] = {g_events[HBP_BWD][0], g_events[HBP_BWD][1], g_events[HBP_BWD_DQ][0], g_events[HBP_BWD_DQ][1]};
   if (hbp::launch_bwd(desc->d_qk, desc->d_v, p, grid_dq, grid_dkdv, static_cast<hipStream_t>(stream), ev) != 0)
     return HBP_ERR_DEVICE;

@@ -319,7 +319,8 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   uint32_t n_done = 0;
   uint64_t t_first = 0, t_last = 0, t_busy = 0;
 
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split};
+  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split,
+                      load_order(p.order, smem + 2 * K_TILE + 2 * V_TILE, tid)};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
@@ -539,18 +540,16 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   }
 }
 
-__global__ void zero_counters_kernel(int32_t* c) {
-  if (threadIdx.x < kNumXcd) c[threadIdx.x * kCounterStride] = 0;
-}
-
-int launch_zero_counters(int32_t* counters, hipStream_t s) {
-  hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, counters);
-  return (int)hipGetLastError();
+// in front of the forward: resets the queues and sorts the tiles
+__global__ __launch_bounds__(kOrderTiles) void fwd_queue_kernel(const FwdParams p) {
+  __shared__ uint16_t keys[kOrderTiles];
+  if (threadIdx.x < kNumXcd) p.counter[threadIdx.x * kCounterStride] = 0;
+  if (p.order) order_tiles<kOrderTiles>(p.tiles, p.n_tiles, p.cu, p.n_samples, p.order, keys, threadIdx.x);
 }
 
 template <int DQK, int DV, int HP, int TP>
 static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s) {
-  constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2);
+  constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2) + kOrderLds;
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute((const void*)fwd_kernel<DQK, DV, HP, TP>,
@@ -561,7 +560,12 @@ static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s) {
   const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * (2 / (HP * TP));
   const int grid = (int)(n_items < cap ? n_items : cap);
   if (direct_items(n_items, cap, p.prof)) p.counter = nullptr;
-  else if (const int e = launch_zero_counters(p.counter, s)) return e;
+  if (!p.counter || p.n_tiles > kOrderTiles) p.order = nullptr;
+  if (p.counter) {
+    hipLaunchKernelGGL(fwd_queue_kernel, dim3(1), dim3(kOrderTiles), 0, s, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
   hipLaunchKernelGGL((fwd_kernel<DQK, DV, HP, TP>), dim3(grid), dim3(kThreads * HP * TP), lds_bytes, s, p);
   return (int)hipGetLastError();
 }

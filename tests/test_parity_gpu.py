@@ -379,6 +379,17 @@ def test_one_workgroup_an_item_and_the_queues_give_the_same_bits(lens, Hq, Hkv, 
         assert np.array_equal(getattr(pa, name).float().cpu().numpy(), out[name]), name
 
 
+@pytest.mark.parametrize("n_short,Hq,Hkv,d,e", [(510, 4, 4, 64, 64), (511, 4, 4, 64, 64), (330, 8, 2, 128, 128),
+                                                (330, 16, 16, 192, 128)])
+def test_tiles_taken_in_order_of_their_key_tiles(n_short, Hq, Hkv, d, e):
+    """Queues, with 512 tiles (the most that are sorted), with one more, and with tails of one row whose place in
+    the worklist (by pairs) is far from their place by key tiles."""
+    lens = [3] * n_short + [129 if n_short > 500 else 641]
+    case = Case(lens, sum(lens), Hq, Hkv, d, e, seed=n_short)
+    pa, _, _ = full(case)
+    assert len(pa.q_tiles) == n_short + (2 if n_short > 500 else 6)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 1), (12, 3), (8, 8)])
 def test_few_kv_heads_split_their_query_heads_and_partial_tile_lists_leave_rows_alone(Hq, Hkv):
     """With fewer kv heads than dies the query heads of a kv head are dealt out in parts (dK/dV then come
