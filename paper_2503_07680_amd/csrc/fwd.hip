@@ -547,9 +547,14 @@ __global__ __launch_bounds__(kOrderTiles) void fwd_queue_kernel(const FwdParams 
   if (p.order) order_tiles<kOrderTiles>(p.tiles, p.n_tiles, p.cu, p.n_samples, p.order, keys, threadIdx.x);
 }
 
+constexpr int kLdsBytes = 160 * 1024;  // of a compute unit
 template <int DQK, int DV, int HP, int TP>
-static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s) {
-  constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2) + kOrderLds;
+static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  // The order has no room where two workgroups' tiles fill a compute unit's LDS (d_qk = 192, 128-row tiles and
+  // odd groups): with it only one of the two would fit.
+  constexpr int kTileLds = 2 * 64 * (DQK * 2 + DV * 2), kPerCu = 2 / (HP * TP);
+  constexpr bool kSorted = kPerCu * (kTileLds + kOrderLds) <= kLdsBytes;
+  constexpr int lds_bytes = kTileLds + (kSorted ? kOrderLds : 0);
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute((const void*)fwd_kernel<DQK, DV, HP, TP>,
@@ -557,35 +562,36 @@ static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s) {
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * (2 / (HP * TP));
+  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * kPerCu;
   const int grid = (int)(n_items < cap ? n_items : cap);
   if (direct_items(n_items, cap, p.prof)) p.counter = nullptr;
-  if (!p.counter || p.n_tiles > kOrderTiles) p.order = nullptr;
+  if (!kSorted || !p.counter || p.n_tiles > kOrderTiles) p.order = nullptr;
   if (p.counter) {
     hipLaunchKernelGGL(fwd_queue_kernel, dim3(1), dim3(kOrderTiles), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }
+  if (ev0 && hipEventRecord(ev0, s) != hipSuccess) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL((fwd_kernel<DQK, DV, HP, TP>), dim3(grid), dim3(kThreads * HP * TP), lds_bytes, s, p);
-  return (int)hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess && ev1 && hipEventRecord(ev1, s) != hipSuccess) return (int)hipErrorInvalidValue;
+  return (int)e;
 }
 // tile_rows: rows per query tile of the worklist, 128 or (odd group sizes only) 256
 template <int DQK, int DV>
-static int launch_fwd_t(const FwdParams& p, int tile_rows, int n_cu, hipStream_t s) {
-  if (p.g % 2 == 0) return tile_rows == 128 ? launch_fwd_hp<DQK, DV, 2, 1>(p, n_cu, s) : (int)hipErrorInvalidValue;
-  return tile_rows == 256 ? launch_fwd_hp<DQK, DV, 1, 2>(p, n_cu, s) : launch_fwd_hp<DQK, DV, 1, 1>(p, n_cu, s);
+static int launch_fwd_t(const FwdParams& p, int tile_rows, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (p.g % 2 == 0)
+    return tile_rows == 128 ? launch_fwd_hp<DQK, DV, 2, 1>(p, n_cu, s, ev0, ev1) : (int)hipErrorInvalidValue;
+  return tile_rows == 256 ? launch_fwd_hp<DQK, DV, 1, 2>(p, n_cu, s, ev0, ev1)
+                          : launch_fwd_hp<DQK, DV, 1, 1>(p, n_cu, s, ev0, ev1);
 }
 
 int launch_fwd(int d_qk, int d_v, const FwdParams& p, int tile_rows, int n_cu, hipStream_t s,
                hipEvent_t ev0, hipEvent_t ev1) {
-  if (ev0 && hipEventRecord(ev0, s) != hipSuccess) return (int)hipErrorInvalidValue;
-  int e;
-  if (d_qk == 64 && d_v == 64) e = launch_fwd_t<64, 64>(p, tile_rows, n_cu, s);
-  else if (d_qk == 128 && d_v == 128) e = launch_fwd_t<128, 128>(p, tile_rows, n_cu, s);
-  else if (d_qk == 192 && d_v == 128) e = launch_fwd_t<192, 128>(p, tile_rows, n_cu, s);
-  else return (int)hipErrorInvalidValue;
-  if (e == 0 && ev1 && hipEventRecord(ev1, s) != hipSuccess) return (int)hipErrorInvalidValue;
-  return e;
+  if (d_qk == 64 && d_v == 64) return launch_fwd_t<64, 64>(p, tile_rows, n_cu, s, ev0, ev1);
+  if (d_qk == 128 && d_v == 128) return launch_fwd_t<128, 128>(p, tile_rows, n_cu, s, ev0, ev1);
+  if (d_qk == 192 && d_v == 128) return launch_fwd_t<192, 128>(p, tile_rows, n_cu, s, ev0, ev1);
+  return (int)hipErrorInvalidValue;
 }
 
 }  // namespace hbp
