@@ -394,9 +394,9 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   const int64_t items_dkdv = (int64_t)n_kv_tiles * p.Hkv * p.n_split, items_dq = (int64_t)n_q_tiles * p.Hq;
   const int grid_dkdv = grid_for(items_dkdv, 1), grid_dq = grid_for(items_dq, 2);
   const int dq_per_cu = desc->d_qk <= 128 ? 2 : 1;
-  p.direct = (hbp::direct_items(items_dkdv, kNumCU, p.prof) ? 1 : 0) |
-             (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq) ? 2 : 0);
-  if (!(p.direct & 2) && n_q_tiles <= hbp::kOrderTiles)
+  if (hbp::direct_items(items_dkdv, kNumCU, p.prof)) p.counter = nullptr;
+  if (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq)) p.counter_dq = nullptr;
+  if (p.counter_dq && n_q_tiles <= hbp::kOrderTiles)
     p.order_dq = reinterpret_cast<uint16_t*>(ws + 2 * kSetBytes);
   hipEvent_t ev[4] = {g_events[HBP_BWD][0], g_events[HBP_BWD][1], g_events[HBP_BWD_DQ][0], g_events[HBP_BWD_DQ][1]};
   if (hbp::launch_bwd(desc->d_qk, desc->d_v, p, grid_dq, grid_dkdv, static_cast<hipStream_t>(stream), ev) != 0)

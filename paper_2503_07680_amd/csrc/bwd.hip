@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
   const uint32_t k_stride_b = (uint32_t)p.k_st * 2, v_stride_b = (uint32_t)p.v_st * 2;
 
   ProfAcc pa;
-  const WorkQueues wq{p.direct & 2 ? nullptr : p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / p.n_split_dq,
+  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / p.n_split_dq,
                       load_order(p.order_dq, smem + 2 * K_TILE + 2 * V_TILE, tid)};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
   // are cut into n_split runs of g_item heads, each an item of its own.
-  const WorkQueues wq{p.direct & 1 ? nullptr : p.counter, p.n_tiles, p.Hkv * p.n_split, 1, 0};
+  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1, 0};
   const int g_item = p.g / p.n_split;
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
@@ -863,8 +863,8 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
   if (blockIdx.x == 0) {
     __shared__ uint16_t keys[kOrderTiles];
     if (threadIdx.x < kNumXcd) {
-      p.counter[threadIdx.x * kCounterStride] = 0;
-      p.counter_dq[threadIdx.x * kCounterStride] = 0;
+      if (p.counter) p.counter[threadIdx.x * kCounterStride] = 0;
+      if (p.counter_dq) p.counter_dq[threadIdx.x * kCounterStride] = 0;
     }
     if (p.order_dq) order_tiles<kThreads>(p.q_tiles, p.n_q_tiles, p.cu, p.n_samples, p.order_dq, keys, threadIdx.x);
   }

@@ -532,9 +532,8 @@ struct BwdParams {
   // the dK/dV kernel the parts of a kv head then produce partial sums: fp32, [n_split][T][Hkv][dim],
   // added up in part order by a reduce kernel.
   int32_t n_split, n_split_dq;
-  uint16_t* order_dq;  // [kOrderTiles] order of the query tiles in the dQ kernel, null: the worklist's
-  int32_t direct;  // bit 0: the dK/dV kernel has one workgroup an item, bit 1: the dQ kernel
   float *dk_part, *dv_part;
+  uint16_t* order_dq;  // [kOrderTiles] order of the query tiles in the dQ kernel, null: the worklist's
 };
 
 // A kernel whose items all fit on the chip at once gets one workgroup an item and no queue: every item starts
