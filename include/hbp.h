@@ -81,6 +81,19 @@ hbp_status hbp_pack_plan(const int32_t* lengths, int32_t n_lengths, int32_t pack
                          hbp_tile* tiles, int64_t* tile_cost, int32_t tile_cap,
                          int32_t* n_tiles_out, int64_t* pack_cost_out);
 
+/*
+ * hbp_order_query_tiles — host only.  The query tiles of a plan in the order in which they are best served:
+ * most 64-key blocks in front of the tile's last row first, the given order among equals.
+ *
+ * The forward and the dQ kernel serve a list as it is.  A query tile takes them as long as it has key blocks,
+ * however few rows it has: the last tile of a sample just over a multiple of the tile size has hardly any pairs,
+ * so the plan's order (by pairs) serves it last and it ends the launch alone.  Results do not depend on the order.
+ * ordered: room for n_tiles, not overlapping tiles.  Errors: INVALID_ARG (null pointers with n_tiles > 0, negative
+ * counts, a tile whose sample or row_end lies outside the pack), NO_MEMORY; nothing is written then.
+ */
+hbp_status hbp_order_query_tiles(const int32_t* cu_seqlens, int32_t n_samples, const hbp_tile* tiles,
+                                 int32_t n_tiles, hbp_tile* ordered);
+
 /* Problem description shared by forward and backward. */
 typedef struct {
   int32_t total_tokens; /* T = cu_seqlens[n_samples]                                   */
@@ -114,9 +127,8 @@ hbp_status hbp_tile_rows(int32_t d_qk, int32_t d_v, int32_t which, int32_t* rows
 hbp_status hbp_fwd_tile_rows(const hbp_attn_desc* desc, int32_t* rows_out);
 
 /* Bytes of device workspace a call needs (256-byte aligned base required).
- * which = HBP_FWD or HBP_BWD.  Forward: the scheduler's per-die queue counters and the order in which
- * the tiles are taken.  Backward: two
- * sets of counters, that order, the per-row D = rowsum(dO*O) and LSE*log2(e), both [Hq,T] fp32; and, with
+ * which = HBP_FWD or HBP_BWD.  Forward: the scheduler's per-die queue counters.  Backward: two
+ * sets of counters, the per-row D = rowsum(dO*O) and LSE*log2(e), both [Hq,T] fp32; and, with
  * fewer than 8 kv heads, fp32 partial sums of dK and dV, [parts][T][Hkv][d_qk + d_v]: the query
  * heads of a kv head are then dealt out in `parts` runs (the smallest divisor of Hq/Hkv with
  * Hkv * parts >= 8, else Hq/Hkv) that are separate work items, and a reduce kernel adds the parts
@@ -152,7 +164,8 @@ hbp_status hbp_profile_capacity(const hbp_attn_desc* desc, int32_t which, int32_
  * q,k,v,o,lse,cu_seqlens,q_tiles,workspace,profile: DEVICE.  desc: HOST.
  * q_tiles: the HBP_TILES_QUERY list of hbp_pack_plan made with hbp_tile_rows(..., HBP_FWD), or
  * with desc->fwd_tile_rows rows when that is set;
- * items are served longest first (most key tiles) by a persistent grid.  Tiles that are malformed (outside
+ * items are served in the list's order by a persistent grid (best: that of hbp_order_query_tiles).
+ * Tiles that are malformed (outside
  * their sample, longer than the tile size) are skipped, never dereferenced.
  * Rows of O/LSE not covered by any tile are left untouched.  n_q_tiles == 0 or T == 0: no-op.
  * Errors: INVALID_ARG (null pointers, negative counts, n_q_tiles * n_q_heads above INT32_MAX, a
@@ -178,8 +191,8 @@ hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void* q, const v
  * reduce kernel when there are fewer than 8 kv heads, see hbp_workspace_bytes) and the persistent
  * query-tile kernel (dQ; it recomputes S and dP).  No atomics: every output element is written
  * once, results are bit-stable.
- * q_tiles: the HBP_TILES_QUERY list made with hbp_tile_rows(..., HBP_FWD) (the forward's list
- * unless that was planned with a larger desc->fwd_tile_rows, which the backward ignores);
+ * q_tiles: the HBP_TILES_QUERY list made with hbp_tile_rows(..., HBP_FWD), served in its order (the
+ * forward's list, hbp_order_query_tiles included, unless that was planned with a larger desc->fwd_tile_rows, which the backward ignores);
  * kv_tiles: the HBP_TILES_KEY list made with hbp_tile_rows(..., HBP_BWD).
  * o and lse are the forward's outputs.  dK/dV rows covered by a key tile and dQ rows covered by a
  * query tile are written; others are left untouched.  profile / profile_dq: optional records of

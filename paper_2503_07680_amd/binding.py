@@ -14,7 +14,7 @@ import numpy as np
 HBP_FWD, HBP_BWD, HBP_BWD_DQ = 0, 1, 2
 HBP_TILES_QUERY, HBP_TILES_KEY = 0, 1
 
-EXPORTED_SYMBOLS = ["hbp_status_string", "hbp_pack_plan", "hbp_tile_rows", "hbp_fwd_tile_rows", "hbp_workspace_bytes",
+EXPORTED_SYMBOLS = ["hbp_status_string", "hbp_pack_plan", "hbp_order_query_tiles", "hbp_tile_rows", "hbp_fwd_tile_rows", "hbp_workspace_bytes",
                     "hbp_profile_capacity", "hbp_varlen_attn_fwd", "hbp_varlen_attn_bwd", "hbp_varlen_attn_bwd_static",
                     "hbp_set_kernel_events", "hbp_mfma_probe", "hbp_balance_packing",
                     "hbp_packed_ce_workspace_bytes", "hbp_packed_ce", "hbp_auto_select"]
@@ -94,6 +94,8 @@ def load_library():
     lib.hbp_status_string.argtypes = [i32]
     lib.hbp_pack_plan.restype = i32
     lib.hbp_pack_plan.argtypes = [i32p, i32, i32, i32, i32, i32p, i32, i32p, i32p, vp, i64p, i32, i32p, i64p]
+    lib.hbp_order_query_tiles.restype = i32
+    lib.hbp_order_query_tiles.argtypes = [vp, i32, vp, i32, vp]
     lib.hbp_tile_rows.restype = i32
     lib.hbp_tile_rows.argtypes = [i32, i32, i32, i32p]
     lib.hbp_fwd_tile_rows.restype = i32
@@ -169,6 +171,19 @@ def hbp_pack_plan(lengths: Sequence[int], pack_len: int, tile_rows: int, kind: i
     if st != 0:
         raise HbpError(st, "hbp_pack_plan")
     return cu, int(nc.value), tiles, cost, int(pc.value)
+
+
+def hbp_order_query_tiles(cu_seqlens: np.ndarray, tiles: np.ndarray) -> np.ndarray:
+    """A plan's query tiles (int32 [n_tiles, 4]) in the order in which they are best served; cu_seqlens and tiles
+    as hbp_pack_plan returns them.  Host only."""
+    cu = np.ascontiguousarray(cu_seqlens, dtype=np.int32)
+    tiles = np.ascontiguousarray(tiles, dtype=np.int32)
+    out = np.empty_like(tiles)
+    at = [x.__array_interface__["data"][0] for x in (cu, tiles, out)]
+    st = load_library().hbp_order_query_tiles(at[0], cu.size - 1, at[1], len(tiles), at[2])
+    if st != 0:
+        raise HbpError(st, "hbp_order_query_tiles")
+    return out
 
 
 def hbp_balance_packing(lengths: Sequence[int], group_lens: Sequence[int], packs_per_batch: Sequence[int],

@@ -9,9 +9,9 @@
 namespace {
 
 constexpr int kNumCU = 256;          // MI355X: 8 accelerator dies x 32 compute units
-constexpr size_t kCounterBytes = 2048;  // two sets of 8 per-die counters, 64 bytes apart, and a tile order
 constexpr size_t kSetBytes = hbp::kNumXcd * hbp::kCounterStride * sizeof(int32_t);
-static_assert(2 * kSetBytes + hbp::kOrderTiles * sizeof(uint16_t) <= kCounterBytes, "counters and order fit");
+constexpr size_t kCounterBytes = 2 * kSetBytes;  // two sets of 8 per-die counters, 128 bytes apart
+static_assert(kCounterBytes == 2048, "callers keep workspaces of this size");
 constexpr int64_t kMaxTokenStride = int64_t{1} << 22;  // elements; see check_desc
 constexpr int kTileRows = 128;       // rows per query / key tile of every kernel (the forward also takes 256)
 
@@ -290,7 +290,6 @@ extern "C" hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void*
   p.v_st = st.v_st; p.v_sh = st.v_sh; p.o_st = st.o_st; p.o_sh = st.o_sh;
   p.scale_log2 = resolve_scale(desc) * 1.4426950408889634f;
   p.counter = static_cast<int32_t*>(workspace);
-  p.order = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + 2 * kSetBytes);
   p.prof = profile;
   p.n_split = hbp::heads_split(p.Hkv, p.g % 2 == 0 ? p.g / 2 : p.g);  // even groups: items are pairs of heads
 
@@ -396,8 +395,6 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   const int dq_per_cu = desc->d_qk <= 128 ? 2 : 1;
   if (hbp::direct_items(items_dkdv, kNumCU, p.prof)) p.counter = nullptr;
   if (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq)) p.counter_dq = nullptr;
-  if (p.counter_dq && n_q_tiles <= hbp::kOrderTiles)
-    p.order_dq = reinterpret_cast<uint16_t*>(ws + 2 * kSetBytes);
   hipEvent_t ev[4] = {g_events[HBP_BWD][0], g_events[HBP_BWD][1], g_events[HBP_BWD_DQ][0], g_events[HBP_BWD_DQ][1]};
   if (hbp::launch_bwd(desc->d_qk, desc->d_v, p, grid_dq, grid_dkdv, static_cast<hipStream_t>(stream), ev) != 0)
     return HBP_ERR_DEVICE;

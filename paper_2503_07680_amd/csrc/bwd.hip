@@ -110,8 +110,7 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
   const uint32_t k_stride_b = (uint32_t)p.k_st * 2, v_stride_b = (uint32_t)p.v_st * 2;
 
   ProfAcc pa;
-  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / p.n_split_dq,
-                      load_order(p.order_dq, smem + 2 * K_TILE + 2 * V_TILE, tid)};
+  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / p.n_split_dq};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
@@ -423,11 +422,11 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   // Pads the code in front of the loops: where the step loop (16.5 KB) lies within a 64-byte instruction cache line
   // is worth 3 % of the launch.  131072 tokens, 64/8 heads, d = 128, ms: loop at byte 40: 288.0, at 0: 292.3,
   // at 16: 294.6, at 24: 294.6, at 56: 294.5.  The launch's time is checked again whenever the code in front changes.
-  if constexpr (DQK == 128) asm volatile(".rept 10\n s_nop 0\n .endr");
+  if constexpr (DQK == 128) asm volatile(".rept 11\n s_nop 0\n .endr");
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
   // are cut into n_split runs of g_item heads, each an item of its own.
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1, 0};
+  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
   const int g_item = p.g / p.n_split;
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
@@ -859,18 +858,13 @@ size_t bwd_partial_floats(int T, int Hkv, int g, int dim) {
   return n_split > 1 ? (size_t)n_split * (size_t)T * (size_t)Hkv * (size_t)dim : 0;
 }
 
-// D[h,r] = sum_x dO[r,h,x] O[r,h,x], LSE2 = LSE*log2(e); resets both scheduler counters and
-// sorts the query tiles for the dQ kernel.
+// D[h,r] = sum_x dO[r,h,x] O[r,h,x], LSE2 = LSE*log2(e); resets both scheduler counters.
 template <int DV>
 __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p) {
   constexpr int LPR = DV / 8;  // lanes per (row, head): 16 bytes of O and dO each
-  if (blockIdx.x == 0) {
-    __shared__ uint16_t keys[kOrderTiles];
-    if (threadIdx.x < kNumXcd) {
-      if (p.counter) p.counter[threadIdx.x * kCounterStride] = 0;
-      if (p.counter_dq) p.counter_dq[threadIdx.x * kCounterStride] = 0;
-    }
-    if (p.order_dq) order_tiles<kThreads>(p.q_tiles, p.n_q_tiles, p.cu, p.n_samples, p.order_dq, keys, threadIdx.x);
+  if (blockIdx.x == 0 && threadIdx.x < kNumXcd) {
+    if (p.counter) p.counter[threadIdx.x * kCounterStride] = 0;
+    if (p.counter_dq) p.counter_dq[threadIdx.x * kCounterStride] = 0;
   }
   const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t rh = gid / LPR;
@@ -898,7 +892,7 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
 
 template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
-  constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2) + kOrderLds;
+  constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
   constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
   static bool attr_set = false;
   if (!attr_set) {

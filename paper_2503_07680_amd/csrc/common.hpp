@@ -346,9 +346,9 @@ __device__ __forceinline__ uint32_t xcc_id_reg() {
 // tiles of each of these heads and share that head's stream (with all of a die's heads innermost,
 // 16 of them for 128 kv heads, only two workgroups would).  A workgroup serves its own die's queue
 // first and then steals from the others, so every item is done whatever the head count and the tail
-// stays balanced.  Counters are 64 bytes apart.
+// stays balanced.  Counters are 128 bytes apart.
 constexpr int kNumXcd = 8;
-constexpr int kCounterStride = 16;  // in int32
+constexpr int kCounterStride = 32;  // in int32
 constexpr int kHeadGroup = 2;  // measured on 128 kv heads: 1 and 2 alike, 4 is 2 % slower, all 16 at once 12 %
 
 struct Taken {
@@ -373,42 +373,13 @@ __device__ __forceinline__ void queue_item(int j, int queue, int nk, int n_tiles
   head = (queue + kNumXcd * (grp * kHeadGroup + rem / per_kv)) * per_kv + rem % per_kv;
 }
 
-// The order in which a queue's tiles are taken, where it is not the worklist's own.  The worklist is sorted by
-// (query, key) pairs; what a query tile costs the forward and the dQ kernel is its number of key tiles, however
-// few rows it has.  The last tile of a sample that is just over a multiple of the tile size has hardly any pairs
-// and as many key tiles as its full neighbour: served last, it alone ended the launch (8192 tokens in 20
-// samples, 32/8 heads: forward 95 us with nine workgroups in ten done at 80, dQ 110 and 95).  So the kernel in
-// front, which resets the counters anyway, also sorts the tiles by key tiles (worklist order among equals).
-// Up to kOrderTiles of them; with more, such a tile is a small part of the launch.
-constexpr int kOrderTiles = 512;
-constexpr int kOrderKeys = 64;  // keys per key tile of both kernels
-
-// Called by all NT threads of one workgroup.  keys: LDS.
-template <int NT>
-__device__ __forceinline__ void order_tiles(const hbp_tile* tiles, int n, const int32_t* cu, int n_samples,
-                                            uint16_t* order, uint16_t (&keys)[kOrderTiles], int tid) {
-  for (int i = tid; i < n; i += NT) {
-    const hbp_tile tl = tiles[i];
-    int blocks = 0;  // a malformed tile: skipped by the kernels
-    if (tl.sample >= 0 && tl.sample < n_samples) blocks = (tl.row_end - cu[tl.sample] + kOrderKeys - 1) / kOrderKeys;
-    keys[i] = (uint16_t)min(max(blocks, 0), 65535);
-  }
-  __syncthreads();
-  for (int i = tid; i < n; i += NT) {
-    const int mine = keys[i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) rank += keys[j] > mine || (keys[j] == mine && j < i);
-    order[rank] = (uint16_t)i;
-  }
-}
-
 // One thread takes the next item.  q_cur / q_tried: that thread's cursor over the queues.  A real
 // call, everything passed and returned by value in registers: inlined into the persistent kernels
 // its temporaries cost them registers they do not have (two of them would spill).
-// steal_stride (odd): how the cursor moves on from an exhausted queue; different workgroups of a die use
-// different strides, so they do not all descend on the same other queue.
+// block: the workgroup's number.  The cursor moves on from an exhausted queue in odd strides; different workgroups
+// of a die use different ones, so they do not all descend on the same other queue.
 __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
-                                                      int q_tried, int block, uint32_t order_lds) {
+                                                      int q_tried, int block) {
   if (!counters) {  // one workgroup an item: workgroups are dealt to the dies in turn
     Taken t{-1, 0, q_cur, kNumXcd};
     if (q_tried == 0) {
@@ -430,7 +401,6 @@ __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_ti
       if (j < len) {
         Taken t{0, 0, q_cur, q_tried};
         queue_item(j, q_cur, nk, n_tiles, per_kv, t.tile_idx, t.head);
-        if (order_lds) t.tile_idx = ((const __attribute__((address_space(3))) uint16_t*)(uintptr_t)order_lds)[t.tile_idx];
         return t;
       }
     }
@@ -443,15 +413,7 @@ __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_ti
 struct WorkQueues {
   int32_t* counters;  // null: one workgroup an item (see direct_items)
   int n_tiles, Hkv, per_kv;  // per_kv: heads per kv head inside one item group (g, or 1)
-  uint32_t order_lds;        // LDS copy of the tiles' order (kOrderTiles entries), 0: the worklist's own
 };
-// brings the order into LDS; the barrier in front of the first item makes it visible
-__device__ __forceinline__ uint32_t load_order(const uint16_t* order, char* lds, int tid) {
-  if (!order) return 0;
-  if (tid < kOrderTiles / 2) ((uint32_t*)lds)[tid] = ((const uint32_t*)order)[tid];
-  return lds_address(lds);
-}
-constexpr int kOrderLds = kOrderTiles * (int)sizeof(uint16_t);
 
 // Workgroup barrier that orders LDS traffic only: waits for this wave's LDS operations, not for its
 // outstanding global stores (the results a previous item is still writing out).
@@ -485,7 +447,7 @@ __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int t
   lds_barrier();  // all LDS reads of the previous item are finished
   if (tid == 0) {
     const Taken tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried,
-                               (int)blockIdx.x, wq.order_lds);
+                               (int)blockIdx.x);
     q_cur = tk.q_cur;
     q_tried = tk.q_tried;
     box[0] = tk.tile_idx;
@@ -509,7 +471,6 @@ struct FwdParams {
   float scale_log2;  // softmax scale * log2(e)
   int32_t* counter;
   hbp_profile_rec* prof;
-  uint16_t* order;   // [kOrderTiles] order of the tiles, null: the worklist's
   int32_t n_split;   // the query heads of a kv head are dealt to the dies in this many parts (see heads_split)
 };
 
@@ -533,7 +494,6 @@ struct BwdParams {
   // added up in part order by a reduce kernel.
   int32_t n_split, n_split_dq;
   float *dk_part, *dv_part;
-  uint16_t* order_dq;  // [kOrderTiles] order of the query tiles in the dQ kernel, null: the worklist's
 };
 
 // A kernel whose items all fit on the chip at once gets one workgroup an item and no queue: every item starts

@@ -1,7 +1,7 @@
 // Forward kernel: causal attention inside each sample of a packed buffer, gfx950.
 //
 // One work item = (query tile, one or two query heads of a kv head).  A persistent grid takes items
-// from per-die queues in worklist order (longest causal cost first).  Per item the workgroup (eight
+// from per-die queues in worklist order (longest first).  Per item the workgroup (eight
 // wavefronts of 32 query rows each: two heads x 128 rows, or one head x 256 rows; four for one head x
 // 128 rows) walks the sample's keys from the sample start to the diagonal.
 //
@@ -319,8 +319,7 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   uint32_t n_done = 0;
   uint64_t t_first = 0, t_last = 0, t_busy = 0;
 
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split,
-                      load_order(p.order, smem + 2 * K_TILE + 2 * V_TILE, tid)};
+  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
@@ -540,21 +539,13 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   }
 }
 
-// in front of the forward: resets the queues and sorts the tiles
-__global__ __launch_bounds__(kOrderTiles) void fwd_queue_kernel(const FwdParams p) {
-  __shared__ uint16_t keys[kOrderTiles];
-  if (threadIdx.x < kNumXcd) p.counter[threadIdx.x * kCounterStride] = 0;
-  if (p.order) order_tiles<kOrderTiles>(p.tiles, p.n_tiles, p.cu, p.n_samples, p.order, keys, threadIdx.x);
+__global__ void zero_counters_kernel(int32_t* c) {
+  if (threadIdx.x < kNumXcd) c[threadIdx.x * kCounterStride] = 0;
 }
 
-constexpr int kLdsBytes = 160 * 1024;  // of a compute unit
 template <int DQK, int DV, int HP, int TP>
 static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  // The order has no room where two workgroups' tiles fill a compute unit's LDS (d_qk = 192, 128-row tiles and
-  // odd groups): with it only one of the two would fit.
-  constexpr int kTileLds = 2 * 64 * (DQK * 2 + DV * 2), kPerCu = 2 / (HP * TP);
-  constexpr bool kSorted = kPerCu * (kTileLds + kOrderLds) <= kLdsBytes;
-  constexpr int lds_bytes = kTileLds + (kSorted ? kOrderLds : 0);
+  constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2);
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute((const void*)fwd_kernel<DQK, DV, HP, TP>,
@@ -562,12 +553,11 @@ static int launch_fwd_hp(FwdParams p, int n_cu, hipStream_t s, hipEvent_t ev0, h
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * kPerCu;
+  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * (2 / (HP * TP));
   const int grid = (int)(n_items < cap ? n_items : cap);
   if (direct_items(n_items, cap, p.prof)) p.counter = nullptr;
-  if (!kSorted || !p.counter || p.n_tiles > kOrderTiles) p.order = nullptr;
   if (p.counter) {
-    hipLaunchKernelGGL(fwd_queue_kernel, dim3(1), dim3(kOrderTiles), 0, s, p);
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, p.counter);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }

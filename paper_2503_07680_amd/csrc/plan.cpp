@@ -103,6 +103,34 @@ static hbp_status hbp_pack_plan_impl(const int32_t* lengths, int32_t n_lengths, 
   return st;
 }
 
+static hbp_status hbp_order_query_tiles_impl(const int32_t* cu, int32_t n_samples, const hbp_tile* tiles,
+                                             int32_t n_tiles, hbp_tile* ordered) {
+  if (n_tiles < 0 || n_samples < 0) return HBP_ERR_INVALID_ARG;
+  if (n_tiles == 0) return HBP_OK;
+  if (!cu || !tiles || !ordered) return HBP_ERR_INVALID_ARG;
+  std::vector<Item> items(n_tiles);
+  for (int32_t i = 0; i < n_tiles; ++i) {
+    const hbp_tile& t = tiles[i];
+    if (t.sample < 0 || t.sample >= n_samples || t.row_end <= cu[t.sample] || t.row_end > cu[t.sample + 1])
+      return HBP_ERR_INVALID_ARG;
+    items[i] = {((int64_t)t.row_end - cu[t.sample] + 63) / 64, t};  // keys in front of the last row, in blocks
+  }
+  std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
+  for (int32_t i = 0; i < n_tiles; ++i) ordered[i] = items[i].t;
+  return HBP_OK;
+}
+
+extern "C" hbp_status hbp_order_query_tiles(const int32_t* cu_seqlens, int32_t n_samples, const hbp_tile* tiles,
+                                            int32_t n_tiles, hbp_tile* ordered) {
+  try {
+    return hbp_order_query_tiles_impl(cu_seqlens, n_samples, tiles, n_tiles, ordered);
+  } catch (const std::bad_alloc&) {
+    return HBP_ERR_NO_MEMORY;
+  } catch (...) {
+    return HBP_ERR_INVALID_ARG;
+  }
+}
+
 // The planner allocates host memory: running out of it is reported, never thrown across the C boundary.
 extern "C" hbp_status hbp_pack_plan(const int32_t* lengths, int32_t n_lengths, int32_t pack_len,
                                     int32_t tile_rows, int32_t kind, int32_t* cu_seqlens,

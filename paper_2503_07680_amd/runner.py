@@ -54,11 +54,20 @@ class PackedAttention:
             self.desc.v_stride_t = n_kv_heads * d_v + self.row_pad
             self.desc.o_stride_t = n_q_heads * d_v + self.row_pad
         dev = self.device
-        self.cu_dev = torch.from_numpy(self.cu).to(dev)
-        self.q_tiles_dev = torch.from_numpy(self.q_tiles).to(dev)
-        self.fwd_tiles_dev = (self.q_tiles_dev if self.fwd_tiles is self.q_tiles
-                              else torch.from_numpy(self.fwd_tiles).to(dev))
-        self.kv_tiles_dev = torch.from_numpy(self.kv_tiles).to(dev)
+        # The plan's query tiles go to the GPU in the order in which they are best served.  8192 tokens in 20 samples,
+        # 32/8 heads of 128, against the plan's order: forward 105 -> 91 us, dQ 106 -> 97.  The order depends on the
+        # pack alone: sorted on the GPU in front of every call it cost launches of even tiles up to 13 % (16384 tokens
+        # in 128 samples, 8 heads of 64: forward 33.8 -> 39.1 us) and the kernels the registers of the look-up.
+        # One copy for all lists (16 bytes a tile, so every list starts on a tile's alignment).
+        own_fwd = self.fwd_tiles is not self.q_tiles
+        lists = [B.hbp_order_query_tiles(self.cu, self.q_tiles), self.kv_tiles]
+        if own_fwd:
+            lists.append(B.hbp_order_query_tiles(self.cu, self.fwd_tiles))
+        n_tiles = [len(x) for x in lists]
+        plan = torch.from_numpy(np.concatenate([x.ravel() for x in lists] + [self.cu])).to(dev)
+        *on_gpu, self.cu_dev = plan.split([4 * n for n in n_tiles] + [len(self.cu)])
+        self.q_tiles_dev, self.kv_tiles_dev, *rest = [x.view(-1, 4) for x in on_gpu]
+        self.fwd_tiles_dev = rest[0] if own_fwd else self.q_tiles_dev
         self.ws_fwd = torch.empty(B.hbp_workspace_bytes(self.desc, B.HBP_FWD), dtype=torch.uint8, device=dev)
         self.ws_bwd = None
         self.prof_fwd = self.prof_bwd = self.prof_dq = None

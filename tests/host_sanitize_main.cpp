@@ -49,6 +49,14 @@ int main() {
       CHECK(hbp_pack_plan(lens.data(), n, pack_len, rows, kind, cu.data(), ns + 1, &ns2, &nc2, small.data(),
                           small_cost.data(), nt - 1, &nt2, &pc) != HBP_OK);
     }
+    std::vector<hbp_tile> ordered(nt);
+    CHECK(hbp_order_query_tiles(cu.data(), ns, tiles.data(), nt, ordered.data()) == HBP_OK);
+    for (int i = 1; i < nt; ++i)
+      CHECK(ordered[i - 1].row_end - cu[ordered[i - 1].sample] + 63 >= (ordered[i].row_end - cu[ordered[i].sample] + 63) / 64 * 64);
+    if (nt > 0) {
+      tiles[0].sample = ns;
+      CHECK(hbp_order_query_tiles(cu.data(), ns, tiles.data(), nt, ordered.data()) == HBP_ERR_INVALID_ARG);
+    }
   }
   {
     int32_t bad[3] = {5, 0, 7}, ns, nc, nt;

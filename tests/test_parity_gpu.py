@@ -382,8 +382,8 @@ def test_one_workgroup_an_item_and_the_queues_give_the_same_bits(lens, Hq, Hkv, 
 @pytest.mark.parametrize("n_short,Hq,Hkv,d,e", [(510, 4, 4, 64, 64), (511, 4, 4, 64, 64), (330, 8, 2, 128, 128),
                                                 (330, 16, 16, 192, 128)])
 def test_tiles_taken_in_order_of_their_key_tiles(n_short, Hq, Hkv, d, e):
-    """Queues, with 512 tiles (the most that are sorted), with one more, and with tails of one row whose place in
-    the worklist (by pairs) is far from their place by key tiles."""
+    """Queues, with 332 to 513 tiles, and with tails of one row whose place in the plan (by pairs) is far from
+    their place by key tiles."""
     lens = [3] * n_short + [129 if n_short > 500 else 641]
     case = Case(lens, sum(lens), Hq, Hkv, d, e, seed=n_short)
     pa, _, _ = full(case)
