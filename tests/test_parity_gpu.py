@@ -369,11 +369,16 @@ def test_wrapped_block_order_with_a_group_of_four_heads_at_head_size_128():
     ([128] * 16 + [1], 16, 16, 192, 128), ([128] * 32 + [1], 16, 16, 64, 64),   # one more than fit
     ([128] * 32, 64, 8, 128, 128)])
 def test_one_workgroup_an_item_and_the_queues_give_the_same_bits(lens, Hq, Hkv, d, e):
-    """Profile records keep the queues; without them a call whose items all fit on the chip has none."""
+    """Profile records keep the queues; without them a call whose items all fit on the chip has none (with one
+    item more than fit, both calls have them).  The second pass starts from NaN: an item it left out would show."""
     case = Case(lens, sum(lens), Hq, Hkv, d, e, seed=len(lens) + Hq)
     pa, dev, out = run_gpu(case, with_profile=True)          # run_gpu asks for no records: its calls may go without queues
     compare(case, pa, out)
+    for buf in (pa.o, pa.lse):
+        buf.fill_(float("nan"))
     pa.forward(dev["q"], dev["k"], dev["v"], profile=True)
+    for buf in (pa.dq, pa.dk, pa.dv):
+        buf.fill_(float("nan"))
     pa.backward(dev["q"], dev["k"], dev["v"], dev["do"], profile=True)
     for name in ("o", "lse", "dq", "dk", "dv"):
         assert np.array_equal(getattr(pa, name).float().cpu().numpy(), out[name]), name
