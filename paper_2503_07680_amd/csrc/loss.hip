@@ -339,7 +339,18 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   rows.before = (int32_t*)(plan_lds + ce_plan_words(p.T) + 1);
   rows.cu = p.n_samples <= kCePlanCu ? rows.before + ce_plan_words(p.T) + 1 : nullptr;
   if (!p.row_start) ce_plan_rows<NT>(p, rows, tid, plan_range, plan_slots);
-  const int row_end = p.row_start ? p.row_start[blockIdx.x + 1] : plan_range[1];
+  // The range is the same in every thread and goes into scalar registers.  Chosen by ?: it came from a load through
+  // one pointer to either memory, whose result counts as different in every thread: a loop over rows by exec masks
+  // and up to 10 more vector registers, of which the longest rows have none (20 chunks: a spill in the loop, whose
+  // reload waits for the gradient stores; T = 8192, V = 160000: 933 -> 929 us).
+  int r, row_end;
+  if (p.row_start) {
+    r = p.row_start[blockIdx.x];
+    row_end = p.row_start[blockIdx.x + 1];
+  } else {
+    r = __builtin_amdgcn_readfirstlane(plan_range[0]);
+    row_end = __builtin_amdgcn_readfirstlane(plan_range[1]);
+  }
   auto stage_rows = [&](int first_row) {  // rows first_row + i, i < kRowBatch
     __syncthreads();                       // the entries of the batch before have all been read
     if (tid < kRowBatch) {
@@ -362,7 +373,6 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     }
     __syncthreads();
   };
-  int r = p.row_start ? p.row_start[blockIdx.x] : plan_range[0];
   if (r >= row_end) return;
   stage_rows(r);
   int label = row_label[0];  // -1: no loss
@@ -487,15 +497,28 @@ __global__ __launch_bounds__(kCeThreads) void ce_reduce_kernel(const CeParams p)
   if (tid == 0) *p.loss_out = acc;
 }
 
+// The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
+// the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
+// many and with one more.  With the gradient: V = 32000: 30.5 / 65.5 / 190 and 34.1 / 65.8 / 193; 45056: 41.1 / 86.8 /
+// 267 and 44.3 / 87.1 / 270; 28672: 30.4 / 57.2 / 174 and 28.0 / 60.0 / 174; 16384: 19.2 / 35.7 / 103 and 19.3 / 38.5 /
+// 104.  Without it: 24576: 14.6 / 26.0 / 60.8 and 16.1 / 25.1 / 58.8; with one fewer, 40960: 18.3 / 35.6 / 86 and
+// 21.2 / 38.1 / 102.
+constexpr int ce_most_per_cu(int nt, int nch, bool with_grad) {
+  if (nt == 256) return !with_grad || nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
+  if (nt == 512) return nch <= 5 ? 4 : !with_grad || nch <= 7 ? 3 : 2;
+  return 2;
+}
+
 // Workgroups resident at once per compute unit.  The main kernel's grid is that times the compute
 // units: a persistent loop over rows; a second batch of workgroups would start with an empty pipeline.
 template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
 static int main_per_cu(int lds) {
-  static int per_cu = 0;  // by registers; same on every device of this part
+  static int per_cu = 0;  // without the planning's LDS; same on every device of this part
   if (per_cu == 0) {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ce_main_kernel<NT, NCH, HOLD, WITH_GRAD>, NT, 0) != hipSuccess || n < 1) n = 1;
-    per_cu = n;
+    constexpr int kMost = ce_most_per_cu(NT, NCH, WITH_GRAD);
+    per_cu = n < kMost ? n : kMost;
   }
   constexpr int kLds = 160 * 1024, kStatic = 4 * 1024;  // LDS of a compute unit; the kernel's own arrays
   const int by_lds = kLds / (lds + kStatic);

@@ -153,3 +153,10 @@ def test_the_forward_kernels_keep_their_registers():
         if "Li128ELi128E" in name:
             assert regs[name] <= 250, (name, regs[name])
         assert spills[name] <= (2 if "Li192ELi128ELi1ELi1E" in name else 0), (name, spills[name])
+
+
+def test_the_loss_kernels_keep_a_row_in_registers_without_spills():
+    """A reload inside the loop over rows waits for the gradient stores of the row before (one counter, in order).
+    With the planned range of rows in vector registers the longest rows (20 chunks, gradient) had one."""
+    spills = {k: v for k, v in kernel_metadata(device_asm("loss.hip")).items() if "ce_main_kernel" in k}
+    assert len(spills) == 70 and not any(spills.values()), {k: v for k, v in spills.items() if v}
