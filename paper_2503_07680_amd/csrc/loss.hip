@@ -570,14 +570,23 @@ static bool launch_held(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t e
 //   32000    192 / 104      192 /  74    195 /  84
 //   65536    381 / 164      375 / 146
 //   81920    476 / 194      473 / 178
-// (with few rows a workgroup, T = 1000, the three are within 10 % from V = 32000 on.)
-constexpr int kCeRow256 = 16384, kCeRow512 = 81920;
+// With few rows, T = 64 / 1000 with the gradient:
+//   4096      9.5 / 17.4     8.3 / 12.5     8.3 / 10.5
+//   16384    10.8 / 23.0    10.0 / 20.3    10.3 / 19.9
+//   32000    13.0 / 33.0    12.3 / 30.5    14.2 / 31.5
+// A call whose workgroups have a row each (two of 512 threads a compute unit) is as long as the compute units with
+// two rows; 1024 threads have half the chain a row and, with one workgroup a compute unit, ranges cut by cost.
+// T = 280 / 512 without the gradient, 1024 threads and 512: V = 81920: 14.1 / 21.4 and 21.1 / 21.8; 65536: 13.2 / 19.0
+// and 17.8 / 18.8; 57344: 12.5 / 17.6 and 16.6 / 17.3; with it, 81920: 24.0 / 40.1 and 27.1 / 42.1; 65536: 21.2 / 33.6
+// and 26.2 / 34.7; T = 256, 57352: 18.3 and 17.3.
+constexpr int kCeRow256 = 16384, kCeRow512 = 81920, kCeRow512Few = 61440;  // Few: a row a workgroup at most
 
 int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   if (p.T > 0) {
+    const int row512 = p.T <= 2 * n_cu ? kCeRow512Few : kCeRow512;
     if (p.V <= kCeRow256) (void)launch_held<256, 1, kCeRow256 / 2048>(p, n_cu, s, ev0, ev1);
-    else if (p.V <= kCeRow512) (void)launch_held<512, kCeRow256 / 4096 + 1, kCeRow512 / 4096>(p, n_cu, s, ev0, ev1);
-    else if (!launch_held<1024, kCeRow512 / 8192 + 1, 20>(p, n_cu, s, ev0, ev1)) launch_main<1024, 1, false>(p, n_cu, s, ev0, ev1);
+    else if (p.V <= row512) (void)launch_held<512, kCeRow256 / 4096 + 1, kCeRow512 / 4096>(p, n_cu, s, ev0, ev1);
+    else if (!launch_held<1024, kCeRow512Few / 8192 + 1, 20>(p, n_cu, s, ev0, ev1)) launch_main<1024, 1, false>(p, n_cu, s, ev0, ev1);
   }
   hipLaunchKernelGGL(ce_reduce_kernel, dim3(1), dim3(kCeThreads), 0, s, p);
   return (int)hipGetLastError();

@@ -159,4 +159,4 @@ def test_the_loss_kernels_keep_a_row_in_registers_without_spills():
     """A reload inside the loop over rows waits for the gradient stores of the row before (one counter, in order).
     With the planned range of rows in vector registers the longest rows (20 chunks, gradient) had one."""
     spills = {k: v for k, v in kernel_metadata(device_asm("loss.hip")).items() if "ce_main_kernel" in k}
-    assert len(spills) == 70 and not any(spills.values()), {k: v for k, v in spills.items() if v}
+    assert len(spills) == 76 and not any(spills.values()), {k: v for k, v in spills.items() if v}

@@ -91,6 +91,13 @@ def test_vocab_sizes_around_the_limits_of_the_workgroup_sizes(V):
     check(bits, y, cu, 1)
 
 
+@pytest.mark.parametrize("lens,V", [([300, 212], 61440), ([300, 212], 61448), ([300, 213], 61448), ([300, 212], 81920),
+                                    ([300, 213], 81920)])
+def test_few_rows_take_the_large_workgroup_from_shorter_rows_on(lens, V):
+    bits, y, cu = make_case(lens, V, V % 83)
+    check(bits, y, cu, 2, t_ave=170.0)
+
+
 @pytest.mark.parametrize("lens", [[63], [64], [40, 25], [1] * 1100 + [60], [70000, 61072], [70000, 61073]])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_rows_and_weights_found_from_the_label_bits(lens, mode):
