@@ -421,7 +421,8 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
 
   // Pads the code in front of the loops: where the step loop (16.5 KB) lies within a 64-byte instruction cache line
   // is worth 3 % of the launch.  131072 tokens, 64/8 heads, d = 128, ms: loop at byte 40: 288.0, at 0: 292.3,
-  // at 16: 294.6, at 24: 294.6, at 56: 294.5.  The launch's time is checked again whenever the code in front changes.
+  // at 16: 294.6, at 24: 294.6, at 56: 294.5 (no other size was measured, nor heads of 64 and 192, which have no pad).
+  // The launch's time is checked again whenever the code in front changes.
   if constexpr (DQK == 128) asm volatile(".rept 11\n s_nop 0\n .endr");
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
@@ -817,8 +818,10 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
 // dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  Workgroups (x, y):
 // share y of key tile x of the worklist (only rows covered by a tile are written, as without parts); a thread
 // handles four consecutive dims of one (key, kv head) at a time.  HBM-bound: every partial sum is read once.
-// With one workgroup a tile there were too few loads under way (T = 32768, 8 query heads on one kv head, 269
-// tiles: 125 us, 2.3 TB/s); kReduceUnits units a thread and four loads of each under way: 53 us, 5.4 TB/s.
+// With one workgroup a tile there were too few loads under way; with kReduceUnits units a thread, T = 32768:
+// 8 parts (8/1 heads) 135 -> 57 us, 5.0 TB/s; 4 parts (12/3) 184 -> 93, 4.9; 3 (6/2, d = 64) 30 -> 19, 6.1;
+// 2 (32/4) 112 -> 60, 5.6; T = 4096, 4 parts: 97 -> 10.  Four loads of a thread are under way from five parts
+// on; with fewer a thread waits for each of its one to three, and the many workgroups make up for it.
 constexpr int kReduceUnits = 2;
 template <int DQK, int DV>
 __global__ __launch_bounds__(kThreads) void bwd_reduce_parts_kernel(const BwdParams p) {
