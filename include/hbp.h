@@ -136,7 +136,10 @@ hbp_status hbp_fwd_tile_rows(const hbp_attn_desc* desc, int32_t* rows_out);
 hbp_status hbp_workspace_bytes(const hbp_attn_desc* desc, int32_t which, size_t* bytes_out);
 
 /* Optional per-workgroup record written by the persistent kernels when `profile` != NULL
- * (device memory, hbp_profile_capacity() records). ticks are the 100 MHz constant clock. */
+ * (device memory, hbp_profile_capacity() records). ticks are the 100 MHz constant clock.
+ * A kernel asked for records always takes its items from queues.  Without them, a kernel whose items all fit on the
+ * chip at once runs one workgroup an item, so the records of such a small pack describe another launch than the plain
+ * one (the results are the same bits). */
 typedef struct {
   uint32_t hw_id;      /* raw HW_ID register of the workgroup's first wave (CU, SE, ...)  */
   uint32_t xcc_id;     /* raw XCC_ID register (accelerator die)                           */
@@ -165,8 +168,7 @@ hbp_status hbp_profile_capacity(const hbp_attn_desc* desc, int32_t which, int32_
  * q_tiles: the HBP_TILES_QUERY list of hbp_pack_plan made with hbp_tile_rows(..., HBP_FWD), or
  * with desc->fwd_tile_rows rows when that is set;
  * items are served in the list's order by a persistent grid (best: that of hbp_order_query_tiles).
- * Tiles that are malformed (outside
- * their sample, longer than the tile size) are skipped, never dereferenced.
+ * Tiles that are malformed (outside their sample, longer than the tile size) are skipped, never dereferenced.
  * Rows of O/LSE not covered by any tile are left untouched.  n_q_tiles == 0 or T == 0: no-op.
  * Errors: INVALID_ARG (null pointers, negative counts, n_q_tiles * n_q_heads above INT32_MAX, a
  * fwd_tile_rows the layout does not take), SHAPE, UNSUPPORTED,
