@@ -274,14 +274,15 @@ def packed_ce_timing(ev, stream, T=8192, V=128256, n_samples=12, reps=10):
 
 
 def plan_timing(w, pa):
-    """Host planning of this pack (both worklists through hbp_pack_plan) and the upload of
-    cu_seqlens and the worklists: outside the timed region, reported on their own."""
+    """Host planning of this pack (both worklists through hbp_pack_plan, the query tiles ordered) and the
+    upload of cu_seqlens and the worklists: outside the timed region, reported on their own."""
     import torch
     import paper_2503_07680_amd as H
     reps, per_call = 20, []
     for i in range(reps + 3):
         t0 = time.perf_counter()
-        H.hbp_pack_plan(w.lengths, w.pack_len, pa.rows_fwd, H.HBP_TILES_QUERY)
+        cu, _, q_tiles, _, _ = H.hbp_pack_plan(w.lengths, w.pack_len, pa.rows_fwd, H.HBP_TILES_QUERY)
+        H.hbp_order_query_tiles(cu, q_tiles)
         H.hbp_pack_plan(w.lengths, w.pack_len, pa.rows_bwd, H.HBP_TILES_KEY)
         if i >= 3:
             per_call.append((time.perf_counter() - t0) * 1e3)
