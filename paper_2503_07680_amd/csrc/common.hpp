@@ -373,26 +373,11 @@ __device__ __forceinline__ void queue_item(int j, int queue, int nk, int n_tiles
   head = (queue + kNumXcd * (grp * kHeadGroup + rem / per_kv)) * per_kv + rem % per_kv;
 }
 
-// One thread takes the next item.  q_cur / q_tried: that thread's cursor over the queues.  A real
-// call, everything passed and returned by value in registers: inlined into the persistent kernels
-// its temporaries cost them registers they do not have (two of them would spill).
-// block: the workgroup's number.  The cursor moves on from an exhausted queue in odd strides; different workgroups
-// of a die use different ones, so they do not all descend on the same other queue.
-__device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
-                                                      int q_tried, int block) {
-  if (!counters) {  // one workgroup an item: workgroups are dealt to the dies in turn
-    Taken t{-1, 0, q_cur, kNumXcd};
-    if (q_tried == 0) {
-      if (Hkv % kNumXcd == 0) {
-        queue_item(block / kNumXcd, block % kNumXcd, Hkv / kNumXcd, n_tiles, per_kv, t.tile_idx, t.head);
-      } else {
-        t.tile_idx = block / (Hkv * per_kv);
-        t.head = block % (Hkv * per_kv);
-      }
-    }
-    return t;
-  }
-  const int steal_stride = 2 * ((block >> 3) & 3) + 1;
+// One thread takes the next item of the queues.  q_cur / q_tried: that thread's cursor over them.
+// steal_stride (odd): how the cursor moves on from an exhausted queue; different workgroups of a die use
+// different strides, so they do not all descend on the same other queue.
+__device__ __forceinline__ Taken queued_item_inline(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
+                                                    int q_tried, int steal_stride) {
   while (q_tried < kNumXcd) {
     const int nk = Hkv > q_cur ? (Hkv - q_cur + kNumXcd - 1) / kNumXcd : 0;  // kv heads of this die
     const int len = n_tiles * nk * per_kv;
@@ -408,6 +393,39 @@ __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_ti
     ++q_tried;
   }
   return Taken{-1, 0, q_cur, q_tried};
+}
+// The one item of workgroup `block` in a launch without queues; workgroups are dealt to the dies in turn.
+__device__ __forceinline__ Taken direct_item_inline(int n_tiles, int Hkv, int per_kv, int q_cur, int q_tried, int block) {
+  Taken t{-1, 0, q_cur, kNumXcd};
+  if (q_tried == 0) {
+    if (Hkv % kNumXcd == 0) {
+      queue_item(block / kNumXcd, block % kNumXcd, Hkv / kNumXcd, n_tiles, per_kv, t.tile_idx, t.head);
+    } else {
+      t.tile_idx = block / (Hkv * per_kv);
+      t.head = block % (Hkv * per_kv);
+    }
+  }
+  return t;
+}
+// Real calls, everything passed and returned by value in registers: inlined into the persistent kernels their
+// temporaries cost them registers they do not have (two of them would spill).  The forward calls one function for
+// either way: with take_item, the one for both, it reloaded 10 more spilled scalars in its hot loop of 1296
+// instructions.  Forward, us, take_item -> two functions: 5515 tokens with a sample of 4017, 12/3 heads of 128: 99.2 ->
+// 94.7; 16000 tokens, 8/1 heads: 193.6 -> 186.7; 7000 tokens, 12/3 heads: 121.7 -> 117.2; 12000 tokens, 24 heads: 286.6
+// -> 287.2; 30000 tokens, 8 heads of 64: 151.4 -> 152.5.  The backward kernels keep take_item: with two functions the
+// training step of 131072 tokens, 64/8 heads, went from 613.0 to 621.4 ms.
+__device__ __attribute__((noinline)) Taken queued_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
+                                                        int q_tried, int steal_stride) {
+  return queued_item_inline(counters, n_tiles, Hkv, per_kv, q_cur, q_tried, steal_stride);
+}
+__device__ __attribute__((noinline)) Taken direct_item(int n_tiles, int Hkv, int per_kv, int q_cur, int q_tried,
+                                                        int block) {
+  return direct_item_inline(n_tiles, Hkv, per_kv, q_cur, q_tried, block);
+}
+__device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
+                                                      int q_tried, int block) {
+  if (!counters) return direct_item_inline(n_tiles, Hkv, per_kv, q_cur, q_tried, block);
+  return queued_item_inline(counters, n_tiles, Hkv, per_kv, q_cur, q_tried, 2 * ((block >> 3) & 3) + 1);
 }
 
 struct WorkQueues {
@@ -438,6 +456,8 @@ __device__ __forceinline__ void race_fence() {
 
 // Workgroup-wide fetch of the next item: thread 0 takes it, everybody reads it back as scalars.
 // slot: two ints of LDS that nobody else touches between the surrounding barriers.
+// TWO: a function for items with queues and one for items without (see queued_item).
+template <bool TWO = false>
 __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int tid, int& q_cur, int& q_tried,
                                           int& tile_idx, int& head) {
   // the slot is addressed as LDS (not through a generic pointer: that becomes flat accesses, each
@@ -446,8 +466,12 @@ __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int t
       (volatile __attribute__((address_space(3))) int*)(uintptr_t)lds_address(slot);
   lds_barrier();  // all LDS reads of the previous item are finished
   if (tid == 0) {
-    const Taken tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried,
-                               (int)blockIdx.x);
+    const int block = (int)blockIdx.x;
+    Taken tk;
+    if constexpr (!TWO) tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, block);
+    else if (wq.counters)
+      tk = queued_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, 2 * ((block >> 3) & 3) + 1);
+    else tk = direct_item(wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, block);
     q_cur = tk.q_cur;
     q_tried = tk.q_tried;
     box[0] = tk.tile_idx;

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
-    if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
+    if (!next_item<true>(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
     h = h * HP + wave / (4 * TP);  // this wave's head
     uint64_t t0 = 0;
     if (p.prof && tid == 0) {

@@ -10,6 +10,8 @@ import re
 import subprocess
 import tempfile
 
+import pytest
+
 from paper_2503_07680_amd import build as B
 
 
@@ -153,6 +155,26 @@ def test_the_forward_kernels_keep_their_registers():
         if "Li128ELi128E" in name:
             assert regs[name] <= 250, (name, regs[name])
         assert spills[name] <= (2 if "Li192ELi128ELi1ELi1E" in name else 0), (name, spills[name])
+
+
+@pytest.mark.parametrize("form", ["Li2ELi1E", "Li1ELi2E"])
+def test_the_forwards_hot_loop_reloads_few_spilled_scalars(form):
+    """Head size 128, eight wavefronts: the loop over pairs of unmasked tiles (64 MFMAs, some 1300 instructions) had 14
+    and 16 such reloads with one function that takes an item with or without queues, and a pack of 5515 tokens with
+    12/3 heads was 4 % longer than with 4 of them."""
+    text = device_asm("fwd.hip")
+    name = next(m for m in re.findall(r"\n(_ZN3hbp\d+fwd_kernel\w+):", text) if "ILi128ELi128E" + form in m)
+    body = text[text.index("\n" + name + ":"):]
+    lines = body[:body.index("s_endpgm")].splitlines()
+    labels = {m.group(1): i for i, m in enumerate(re.match(r"(\.LBB\w+):", l) for l in lines) if m}
+    loops = []
+    for i, line in enumerate(lines):
+        m = re.search(r"\ts_c?branch\w*\s+(\.LBB\w+)", line)
+        if m and labels.get(m.group(1), i) < i:
+            loop = [l for l in lines[labels[m.group(1)]:i + 1] if re.match(r"\t[a-z]", l)]
+            if len(loop) < 1800 and sum("v_mfma" in l for l in loop) == 64:
+                loops.append(sum("v_readlane" in l for l in loop))
+    assert len(loops) == 1 and loops[0] <= 4, loops
 
 
 def test_the_loss_kernels_keep_a_row_in_registers_without_spills():
