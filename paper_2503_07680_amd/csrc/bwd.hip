@@ -815,6 +815,401 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   prof_write(pa, p.prof, tid);
 }
 
+// ------------------------------------------------------------------- dK, dV, eight wavefronts
+// The same items with two wavefronts per SIMD, head sizes 64 and 128: two groups of four wavefronts.  Wave kg of either
+// group holds the dK^T / dV^T accumulators of keys 32 kg .. 32 kg + 31; group 0 takes the first 32 rows of every block
+// of 64 query rows, group 1 the last.  At the end of an item each of the two waves of a key group hands one of its two
+// accumulators to the other through LDS and finishes the other one.
+//
+// A lone wave per SIMD (the kernel above) issues one instruction every 5 to 6 clocks, and a step has about 6 an MFMA:
+// it is bound by its own instruction stream, the matrix pipe 57 % busy.  Two waves of half the rows fill each other's
+// gaps (65 %), and the fewer clocks of a step matter most where the card is not at its power limit.  What makes room
+// for the second wave in 256 registers a lane: the scores of 32 rows alone in flight, their own four stages following
+// each other (S | dP and the probabilities | dV and dS | dK), and at head size 128 the K fragments read from LDS in
+// every step.  dK/dV kernel, four waves -> eight, us: 8192 tokens, 32/8 heads of 128: 184 -> 159; 32768 tokens with a
+// sample of 16384: 4062 -> 3869, 8/1 heads 1067 -> 1039; 131072 tokens, 64/8 heads, ms: 291 -> 277; 5497 tokens, 8 heads
+// of 64: 49.3 -> 42.5; 1024 tokens, 4 heads of 64: 14.8 -> 13.5.
+// The exchange at the end costs an item 1.9 us: see eight_waves() for where the line lies.
+//
+// Tried here and slower or the same: V in LDS too (the LDS pipe, busy in half the clocks, costs power: +2 %); the two
+// groups half a step apart (+2 %); s_setprio around the MFMA chains; copies with a wait of their own in mid-step.
+template <int DQK, int DV>
+__global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdParams p) {
+  static_assert(DQK == DV, "one set of lane offsets for Q and dO");
+  constexpr int BN = 128, BQ = 64, SUB = 32, NBUF = 3;
+  constexpr int QRB = DQK * 2;
+  constexpr int TILE = SUB * QRB, PAIR = 2 * TILE;  // Q and dO of a step, one group
+  constexpr int NC = DQK / 16, NDB = DQK / 32;
+  constexpr bool kKLds = DQK > 64;  // K fragments read from LDS in every step
+  constexpr int K_AT = 2 * NBUF * PAIR, ROWS_AT = K_AT + (kKLds ? 4 * NC * 1024 : 0);
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // [group][buffer][Q | dO], [K fragments], [group][buffer][64 LSE2 | 64 D | 128 of no use]
+  // (32 used of each 64: a copy by 64 lanes writes zeros behind its rows)
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave & 3, qs = wave >> 2;
+  const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+
+  const uint32_t lds0 = lds_address(smem);
+  uint32_t qoff[NC], qtoff[2][NDB];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) qoff[c] = lds0 + qs * (NBUF * PAIR) + l32 * QRB + swz<DQK>(2 * c + hh, l32) * 16;
+  {
+    const int G = lane >> 4, s = lane & 15;
+    const int k8 = 4 * hh + (s >> 2);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const int c = 4 * db + 2 * (G & 1) + ((s & 3) >> 1);
+        qtoff[r][db] = lds0 + qs * (NBUF * PAIR) + (8 * r + k8) * QRB + swz<DQK>(c, 8 * r + k8) * 16 + (s & 1) * 8;
+      }
+  }
+  const uint32_t kfoff = lds0 + K_AT + kg * (NC * 1024) + lane * 16;
+  uint32_t lseoff = lds0 + ROWS_AT + qs * (NBUF * 1024) + 16 * hh;
+  // opaque: the compiler would otherwise rebuild some of these from each other in front of their reads
+  asm volatile("" : "+v"(lseoff));
+#pragma unroll
+  for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qoff[c]));
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(qtoff[0][db]), "+v"(qtoff[1][db]));
+  const uint32_t tiles = lds0 + qs * (NBUF * PAIR) + kg * 1024, rows_lds = lds0 + ROWS_AT + qs * (NBUF * 1024) + kg * 256;
+
+  const uint32_t q_stride_b = (uint32_t)p.q_st * 2, o_stride_b = (uint32_t)p.o_st * 2;
+  FullTileLoader<DQK, SUB> q_loader, o_loader;
+  q_loader.init(kg, lane, q_stride_b);
+  o_loader.init(kg, lane, o_stride_b);
+
+  ProfAcc pa;
+  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
+  const int g_item = p.g / p.n_split;
+  int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
+  for (;;) {
+    int tile_idx, vh;
+    if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
+    const int kh = vh / p.n_split, part = vh - kh * p.n_split;
+    const int head0 = vh * g_item;
+    prof_begin(pa, p.prof, wave);
+
+    hbp_tile tl = p.tiles[tile_idx];
+    tl.row_begin = __builtin_amdgcn_readfirstlane(tl.row_begin);
+    tl.row_end = __builtin_amdgcn_readfirstlane(tl.row_end);
+    tl.tile = __builtin_amdgcn_readfirstlane(tl.tile);
+    bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
+    int s0 = 0, s1 = 0;
+    if (ok) {
+      s0 = __builtin_amdgcn_readfirstlane(p.cu[tl.sample]);
+      s1 = __builtin_amdgcn_readfirstlane(p.cu[tl.sample + 1]);
+      ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
+           tl.row_end <= s1 && tl.row_end - tl.row_begin <= BN;
+    }
+    if (ok) {
+      const int s_len = s1 - s0;
+      const int k0_in = tl.row_begin - s0;
+      const int kw0_in = k0_in + 32 * kg;
+      const int my_key = tl.row_begin + 32 * kg + l32;
+      const bool key_valid = my_key < tl.row_end;
+      const bool wave_active = tl.row_begin + 32 * kg < tl.row_end;
+
+      const int qb_start = (k0_in / BQ) * BQ;
+      const int nqb = (s_len - qb_start + BQ - 1) / BQ;
+      const int n_steps = nqb * g_item;
+      const int w_share = (int)gridDim.x / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);
+      int skip = w_share >= 8 && ((tl.tile / w_share) & 1) ? (tl.tile % w_share) * (BN / BQ) : 0;
+      skip = max(0, min(skip, nqb - 1));
+      // Step order as in the four-wave kernel.  The copies of a step's operands run two steps ahead, one by one behind the
+      // updates: their address path takes 16 clocks of the compute unit a copy, and a burst of them holds the waves.  State of the copying side: the block and head of the next
+      // step to copy, its first row of this group's 32 (in-sample), the steps left, and the descriptors of the three
+      // sources (Q, dO, and LSE2 or D: waves 0 and 1 of a group copy those).
+      int blk_next = nqb - 1 - skip, head_next = 0, copies_left = n_steps;
+      int q0_next = qb_start + blk_next * BQ + SUB * qs;
+      u32x4 q_desc, o_desc, r_desc;
+      auto set_spans = [&]() {
+        const int rows = copies_left > 0 ? s_len - q0_next : 0;
+        q_desc[2] = rows_span(rows, SUB, q_stride_b, QRB);
+        o_desc[2] = rows_span(rows, SUB, o_stride_b, QRB);
+        r_desc[2] = kg < 2 ? rows_span(rows, SUB, 4, 4) : 0;
+      };
+      {
+        const int64_t row = (int64_t)s0 + q0_next;
+        q_desc = buffer_desc(p.q + row * p.q_st + (int64_t)head0 * p.q_sh, 0);
+        o_desc = buffer_desc(p.d_o + row * p.o_st + (int64_t)head0 * p.o_sh, 0);
+        r_desc = buffer_desc((kg == 0 ? p.lse2 : p.D) + (int64_t)head0 * p.T + row, 0);
+        set_spans();
+      }
+      constexpr int NQC = decltype(q_loader)::PER_WAVE, N_COPY = 2 * NQC + 1;
+      int q0_in[NBUF] = {0, 0, 0};
+      auto issue_copy = [&](auto slot_tag, auto buf_tag) {
+        constexpr int SLOT = decltype(slot_tag)::value, BUF = decltype(buf_tag)::value;
+        if constexpr (SLOT < NQC) buffer_copy16<BUF * PAIR + SLOT * 4096>(q_desc, q_loader.off[SLOT], tiles);
+        else if constexpr (SLOT < 2 * NQC) buffer_copy16<BUF * PAIR + TILE + (SLOT - NQC) * 4096>(o_desc, o_loader.off[SLOT - NQC], tiles);
+        else buffer_copy4<BUF * 1024>(r_desc, lane * 4, rows_lds);
+      };
+      // to the first head of the block before, from the last head of a block
+      const int64_t q_blk = -2 * ((int64_t)BQ * p.q_st + (int64_t)(g_item - 1) * p.q_sh);
+      const int64_t o_blk = -2 * ((int64_t)BQ * p.o_st + (int64_t)(g_item - 1) * p.o_sh);
+      const int64_t r_blk = -4 * ((int64_t)BQ + (int64_t)(g_item - 1) * p.T);
+      auto advance = [&](int buf) {
+        q0_in[buf] = q0_next;
+        --copies_left;
+        if (++head_next < g_item) {
+          buffer_advance(q_desc, 2 * p.q_sh);
+          buffer_advance(o_desc, 2 * p.o_sh);
+          buffer_advance(r_desc, 4 * (int64_t)p.T);
+        } else {
+          head_next = 0;
+          buffer_advance(q_desc, q_blk);
+          buffer_advance(o_desc, o_blk);
+          buffer_advance(r_desc, r_blk);
+          q0_next -= BQ;
+          if (--blk_next < 0) {  // on from the tile's own block to the sample's last
+            blk_next += nqb;
+            q0_next += nqb * BQ;
+            buffer_advance(q_desc, 2 * (int64_t)nqb * BQ * p.q_st);
+            buffer_advance(o_desc, 2 * (int64_t)nqb * BQ * p.o_st);
+            buffer_advance(r_desc, 4 * (int64_t)nqb * BQ);
+          }
+          // only the sample's last block may have fewer rows; and none are copied behind the item's last step
+          if (blk_next >= nqb - 2 || copies_left <= 0) set_spans();
+        }
+      };
+      auto issue_all = [&](auto buf_tag) {
+        issue_copy(std::integral_constant<int, 0>{}, buf_tag);
+        issue_copy(std::integral_constant<int, 1>{}, buf_tag);
+        issue_copy(std::integral_constant<int, 2>{}, buf_tag);
+        if constexpr (N_COPY > 3) issue_copy(std::integral_constant<int, 3>{}, buf_tag);
+        if constexpr (N_COPY > 4) issue_copy(std::integral_constant<int, 4>{}, buf_tag);
+      };
+      static_assert(N_COPY == 3 || N_COPY == 5, "32 rows of 128 or 256 bytes on four waves");
+      issue_all(std::integral_constant<int, 0>{});
+      advance(0);
+      issue_all(std::integral_constant<int, 1>{});
+      advance(1);
+
+      Frag knat[kKLds ? 1 : NC], vnat[NC];
+      {
+        const uint16_t* kp = p.k + (int64_t)my_key * p.k_st + (int64_t)kh * p.k_sh + 8 * hh;
+        const uint16_t* vp = p.v + (int64_t)my_key * p.v_st + (int64_t)kh * p.v_sh + 8 * hh;
+        if constexpr (kKLds) {  // the two waves of a key group write half of the fragments each
+#pragma unroll
+          for (int c = 0; c < NC / 2; ++c) {
+            const u32x4 x = key_valid ? *(const u32x4*)(kp + 16 * (2 * c + qs)) : u32x4{0, 0, 0, 0};
+            *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(kfoff + (2 * c + qs) * 1024) = x;
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < NC; ++c) knat[c].u = key_valid ? *(const u32x4*)(kp + 16 * c) : u32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) vnat[c].u = key_valid ? *(const u32x4*)(vp + 16 * c) : u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) vnat[c].u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+      }
+      f32x16 dkt[NDB], dvt[NDB];
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dkt[db][i] = dvt[db][i] = 0.f;
+
+      constexpr int kPD = 3;
+      auto pin = [](auto& x) {  // keeps a slice's result where it is computed: it is used behind the next chain
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(x));
+#endif
+      };
+      const int kw0 = wave_active ? kw0_in : 0x7fffffe0;  // no block is in reach of an idle wave
+      // The copies of the step after next go to the buffer that the step before this one has left.
+      auto do_step = [&](auto buf_tag) {
+        constexpr int BUF = decltype(buf_tag)::value, CBUF = (BUF + 2) % NBUF;
+        const std::integral_constant<int, CBUF> cbuf{};
+        __builtin_amdgcn_s_waitcnt(0x0F70 + N_COPY);  // all copies but the last step's, which are the next step's operands
+        __syncthreads();
+        const int q0 = q0_in[BUF];
+        const bool need = ((q0 + 31 - kw0) | (s_len - 1 - q0)) >= 0;  // not above this wave's keys, nor behind the sample
+        typedef const __attribute__((address_space(3))) u32x4* lds_u4;
+        typedef const __attribute__((address_space(3))) f32x4* lds_f4;
+        auto q_load = [&](int i) { Frag a; a.u = *(lds_u4)(uintptr_t)(qoff[i] + BUF * PAIR); return a; };
+        auto o_load = [&](int i) { Frag a; a.u = *(lds_u4)(uintptr_t)(qoff[i] + (BUF * PAIR + TILE)); return a; };
+        auto k_load = [&](int i) { Frag a; a.u = *(lds_u4)(uintptr_t)(kfoff + i * 1024); return a; };
+        auto t_load = [&](int i, int base) {
+          const int db = i % NDB, j = i / NDB;
+          Frag a;
+          a.h[0] = lds_read_tr16_at(qtoff[0][db] + (16 * j * QRB + base));
+          a.h[1] = lds_read_tr16_at(qtoff[1][db] + (16 * j * QRB + base));
+          return a;
+        };
+        if (need) {
+          f32x16 s, dp;
+          Frag pb[2], dsb[2];
+          // ---- S = Q K^T
+          Frag rq[kPD], rk[kPD];
+#pragma unroll
+          for (int i = 0; i < kPD; ++i) {
+            rq[i] = q_load(i);
+            if constexpr (kKLds) rk[i] = k_load(i);
+          }
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {  // D of the rows: dP starts there (V is held negated: it ends as D - dP)
+            const f32x4 t = *(lds_f4)(uintptr_t)(lseoff + BUF * 1024 + 256 + 32 * b);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dp[4 * b + v] = t[v];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < NC; ++i) {
+            const bf16x8 kb = kKLds ? rk[i % kPD].v : knat[kKLds ? 0 : i].v;
+            if (i == 0) s = mfma32_vgpr_first(rq[0].v, kb);
+            else mfma32_vgpr(s, rq[i % kPD].v, kb);
+            if (i + kPD < NC) {
+              rq[i % kPD] = q_load(i + kPD);
+              if constexpr (kKLds) rk[i % kPD] = k_load(i + kPD);
+            } else {
+              rq[i % kPD] = o_load(i + kPD - NC);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // ---- dP = dO V^T, the probabilities behind it
+          f32x4 l4 = *(lds_f4)(uintptr_t)(lseoff + BUF * 1024), l4n;
+          mfma32_vgpr(dp, rq[NC % kPD].v, vnat[0].v);
+          rq[NC % kPD] = o_load(kPD);
+          mfma_result_ready(s);
+          if (((q0 - kw0_in - 31) | (s_len - 32 - q0)) < 0) {  // the diagonal or the sample's end in reach
+            int x = lane;  // opaque: rebuilt here, not held across the loop
+            asm volatile("" : "+v"(x));
+            const int e0 = q0 + 4 * (x >> 5);
+            int d = kw0_in + (x & 31) - e0, e = s_len - e0;  // row 8b + 4hh + v: masked below d and from e on
+            asm volatile("" : "+v"(d), "+v"(e));
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              if (8 * (i >> 2) + (i & 3) < d || 8 * (i >> 2) + (i & 3) >= e) s[i] = -INFINITY;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          auto p_slice = [&](int i) {  // 0..16: exp of element i, pack of the pair that ends at element i - 1
+            if (i < 16) {
+              const int b = i >> 2, v = i & 3;
+              if (v == 0) {
+                if (i) l4 = l4n;
+                if (b < 3) l4n = *(lds_f4)(uintptr_t)(lseoff + BUF * 1024 + 32 * (b + 1));
+              }
+              float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], p.scale_log2, -l4[v]));
+              pin(e);
+              s[i] = e;
+            }
+            if (i > 0 && (i & 1) == 0) {
+              const int e = i - 2;
+              pb[e >> 3].w[(e & 7) >> 1] = pack_bf16(s[e], s[e + 1]);
+              pin(pb[e >> 3].w[(e & 7) >> 1]);
+            }
+          };
+          constexpr int LP = NC - 1;
+#pragma unroll
+          for (int i = 1; i < NC; ++i) {
+            mfma32_vgpr(dp, rq[(NC + i) % kPD].v, vnat[i].v);
+            if (i + kPD < NC) rq[(NC + i) % kPD] = o_load(i + kPD);
+#pragma unroll
+            for (int sl = (i - 1) * 17 / LP; sl < i * 17 / LP; ++sl) p_slice(sl);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // ---- dV^T += dO^T P, dS behind it; dK^T += Q^T dS
+          Frag rt[kPD];
+          auto g_load = [&](int i) { return i < 2 * NDB ? t_load(i, BUF * PAIR + TILE) : t_load(i - 2 * NDB, BUF * PAIR); };
+#pragma unroll
+          for (int i = 0; i < kPD; ++i) rt[i] = g_load(i);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma_result_ready(dp);
+          constexpr int LG = 4 * NDB, LV = 2 * NDB, GAP = LG / N_COPY;
+          auto copy_behind = [&](auto slot_tag, int i) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            if constexpr (SLOT < N_COPY)
+              if (i == 1 + SLOT * GAP) issue_copy(slot_tag, cbuf);
+          };
+#pragma unroll
+          for (int i = 0; i < LG; ++i) {
+            const int db = i % NDB, j = (i / NDB) & 1;
+            if (i < LV) dvt[db] = mfma32(rt[i % kPD].v, pb[j].v, dvt[db]);
+            else dkt[db] = mfma32(rt[i % kPD].v, dsb[j].v, dkt[db]);
+            if (i + kPD < LG) rt[i % kPD] = g_load(i + kPD);
+            if (i < LV) {
+#pragma unroll
+              for (int e = i * 8 / LV * 2; e < (i + 1) * 8 / LV * 2; e += 2) {
+                dsb[e >> 3].w[(e & 7) >> 1] = pack_bf16(s[e] * dp[e], s[e + 1] * dp[e + 1]);
+                pin(dsb[e >> 3].w[(e & 7) >> 1]);
+              }
+            }
+            copy_behind(std::integral_constant<int, 0>{}, i);
+            copy_behind(std::integral_constant<int, 1>{}, i);
+            copy_behind(std::integral_constant<int, 2>{}, i);
+            copy_behind(std::integral_constant<int, 3>{}, i);
+            copy_behind(std::integral_constant<int, 4>{}, i);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          issue_all(cbuf);
+        }
+        advance(CBUF);
+        race_fence();
+      };
+
+      for (int step = 0; step < n_steps; step += 3) {
+        do_step(std::integral_constant<int, 0>{});
+        if (step + 1 < n_steps) do_step(std::integral_constant<int, 1>{});
+        if (step + 2 < n_steps) do_step(std::integral_constant<int, 2>{});
+      }
+      wait_async_loads();
+
+      // The two waves of a pair: the upper rows' wave hands over its dK^T and finishes dV, the other the reverse.
+      __syncthreads();  // the tile buffers are no longer read
+      const uint32_t mine = lds0 + wave * (NDB * 4096) + lane * 16, theirs = lds0 + (wave ^ 4) * (NDB * 4096) + lane * 16;
+      typedef __attribute__((address_space(3))) f32x4* lds_w4;
+      auto send = [&](const f32x16 (&acc)[NDB]) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            *(lds_w4)(uintptr_t)(mine + (4 * db + b) * 1024) = f32x4{acc[db][4 * b], acc[db][4 * b + 1], acc[db][4 * b + 2], acc[db][4 * b + 3]};
+      };
+      auto receive = [&](f32x16 (&acc)[NDB]) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const f32x4 t = *(const __attribute__((address_space(3))) f32x4*)(uintptr_t)(theirs + (4 * db + b) * 1024);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[db][4 * b + v] += t[v];
+          }
+      };
+      auto store = [&](const f32x16 (&acc)[NDB], uint16_t* out, int64_t st, int64_t sh, float* parts, float scale) {
+        if (p.n_split == 1) {
+          uint16_t* row = out + (int64_t)my_key * st + (int64_t)kh * sh;
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) store_block_bf16(row + 32 * db, acc[db], scale, hh, key_valid);
+        } else if (key_valid) {
+          float* row = parts + (((int64_t)part * p.T + my_key) * p.Hkv + kh) * DQK + 4 * hh;
+#pragma unroll
+          for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              *(f32x4*)(row + 32 * db + 8 * b) = f32x4{acc[db][4 * b] * scale, acc[db][4 * b + 1] * scale,
+                                                         acc[db][4 * b + 2] * scale, acc[db][4 * b + 3] * scale};
+        }
+      };
+      if (qs == 0) send(dkt);
+      else send(dvt);
+      __syncthreads();
+      if (qs == 0) {
+        receive(dvt);
+        store(dvt, p.dv, p.v_st, p.v_sh, p.dv_part, 1.0f);
+      } else {
+        receive(dkt);
+        store(dkt, p.dk, p.k_st, p.k_sh, p.dk_part, -p.scale);
+      }
+    }
+    prof_end(pa, p.prof, wave);
+  }
+  prof_write(pa, p.prof, tid);
+}
+
 // dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  Workgroups (x, y):
 // share y of key tile x of the worklist (only rows covered by a tile are written, as without parts); a thread
 // handles four consecutive dims of one (key, kv head) at a time.  HBM-bound: every partial sum is read once.
@@ -893,10 +1288,45 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
   }
 }
 
+// Eight or four wavefronts a key tile (dK/dV kernel).  Eight pay per step and cost per item, so the line is the mean
+// number of steps an item has: heads of the item x blocks of 64 rows from the tile to its sample's end.  Time of the
+// backward, four / eight, T = 512 to 32768, samples of one size and mixed ones:
+//   d = 128, one head an item    samples of 60: .81 to .97; 250: .90 to .96; 600: .95 to .99; 1000: .98 to 1.01;
+//                                1200: 1.00 to 1.01; 1500: 1.00 to 1.02; 2500: 1.02 to 1.03
+//            two                 60: .92; 150: .98; 290: 1.02; 580: 1.03; 1000: 1.03
+//            three and more      25: 1.01 (four) and 1.11 (eight); 60: 1.00 and 1.10; 250: 1.08; 1000: 1.06
+//   d = 64, one                  25: 1.01; 60: 1.00; 126: .94 to .99; 240: 1.00 to 1.07; 800: 1.03 to 1.08
+// With no more items than compute units the launch is as long as its longest item: eight from 100 tokens a sample on
+// (.995 to 1.39; of 60: .96 to .99).
+static bool eight_waves(int d, const BwdParams& p) {
+  const double len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
+  const int heads = p.g / p.n_split;
+  if ((int64_t)p.n_tiles * p.Hkv * p.n_split <= 256) return len >= 100;
+  const double steps = heads * (len / 128 + 1);
+  return d == 64 ? steps >= 2.5 : heads >= 3 || steps >= (heads == 2 ? 6.5 : 10);
+}
+template <int DQK, int DV>
+static int launch_dkdv8(const BwdParams& p, int grid, hipStream_t s) {
+  constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + (DQK > 64 ? 128 * DQK * 2 : 0) + 2 * 3 * 1024;
+  constexpr int sums = 8 * DQK / 32 * 4096;
+  constexpr int lds = tiles > sums ? tiles : sums;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)bwd_dkdv8_kernel<DQK, DV>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return (int)e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((bwd_dkdv8_kernel<DQK, DV>), dim3(grid), dim3(2 * kThreads), lds, s, p);
+  return 0;
+}
+
 template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
   constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
   constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
+  bool eight = false;
+  if constexpr (DQK == DV) eight = grid_dkdv > 0 && eight_waves(DQK, p);
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)bwd_dq_kernel<DQK, DV>,
@@ -914,7 +1344,14 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
   if (e != hipSuccess) return (int)e;
   if (grid_dkdv > 0) {
     if (ev[0] && hipEventRecord(ev[0], s) != hipSuccess) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL((bwd_dkdv_kernel<DQK, DV>), dim3(grid_dkdv), dim3(kThreads), lds_dkdv, s, p);
+    if constexpr (DQK == DV) {
+      if (eight) {
+        const int err = launch_dkdv8<DQK, DV>(p, grid_dkdv, s);
+        if (err) return err;
+      }
+    }
+    if (!eight)
+      hipLaunchKernelGGL((bwd_dkdv_kernel<DQK, DV>), dim3(grid_dkdv), dim3(kThreads), lds_dkdv, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
     if (p.n_split > 1) {

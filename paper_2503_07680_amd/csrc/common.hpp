@@ -49,6 +49,7 @@ __device__ __forceinline__ void mfma32_vgpr(f32x16& c, bf16x8 a, bf16x8 b) {
 __device__ __forceinline__ void mfma_results_ready(f32x16& x, f32x16& y) {
   asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x), "+v"(y));
 }
+__device__ __forceinline__ void mfma_result_ready(f32x16& x) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x)); }
 
 union Frag {
   bf16x8 v;
@@ -176,6 +177,43 @@ __device__ __forceinline__ void async_copy4(const void* base_uniform, uint32_t l
       :
       : "s"(lds_addr_uniform), "v"(lane_byte_off), "s"(base_uniform)
       : "memory", "m0");
+}
+
+// The same through a buffer descriptor (raw, range-checked): lanes whose offset lies behind `bytes` read nothing and
+// write zeros to LDS, so the rows behind a sample's end need neither a clamp nor a second path.  lds_addr + AT is
+// the LDS address.
+__device__ __forceinline__ u32x4 buffer_desc(const void* base, uint32_t bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes, 0x00020000u};
+}
+__device__ __forceinline__ void buffer_advance(u32x4& desc, int64_t bytes) {
+  const uint64_t a = (((uint64_t)desc[1] << 32) | desc[0]) + (uint64_t)bytes;
+  desc[0] = (uint32_t)a;
+  desc[1] = (uint32_t)(a >> 32);
+}
+template <int AT>
+__device__ __forceinline__ void buffer_copy16(const u32x4& desc, uint32_t lane_byte_off, uint32_t lds_addr_uniform) {
+  asm volatile(
+      "s_add_u32 m0, %0, %3\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, 0 offen lds"
+      :
+      : "s"(lds_addr_uniform), "v"(lane_byte_off), "s"(desc), "i"(AT)
+      : "memory", "m0", "scc");
+}
+template <int AT>
+__device__ __forceinline__ void buffer_copy4(const u32x4& desc, uint32_t lane_byte_off, uint32_t lds_addr_uniform) {
+  asm volatile(
+      "s_add_u32 m0, %0, %3\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dword %1, %2, 0 offen lds"
+      :
+      : "s"(lds_addr_uniform), "v"(lane_byte_off), "s"(desc), "i"(AT)
+      : "memory", "m0", "scc");
+}
+// bytes that `rows` rows of row_bytes each span, at most max_rows of them (0 for none)
+__device__ __forceinline__ uint32_t rows_span(int rows, int max_rows, uint32_t stride_bytes, uint32_t row_bytes) {
+  return rows <= 0 ? 0 : (uint32_t)(min(rows, max_rows) - 1) * stride_bytes + row_bytes;
 }
 
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
