@@ -291,7 +291,6 @@ extern "C" hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void*
   p.scale_log2 = resolve_scale(desc) * 1.4426950408889634f;
   p.counter = static_cast<int32_t*>(workspace);
   p.prof = profile;
-  p.n_split = hbp::heads_split(p.Hkv, p.g % 2 == 0 ? p.g / 2 : p.g);  // even groups: items are pairs of heads
 
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (hbp::launch_fwd(desc->d_qk, desc->d_v, p, desc->fwd_tile_rows ? desc->fwd_tile_rows : kTileRows, kNumCU, hs, g_events[HBP_FWD][0], g_events[HBP_FWD][1]) != 0) return HBP_ERR_DEVICE;

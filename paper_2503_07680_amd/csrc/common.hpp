@@ -561,10 +561,8 @@ struct BwdParams {
 // A kernel whose items all fit on the chip at once gets one workgroup an item and no queue: every item starts
 // at once whatever its order, and the launch that resets the counters (5 us of the stream's time) and the
 // atomic in front of an item fall away.  Training step of a 1024-token pack with 4 heads of 64: 46.0 -> 36.6 us;
-// of 5497 tokens with 8 heads: 119 -> 110.  Not for more items than that: the hardware's dispatch of the later
-// ones balances uneven items worse than the queues do (up to eight rounds of workgroups: 8192 tokens, 32/8
-// heads -1 %, but 32768 tokens, 8/1 heads +3 %).  Profile records are one per resident workgroup, so a call
-// that asks for them keeps the queues.
+// of 5497 tokens with 8 heads: 119 -> 110.  The forward goes further (fwd_way).  Profile records are one per resident
+// workgroup, so a call that asks for them keeps the queues.
 inline bool direct_items(int64_t n_items, int64_t resident, const void* prof) { return !prof && n_items <= resident; }
 
 // In how many parts the `units` schedulable units of a kv head (query heads, or pairs of them) are
