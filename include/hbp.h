@@ -138,8 +138,8 @@ hbp_status hbp_workspace_bytes(const hbp_attn_desc* desc, int32_t which, size_t*
 /* Optional per-workgroup record written by the persistent kernels when `profile` != NULL
  * (device memory, hbp_profile_capacity() records). ticks are the 100 MHz constant clock.
  * A kernel asked for records always takes its items from queues.  Without them, a kernel whose items all fit on the
- * chip at once runs one workgroup an item, so the records of such a small pack describe another launch than the plain
- * one (the results are the same bits). */
+ * chip at once runs one workgroup an item, and dK/dV and dQ of a pack of few rounds go in one launch, so the records of
+ * such a pack describe other launches than the plain ones (the results are the same bits). */
 typedef struct {
   uint32_t hw_id;      /* raw HW_ID register of the workgroup's first wave (CU, SE, ...)  */
   uint32_t xcc_id;     /* raw XCC_ID register (accelerator die)                           */
@@ -246,7 +246,8 @@ hbp_status hbp_varlen_attn_bwd_static(const hbp_attn_desc* desc, const void* q, 
  * the entry point that launches the chosen kernel (which = HBP_FWD, HBP_BWD, HBP_BWD_DQ, HBP_LOSS) records
  * `start` on its stream immediately before, and `stop` immediately after, that persistent kernel
  * (the forward kernel; the dK/dV kernel; the dQ kernel), so a caller can time that one launch with
- * hipEventElapsedTime.  Events are hipEvent_t passed as void*, owned by the caller; pass NULLs to
+ * hipEventElapsedTime.  While events are set for the dK/dV or the dQ kernel the two always have a launch each (without
+ * them a pack of few rounds has one launch for both; same bits).  Events are hipEvent_t passed as void*, owned by the caller; pass NULLs to
  * switch the hook off.  Process-wide state, not thread safe.  Returns HBP_ERR_INVALID_ARG for a
  * bad `which` or when exactly one event is NULL.
  */

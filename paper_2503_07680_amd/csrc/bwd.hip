@@ -58,8 +58,12 @@ __device__ __forceinline__ void prof_write(const ProfAcc& a, hbp_profile_rec* pr
 // ------------------------------------------------------------------------------------- dQ
 // Two workgroups per compute unit where the kernel fits 256 registers (d_qk <= 128): the second
 // wavefront on each SIMD fills the issue slots the first one leaves open.
-template <int DQK, int DV>
-__global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(const BwdParams p) {
+//
+// HALVES = 2 (see bwd_both_kernel): the workgroup has eight wavefronts, four for each of two neighbouring query heads of
+// the same tile, and takes the launch's item `block` alone.  SHARED: both heads read the same kv head and work off the
+// same tiles in LDS (half the copies); otherwise each half has its own.
+template <int DQK, int DV, int HALVES = 1, bool SHARED = false>
+__device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
   constexpr int BM = 128, BN = 64;
   constexpr int KRB = DQK * 2, VRB = DV * 2;
   constexpr int K_TILE = BN * KRB, V_TILE = BN * VRB;
@@ -69,14 +73,15 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
   // time); the builtin form stays as the fallback.
   constexpr bool kVgprScores = true;
 
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // [K buf0][K buf1][V buf0][V buf1]
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  const int tid = threadIdx.x;
+  const int wave_in_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = HALVES == 1 ? wave_in_wg : wave_in_wg & 3, half = HALVES == 1 ? 0 : wave_in_wg >> 2;
+  const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+  // a half's [K buf0][K buf1][V buf0][V buf1]
+  char* const smem = smem_all + (SHARED ? 0 : half * (2 * K_TILE + 2 * V_TILE));
   char* const k_lds = smem;
   char* const v_lds = smem + 2 * K_TILE;
-
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
 
   // Absolute LDS addresses of this lane's fragments: workgroup base and current buffer included
   // (toggled once per tile), so a read needs no address arithmetic.
@@ -103,18 +108,27 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
       }
   }
 
-  TileLoader<DQK, BN> k_loader;
-  TileLoader<DV, BN> v_loader;  // same lane pattern as k_loader when the row sizes agree: then only that one is kept
-  k_loader.init(wave, lane);
-  if (!kSameRows) v_loader.init(wave, lane);
+  constexpr int NW = SHARED ? 8 : 4;  // wavefronts that copy a tile
+  const int cwave = SHARED ? wave_in_wg : wave;
+  TileLoader<DQK, BN, NW> k_loader;
+  TileLoader<DV, BN, NW> v_loader;  // same lane pattern as k_loader when the row sizes agree: then only that one is kept
+  k_loader.init(cwave, lane);
+  if (!kSameRows) v_loader.init(cwave, lane);
   const uint32_t k_stride_b = (uint32_t)p.k_st * 2, v_stride_b = (uint32_t)p.v_st * 2;
 
   ProfAcc pa;
-  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / p.n_split_dq};
+  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / (SHARED ? 2 : 1) / p.n_split_dq};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
-    if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
+    if constexpr (HALVES == 1) {
+      if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
+    } else {
+      const Taken tk = SHARED ? direct_item_inline(wq.n_tiles, wq.Hkv, wq.per_kv, 0, 0, block)
+                              : direct_item_inline(wq.n_tiles, (p.Hq + 1) / 2, 1, 0, 0, block);
+      tile_idx = __builtin_amdgcn_readfirstlane(tk.tile_idx);
+      h = 2 * __builtin_amdgcn_readfirstlane(tk.head) + half;
+    }
     prof_begin(pa, p.prof_dq, tid);
 
     const hbp_tile tl = p.q_tiles[tile_idx];
@@ -128,11 +142,13 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
     }
     if (ok) {
       const int r0 = tl.row_begin, r1 = tl.row_end;
+      const bool has_head = HALVES == 1 || SHARED || h < p.Hq;  // an odd number of heads: the last pair has one
+      if (!has_head) h = p.Hq - 1;
       const int kh = h / p.g;
       const int qw0 = r0 - s0 + 32 * wave;
       const int my_row = r0 + 32 * wave + l32;
-      const bool row_valid = my_row < r1;
-      const bool wave_active = r0 + 32 * wave < r1;
+      const bool row_valid = has_head && my_row < r1;
+      const bool wave_active = has_head && r0 + 32 * wave < r1;
       const int n_keys = r1 - s0;
       const int nkt = (n_keys + BN - 1) / BN;
       const uint16_t* kbase = p.k + (int64_t)s0 * p.k_st + (int64_t)kh * p.k_sh;
@@ -144,11 +160,11 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
         const int k_off = kt * BN;
         const int valid = n_keys - k_off;
         if (slot < NKCP) {
-          k_loader.issue_one(slot, kbase + (int64_t)k_off * p.k_st, k_stride_b, valid, k_lds + (kt & 1) * K_TILE, wave);
+          k_loader.issue_one(slot, kbase + (int64_t)k_off * p.k_st, k_stride_b, valid, k_lds + (kt & 1) * K_TILE, cwave);
         } else if constexpr (kSameRows) {
-          k_loader.issue_one(slot - NKCP, vbase + (int64_t)k_off * p.v_st, v_stride_b, valid, v_lds + (kt & 1) * V_TILE, wave);
+          k_loader.issue_one(slot - NKCP, vbase + (int64_t)k_off * p.v_st, v_stride_b, valid, v_lds + (kt & 1) * V_TILE, cwave);
         } else {
-          v_loader.issue_one(slot - NKCP, vbase + (int64_t)k_off * p.v_st, v_stride_b, valid, v_lds + (kt & 1) * V_TILE, wave);
+          v_loader.issue_one(slot - NKCP, vbase + (int64_t)k_off * p.v_st, v_stride_b, valid, v_lds + (kt & 1) * V_TILE, cwave);
         }
       };
       auto issue = [&](int kt) {
@@ -355,8 +371,13 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
       }
     }
     prof_end(pa, p.prof_dq, tid);
+    if constexpr (HALVES == 2) break;
   }
   prof_write(pa, p.prof_dq, tid);
+}
+template <int DQK, int DV>
+__global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(const BwdParams p) {
+  dq_items<DQK, DV>(p, 0);
 }
 
 // ----------------------------------------------------------------------------------- dK, dV
@@ -833,8 +854,10 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
 //
 // Tried here and slower or the same: V in LDS too (the LDS pipe, busy in half the clocks, costs power: +2 %); the two
 // groups half a step apart (+2 %); s_setprio around the MFMA chains; copies with a wait of their own in mid-step.
-template <int DQK, int DV>
-__global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdParams p) {
+//
+// DIRECT: the launch's item `block` and no other (see bwd_both_kernel).  n_resident: workgroups under way at a time.
+template <int DQK, int DV, bool DIRECT = false>
+__device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n_resident) {
   static_assert(DQK == DV, "one set of lane offsets for Q and dO");
   constexpr int BN = 128, BQ = 64, SUB = 32, NBUF = 3;
   constexpr int QRB = DQK * 2;
@@ -887,7 +910,13 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdPar
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, vh;
-    if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
+    if constexpr (DIRECT) {
+      const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
+      tile_idx = __builtin_amdgcn_readfirstlane(tk.tile_idx);
+      vh = __builtin_amdgcn_readfirstlane(tk.head);
+    } else {
+      if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
+    }
     const int kh = vh / p.n_split, part = vh - kh * p.n_split;
     const int head0 = vh * g_item;
     prof_begin(pa, p.prof, wave);
@@ -915,7 +944,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdPar
       const int qb_start = (k0_in / BQ) * BQ;
       const int nqb = (s_len - qb_start + BQ - 1) / BQ;
       const int n_steps = nqb * g_item;
-      const int w_share = (int)gridDim.x / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);
+      const int w_share = n_resident / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);
       int skip = w_share >= 8 && ((tl.tile / w_share) & 1) ? (tl.tile % w_share) * (BN / BQ) : 0;
       skip = max(0, min(skip, nqb - 1));
       // Step order as in the four-wave kernel.  The copies of a step's operands run two steps ahead, one by one behind the
@@ -1206,8 +1235,37 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdPar
       }
     }
     prof_end(pa, p.prof, wave);
+    if constexpr (DIRECT) break;
   }
   prof_write(pa, p.prof, tid);
+}
+template <int DQK, int DV>
+__global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdParams p) {
+  dkdv8_items<DQK, DV>(p, 0, (int)gridDim.x);
+}
+
+// dK/dV and dQ in one launch, for packs of few rounds: neither needs the other, and with two launches the chip is partly
+// idle at the end of each (a dK/dV item is as long as its sample, and the second launch waits for the last one).  Every
+// workgroup takes one item, dispatched in order, without queues: a dK/dV item, or dQ of one tile for two query heads.
+// interleave = 0: dK/dV first (its items are the longer ones), then dQ.  interleave = 1: both worklists (longest first)
+// in proportion, eight workgroups, one a die, at a time; so the launch ends with the shortest items of both and not with
+// all of dQ.  Measured lines and gains: see one_launch().
+// Tried and dropped: dQ in pairs of heads in a launch of its own with queues (.86 to 1.02 of the present one's speed).
+template <int DQK, int DV, bool SHARED>
+__global__ __launch_bounds__(2 * kThreads, 2) void bwd_both_kernel(const BwdParams p, int n_dkdv, int n_dq, int n_resident,
+                                                                   int interleave) {
+  bool is_dkdv = (int)blockIdx.x < n_dkdv;
+  int block = is_dkdv ? (int)blockIdx.x : (int)blockIdx.x - n_dkdv;
+  if (interleave) {  // of the first k groups of eight, ceil(k groups_dkdv / groups) are dK/dV
+    const uint32_t groups_dkdv = (uint32_t)(n_dkdv + kNumXcd - 1) / kNumXcd;
+    const uint32_t groups = groups_dkdv + (uint32_t)(n_dq + kNumXcd - 1) / kNumXcd, k = blockIdx.x / kNumXcd;
+    const uint32_t in_front = (k * groups_dkdv + groups - 1) / groups;
+    is_dkdv = ((k + 1) * groups_dkdv + groups - 1) / groups > in_front;
+    block = (int)(kNumXcd * (is_dkdv ? in_front : k - in_front) + blockIdx.x % kNumXcd);
+    if (block >= (is_dkdv ? n_dkdv : n_dq)) return;
+  }
+  if (is_dkdv) dkdv8_items<DQK, DV, true>(p, block, n_resident);
+  else dq_items<DQK, DV, 2, SHARED>(p, block);
 }
 
 // dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  Workgroups (x, y):
@@ -1297,7 +1355,7 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
 //            three and more      25: 1.01 (four) and 1.11 (eight); 60: 1.00 and 1.10; 250: 1.08; 1000: 1.06
 //   d = 64, one                  25: 1.01; 60: 1.00; 126: .94 to .99; 240: 1.00 to 1.07; 800: 1.03 to 1.08
 // With no more items than compute units the launch is as long as its longest item: eight from 100 tokens a sample on
-// (.995 to 1.39; of 60: .96 to .99).
+// (.995 to 1.39; of 60: .96 to .99).  Where dK/dV and dQ go in one launch there are always eight: see one_launch().
 static bool eight_waves(int d, const BwdParams& p) {
   const double len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
   const int heads = p.g / p.n_split;
@@ -1305,11 +1363,42 @@ static bool eight_waves(int d, const BwdParams& p) {
   const double steps = heads * (len / 128 + 1);
   return d == 64 ? steps >= 2.5 : heads >= 3 || steps >= (heads == 2 ? 6.5 : 10);
 }
+// dK/dV and dQ in one launch (bwd_both_kernel), and with their items interleaved?  `rounds`: dK/dV items to a compute
+// unit; heads: query heads an item loops over; len: tokens a sample.  Time of the backward, two launches / one, T = 512 to
+// 50000; samples of 60, 250, 800, 3000 (log-normal) and one sample of .4 or .5 of the pack among short ones:
+//   one head     interleaved.  To 1 round 1.3 to 1.75; to 3: 1.1 to 1.8.  Dispatched dK/dV first .94 to 1.6.
+//     d = 64     to 7.5: 1.00 to 1.36; 8.2 to 12.9, len >= 900: .97 to 1.03; len <= 320, to 19: 1.01 to 1.08
+//     d = 128    len 150 to 1500, to 15: 1.01 to 1.20; 18 to 25: .95 to 1.04
+//                shorter, to 8: 1.02 to 1.18; 8.6 to 12.7: .95 to 1.01; longer, to 9: 1.00 to 1.10; 12.5: .98 to 1.06
+//   more heads   dK/dV first.  To 1 round 1.16 to 1.9.  Interleaved, two heads: .84 to 1.5 (as many dQ items as dK/dV, so
+//                every second group of a die, and these go to the same of its shader engines); from four: .90 to 1.1
+//     two        to 4: 1.03 to 1.63; 4.2: .99 to 1.04; len <= 320, to 5: 1.05 to 1.08
+//     to five    to 4: 1.01 to 1.38 (d = 64, 3.1: .99, so to 2.9 there); 4.2 to 5.3: .98 to 1.02; len <= 100, to 12:
+//                1.01 to 1.13
+//     to eight   to 2.7: 1.00 to 1.29; 3.1 to 3.6: .97 to 1.03; len <= 100, to 12: 1.00 to 1.07.  Not measured beyond.
+enum Launches { kTwo, kOne, kOneInterleaved };
+static Launches one_launch(int d, const BwdParams& p) {
+  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || (double)p.n_q_tiles * p.Hq > 64 * 512) return kTwo;  // 49 rounds of dQ measured
+  const int heads = p.g / p.n_split;
+  const double rounds = (double)p.n_tiles * p.Hkv * p.n_split / 256, len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
+  if (heads == 1) {
+    const bool one = d == 64 ? rounds <= 7.5 || (len <= 320 && rounds <= 19)
+                             : rounds <= 8 || (len >= 150 && rounds <= (len <= 1500 ? 15 : 9));
+    return !one ? kTwo : p.Hq > 1 ? kOneInterleaved : kOne;
+  }
+  if (heads == 2) return rounds <= 4 || (len <= 320 && rounds <= 5) ? kOne : kTwo;
+  const double most = heads <= 5 ? (d == 64 ? 2.9 : 4) : 2.7;
+  return heads <= 8 && (rounds <= most || (len <= 100 && rounds <= 12)) ? kOne : kTwo;
+}
 template <int DQK, int DV>
-static int launch_dkdv8(const BwdParams& p, int grid, hipStream_t s) {
+constexpr int dkdv8_lds() {
   constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + (DQK > 64 ? 128 * DQK * 2 : 0) + 2 * 3 * 1024;
   constexpr int sums = 8 * DQK / 32 * 4096;
-  constexpr int lds = tiles > sums ? tiles : sums;
+  return tiles > sums ? tiles : sums;
+}
+template <int DQK, int DV>
+static int launch_dkdv8(const BwdParams& p, int grid, hipStream_t s) {
+  constexpr int lds = dkdv8_lds<DQK, DV>();
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute((const void*)bwd_dkdv8_kernel<DQK, DV>,
@@ -1321,12 +1410,38 @@ static int launch_dkdv8(const BwdParams& p, int grid, hipStream_t s) {
   return 0;
 }
 
+template <int DQK, int DV, bool SHARED>
+static int launch_both(BwdParams p, int n_resident, bool interleave, hipStream_t s) {
+  constexpr int lds_dq = (SHARED ? 2 : 4) * 64 * (DQK * 2 + DV * 2), lds_dkdv = dkdv8_lds<DQK, DV>();
+  constexpr int lds = lds_dq > lds_dkdv ? lds_dq : lds_dkdv;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)bwd_both_kernel<DQK, DV, SHARED>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return (int)e;
+    attr_set = true;
+  }
+  if (SHARED) p.n_split_dq = heads_split(p.Hkv, p.g / 2);  // its items are pairs of heads
+  const int n_dkdv = p.n_tiles * p.Hkv * p.n_split, n_dq = p.n_q_tiles * ((p.Hq + 1) / 2);
+  auto whole = [](int n) { return (n + kNumXcd - 1) / kNumXcd * kNumXcd; };
+  const int grid = interleave ? whole(n_dkdv) + whole(n_dq) : n_dkdv + n_dq;
+  hipLaunchKernelGGL((bwd_both_kernel<DQK, DV, SHARED>), dim3(grid), dim3(2 * kThreads), lds, s, p, n_dkdv, n_dq,
+                     n_resident, (int)interleave);
+  return (int)hipGetLastError();
+}
+
 template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
   constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
   constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
-  bool eight = false;
-  if constexpr (DQK == DV) eight = grid_dkdv > 0 && eight_waves(DQK, p);
+  bool eight = false, both = false, interleave = false;
+  if constexpr (DQK == DV) {
+    const Launches way = one_launch(DQK, p);
+    eight = grid_dkdv > 0 && (way != kTwo || eight_waves(DQK, p));
+    // a call that asks for records or events of either kernel keeps two launches (and gets the same bits)
+    both = way != kTwo && !p.prof && !p.prof_dq && !ev[0] && !ev[2];
+    interleave = way == kOneInterleaved;
+  }
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)bwd_dq_kernel<DQK, DV>,
@@ -1342,15 +1457,22 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
   hipLaunchKernelGGL((bwd_prepass_kernel<DV>), dim3(pre_grid ? pre_grid : 1), dim3(kThreads), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
+  if constexpr (DQK == DV) {
+    if (both) {
+      const int err = p.g % 2 == 0 ? launch_both<DQK, DV, true>(p, grid_dkdv, interleave, s)
+                                   : launch_both<DQK, DV, false>(p, grid_dkdv, interleave, s);
+      if (err) return err;
+    }
+  }
   if (grid_dkdv > 0) {
     if (ev[0] && hipEventRecord(ev[0], s) != hipSuccess) return (int)hipErrorInvalidValue;
     if constexpr (DQK == DV) {
-      if (eight) {
+      if (eight && !both) {
         const int err = launch_dkdv8<DQK, DV>(p, grid_dkdv, s);
         if (err) return err;
       }
     }
-    if (!eight)
+    if (!eight && !both)
       hipLaunchKernelGGL((bwd_dkdv_kernel<DQK, DV>), dim3(grid_dkdv), dim3(kThreads), lds_dkdv, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
@@ -1363,7 +1485,7 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
     }
     if (ev[1] && hipEventRecord(ev[1], s) != hipSuccess) return (int)hipErrorInvalidValue;
   }
-  if (grid_dq > 0) {
+  if (grid_dq > 0 && !both) {
     if (ev[2] && hipEventRecord(ev[2], s) != hipSuccess) return (int)hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_dq_kernel<DQK, DV>), dim3(grid_dq), dim3(kThreads), lds_dq, s, p);
     e = hipGetLastError();

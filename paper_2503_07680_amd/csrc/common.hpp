@@ -222,17 +222,17 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 
 // Tile copy with the lane-dependent part (LDS row, swizzled chunk) packed once per kernel.  Rows
 // >= rows_valid re-read the last valid row (never out of bounds; the caller masks their products).
-template <int D, int ROWS>
+template <int D, int ROWS, int NW = 4>
 struct TileLoader {
   static constexpr int RB = D * 2;
   static constexpr int N_INSTR = ROWS * RB / 1024;
-  static constexpr int PER_WAVE = (N_INSTR + 3) / 4;
+  static constexpr int PER_WAVE = (N_INSTR + NW - 1) / NW;  // NW waves share the tile's copies
   uint32_t rc[PER_WAVE];  // (row << 16) | byte offset of the source chunk inside its row
 
   __device__ __forceinline__ void init(int wave, int lane) {
 #pragma unroll
     for (int ii = 0; ii < PER_WAVE; ++ii) {
-      const int pos = (wave + 4 * ii) * 1024 + lane * 16;
+      const int pos = (wave + NW * ii) * 1024 + lane * 16;
       const int row = pos / RB, cpos = (pos % RB) / 16;
       rc[ii] = ((uint32_t)row << 16) | (uint32_t)(swz<D>(cpos, row) * 16);
     }
@@ -242,8 +242,8 @@ struct TileLoader {
   // g: first row of the tile (wave-uniform); row * stride_bytes fits 32 bits.
   __device__ __forceinline__ void issue_one(int ii, const uint16_t* g, uint32_t stride_bytes, int rows_valid,
                                             const char* lds_tile, int wave) const {
-    const int inst = wave + 4 * ii;
-    if (N_INSTR % 4 != 0 && inst >= N_INSTR) return;
+    const int inst = wave + NW * ii;
+    if (N_INSTR % NW != 0 && inst >= N_INSTR) return;
     const uint32_t last = (uint32_t)(rows_valid - 1);
     const uint32_t row = rc[ii] >> 16;
     const uint32_t off = __umul24(row < last ? row : last, stride_bytes) + (rc[ii] & 0xffffu);
