@@ -311,12 +311,21 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
 
   // -inf stands for "no entry": its exponent offset is taken as 0 so that no inf - inf appears
   auto finite_or_zero = [](float m) { return m == -INFINITY ? 0.f : m; };
+  // The instruction itself: fmaxf of unpacked bits costs another maximum an operand to quieten a NaN, 11 of a chunk's 58
+  // instructions.  (A NaN among the entries makes the sum, and so the row's loss, a NaN whatever the maximum is.)
+  auto max3 = [](float a, float b, float c) {
+    float m = a;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+#endif
+    return m;
+  };
   // running (maximum, sum of exponentials) of this thread's entries, base 2 with log2(e) folded in
   float mx = -INFINITY, sm = 0.f;
   auto add_to_stats = [&](const u32x4& v) {
     float m_new = mx;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m_new = fmaxf(m_new, fmaxf(bf16_lo(v[k]), bf16_hi(v[k])));
+    for (int k = 0; k < 4; ++k) m_new = max3(m_new, bf16_lo(v[k]), bf16_hi(v[k]));
     const float m2 = finite_or_zero(m_new) * kLog2eF;
     float a = 0.f;
 #pragma unroll
@@ -365,6 +374,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
           zl = __uint_as_float((uint32_t)p.logits[rr * p.stride_t + lab] << 16);
         } else {
           lab = -1;
+          if (HOLD && !WITH_GRAD) p.token_loss[rr] = p.weighted[rr] = 0.f;
         }
       }
       row_label[tid] = lab;
@@ -374,6 +384,80 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     __syncthreads();
   };
   if (r >= row_end) return;
+  // log2-sum-exp2 of a row from every thread's statistics; one barrier.  parity: which set of the slots
+  auto row_lse2 = [&](int parity) {
+    const float m_wave = wave_max(mx);
+    sm *= __builtin_amdgcn_exp2f((finite_or_zero(mx) - finite_or_zero(m_wave)) * kLog2eF);
+    sm = wave_sum(sm);
+    if ((tid & 63) == 0) {
+      slot_m[parity][tid >> 6] = m_wave;
+      slot_s[parity][tid >> 6] = sm;
+    }
+    __syncthreads();
+    float m_row = slot_m[parity][0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) m_row = fmaxf(m_row, slot_m[parity][i]);
+    const float m_row0 = finite_or_zero(m_row);
+    float s_row = 0.f;
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+      s_row += slot_s[parity][i] * __builtin_amdgcn_exp2f((finite_or_zero(slot_m[parity][i]) - m_row0) * kLog2eF);
+    return m_row0 * kLog2eF + __builtin_amdgcn_logf(s_row);
+  };
+  if constexpr (HOLD && !WITH_GRAD) {
+    // HBM-bound, reads alone.  A chunk is done with once it is in the statistics, so its registers take the same chunk of
+    // the next row that has a loss at once: a whole row is always under way, over the reduction and over rows without a
+    // loss too.  (The loop below waits for each load kLag chunks later, which is enough between the gradient's stores:
+    // with it T = 4096, V = 151936, 30 % of the rows without a loss: 169 us, 5.1 TB/s; this way 146, 5.9.  V = 128256:
+    // 146 -> 124; 65536: 79 -> 68; 50304: 66 -> 54; 32000: 40.6 -> 38.0; 4096: 17.9 -> 14.0; T = 1000, V = 65536: 30 -> 23.)
+    // through a descriptor of the row: no address arithmetic for the vector unit, and the last chunk needs no clamp (the
+    // offset opaque, or the compiler moves a load from the iteration before to its use)
+    auto load_in_row = [&](int row, int c) {
+      const auto src = __builtin_amdgcn_make_buffer_rsrc((void*)(p.logits + (int64_t)row * p.stride_t), 0, 2 * p.V, 0x00020000);
+      return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, fresh(byte_in_chunk), c * 2 * kCeChunk, 2 /* nt */));
+    };
+    for (int base = r, parity = 0; base < row_end; base += kRowBatch) {
+      stage_rows(base);
+      const int n = min(row_end - base, kRowBatch);
+      auto next_live = [&](int i) {  // the first row from i on with a loss; n: none
+        while (i < n && row_label[i] < 0) ++i;
+        return __builtin_amdgcn_readfirstlane(i);
+      };
+      int i = next_live(0);
+      if (i == n) continue;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) held[c] = load_in_row(base + i, c);
+      while (i < n) {
+        const int i_next = next_live(i + 1);
+        if (i_next < n) {
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            add_to_stats(entries(held[c], c));
+            held[c] = load_in_row(base + i_next, c);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          // opaque: what both sides compute from a chunk is otherwise moved in front of the branch, for all chunks, with
+          // registers that are not there
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            add_to_stats(entries(fresh(held[c]), c));
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        const float ce = row_lse2(parity) * kLn2F - row_zlabel[i];
+        if (tid == 0) {
+          p.token_loss[base + i] = ce;
+          p.weighted[base + i] = row_weight[i] * ce;
+        }
+        parity ^= 1;
+        mx = -INFINITY;
+        sm = 0.f;
+        i = i_next;
+      }
+    }
+    return;
+  }
   stage_rows(r);
   int label = row_label[0];  // -1: no loss
   float w = row_weight[0], z_label = row_zlabel[0];
@@ -401,24 +485,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
       if (!HOLD) {
         for (int c = 0; c < my_chunks; ++c) add_to_stats(*chunk_ptr(row, c));
       }
-      // wave, then workgroup
-      const float m_wave = wave_max(mx);
-      sm *= __builtin_amdgcn_exp2f((finite_or_zero(mx) - finite_or_zero(m_wave)) * kLog2eF);
-      sm = wave_sum(sm);
-      if ((tid & 63) == 0) {
-        slot_m[parity][tid >> 6] = m_wave;
-        slot_s[parity][tid >> 6] = sm;
-      }
-      __syncthreads();
-      float m_row = slot_m[parity][0];
-#pragma unroll
-      for (int i = 1; i < NW; ++i) m_row = fmaxf(m_row, slot_m[parity][i]);
-      const float m_row0 = finite_or_zero(m_row);
-      float s_row = 0.f;
-#pragma unroll
-      for (int i = 0; i < NW; ++i)
-        s_row += slot_s[parity][i] * __builtin_amdgcn_exp2f((finite_or_zero(slot_m[parity][i]) - m_row0) * kLog2eF);
-      const float lse2 = m_row0 * kLog2eF + __builtin_amdgcn_logf(s_row);  // log2-sum-exp2 of the row
+      const float lse2 = row_lse2(parity);
       const float ce = lse2 * kLn2F - z_label;
       lse2w = lse2 - __builtin_amdgcn_logf(w);  // w exp2(x - lse2) = exp2(x - lse2w)
       if (tid == 0) {
@@ -459,11 +526,9 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
         // No store or load of this loop sits in a branch on a uniform condition (the arithmetic does):
         // with one there the compiler waits for ALL outstanding memory operations at every use of a
         // loaded chunk instead of for that chunk's load.
-        if (WITH_GRAD) {
-          const u32x4 g = chunk_grad(held[c], c);
-          if (c < NCH - 1) __builtin_nontemporal_store(g, chunk_ptr(grow, c));
-          else if (tail_valid) __builtin_nontemporal_store(g, chunk_ptr(grow, c));
-        }
+        const u32x4 g = chunk_grad(held[c], c);
+        if (c < NCH - 1) __builtin_nontemporal_store(g, chunk_ptr(grow, c));
+        else if (tail_valid) __builtin_nontemporal_store(g, chunk_ptr(grow, c));
         if (fetch_next) {
           held[c] = load_chunk(row_next, c);
           if (c >= kLag) add_to_stats(entries(held[c - kLag], c - kLag));
@@ -501,11 +566,15 @@ __global__ __launch_bounds__(kCeThreads) void ce_reduce_kernel(const CeParams p)
 // the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
 // many and with one more.  With the gradient: V = 32000: 30.5 / 65.5 / 190 and 34.1 / 65.8 / 193; 45056: 41.1 / 86.8 /
 // 267 and 44.3 / 87.1 / 270; 28672: 30.4 / 57.2 / 174 and 28.0 / 60.0 / 174; 16384: 19.2 / 35.7 / 103 and 19.3 / 38.5 /
-// 104.  Without it: 24576: 14.6 / 26.0 / 60.8 and 16.1 / 25.1 / 58.8; with one fewer, 40960: 18.3 / 35.6 / 86 and
-// 21.2 / 38.1 / 102.
+// 104.
+// Without it a workgroup has a row under way whatever its work is, so fewer are enough.  With 1 / 2 / 4 of 256 threads,
+// V = 4096: 9.9 / 9.7 / 8.9, 16.0 / 13.4 / 11.8 and 37 / 28 / 23; 8000: 10.6 / 10.5 / 9.8, 17 / 15 / 14, 41 / 32 / 29 (8:
+// 13.3 and 14.7 at T = 2500); with 1 / 2 of 512, V = 32000: 16.0 / 18.1, 26.6 / 29.3, 68 / 70; 65536: 24.6 / 29.7, 43.5 /
+// 49.0, 130 / 129.
 constexpr int ce_most_per_cu(int nt, int nch, bool with_grad) {
-  if (nt == 256) return !with_grad || nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
-  if (nt == 512) return nch <= 5 ? 4 : !with_grad || nch <= 7 ? 3 : 2;
+  if (!with_grad) return nt == 256 ? 4 : 1;
+  if (nt == 256) return nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
+  if (nt == 512) return nch <= 5 ? 4 : nch <= 7 ? 3 : 2;
   return 2;
 }
 
@@ -565,20 +634,20 @@ static bool launch_held(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t e
 // else to run on the compute unit if the workgroup fills it; several smaller workgroups overlap theirs.  A
 // longer row has to be spread over more threads to be held.  us at T = 8192 with the gradient / without:
 //   V        1024 threads   512          256
-//   4096      65 /  41       41 /  29     37 /  28
-//   16384    111 /  56      104 /  46    104 /  46
-//   32000    192 / 104      192 /  74    195 /  84
-//   65536    381 / 164      375 / 146
-//   81920    476 / 194      473 / 178
+//   4096      65 /  41       41 /  27     37 /  22
+//   16384    111 /  50      104 /  42    104 /  43
+//   32000    192 /  70      192 /  68    195 /  72
+//   65536    381 / 130      375 / 130
+//   81920    476 / 156      473 / 157
 // With few rows, T = 64 / 1000 with the gradient:
 //   4096      9.5 / 17.4     8.3 / 12.5     8.3 / 10.5
 //   16384    10.8 / 23.0    10.0 / 20.3    10.3 / 19.9
 //   32000    13.0 / 33.0    12.3 / 30.5    14.2 / 31.5
 // A call whose workgroups have a row each (two of 512 threads a compute unit) is as long as the compute units with
 // two rows; 1024 threads have half the chain a row and, with one workgroup a compute unit, ranges cut by cost.
-// T = 280 / 512 without the gradient, 1024 threads and 512: V = 81920: 14.1 / 21.4 and 21.1 / 21.8; 65536: 13.2 / 19.0
-// and 17.8 / 18.8; 57344: 12.5 / 17.6 and 16.6 / 17.3; with it, 81920: 24.0 / 40.1 and 27.1 / 42.1; 65536: 21.2 / 33.6
-// and 26.2 / 34.7; T = 256, 57352: 18.3 and 17.3.
+// T = 280 / 512 with the gradient, 1024 threads and 512: V = 81920: 24.0 / 40.1 and 27.1 / 42.1; 65536: 21.2 / 33.6 and
+// 26.2 / 34.7; T = 256, 57352: 18.3 and 17.3.  Without it both have one workgroup a compute unit and are alike (81920:
+// 14.0 / 21.8 and 14.3 / 21.3; 65536: 12.8 / 19.2 and 13.0 / 19.4); the line is the same, so the losses are the same bits.
 constexpr int kCeRow256 = 16384, kCeRow512 = 81920, kCeRow512Few = 61440;  // Few: a row a workgroup at most
 
 int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
