@@ -534,6 +534,7 @@ struct FwdParams {
   int32_t* counter;
   hbp_profile_rec* prof;
   int32_t n_split;   // the query heads of a kv head are dealt to the dies in this many parts (see heads_split)
+  int32_t halves;    // 1: n_tiles counts halves of 256-row tiles
 };
 
 struct BwdParams {

@@ -331,7 +331,13 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
       if (n_done == 0) t_first = t0;
     }
 
-    const hbp_tile tl = p.tiles[tile_idx];
+    // halves (see fwd_way): the list has 256-row tiles and a workgroup takes 128 rows of one.  Which half of a pair comes
+    // first goes by the parity of the bits of its number: short samples have no second half, and an order with a period
+    // of two or four would leave the empty ones to the same of a die's four shader engines, to which its workgroups are
+    // dealt in turn (samples of 60 tokens, 12000 tokens, 24 heads of 128: .84 of the 256-row tiles' speed in plain order,
+    // 1.23 this way).
+    const int halves = HP * TP == 1 ? p.halves : 0, half = __builtin_popcount(tile_idx) & halves;
+    const hbp_tile tl = p.tiles[tile_idx >> halves];
     bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
     int s0 = 0, s1 = 0;
     if (ok) {
@@ -340,10 +346,11 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
       // tiles start a multiple of 32 rows into their sample: each wave then has exactly one key
       // block that crosses its diagonal
       ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
-           tl.row_end <= s1 && tl.row_end - tl.row_begin <= BM && (tl.row_begin - s0) % 32 == 0;
+           tl.row_end <= s1 && tl.row_end - tl.row_begin <= BM << halves && (tl.row_begin - s0) % 32 == 0 &&
+           tl.row_begin + BM * half < tl.row_end;
     }
     if (ok) {
-      const int r0 = tl.row_begin, r1 = tl.row_end;
+      const int r0 = tl.row_begin + BM * half, r1 = halves ? min(r0 + BM, tl.row_end) : tl.row_end;
       const int kh = h / p.g;
       const int qw0 = r0 - s0 + 32 * rw;  // in-sample index of this wave's first query
       const int my_row = r0 + 32 * rw + l32;
@@ -583,12 +590,28 @@ static int launch_fwd_hp(FwdParams p, bool direct, int n_cu, hipStream_t s, hipE
 //     else           pairs, 2 to 2.7: 1.00 to 1.10; 3.1: .98; singles, 2.5: .98 to 1.03
 //   odd              256-row tiles, to 3.5: 1.00 to 1.52; 3.6: .99; 4.2 to 4.7: .97 to 1.03; samples to 128, 4.0 to 5.5:
 //                    1.04 to 1.14
+//   odd, kHalves     a workgroup of four wavefronts takes half of a 256-row tile: the longest item's chain of key tiles runs
+//                    without a second wavefront on its SIMD.  Against 256-row tiles, mixed samples and one of .4 or .5:
+//     d = 64         to 4.2: 1.00 to 1.31; 4.5: .97 to 1.09; len to 320, to 7.5: 1.01 to 1.24
+//     d = 128        to .75: 1.02 to 1.23; .8 to 2: .93 to 1.17; len to 350, to 9: 1.02 to 1.42; 11 to 22: .95 to 1.10
+//     d = 192        to 2.3: 1.01 to 1.21; 3 to 4.5: .97 to 1.13; len to 350, to 6: 1.01 to 1.20; 7.4: .99
+//     len to 100     from 1.05 on: 1.10 to 1.45, and packs of that mean with a long sample .97 to 1.02 to T = 16384; with a
+//                    round or less: .97 to 1.03
 // Beyond two rounds only for packs that cannot hold a very long sample beside the short ones (the host knows their mean
 // alone): 9500 tokens with a sample of 7125, 16/8 heads of 128: .96; 20000 with one of 15000, 8 heads of 64: .98.
-enum FwdWay { kQueues, kDirect, kSingles };
+enum FwdWay { kQueues, kDirect, kSingles, kHalves };
 static FwdWay fwd_way(const FwdParams& p, int d_qk, int64_t n_items, int n_cu) {
   if (p.prof) return kQueues;  // records are one per resident workgroup
   const double rounds = (double)n_items / n_cu, len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
+  if (p.g % 2 && rounds <= 300) {
+    if (len <= 100) {
+      if (rounds > 1.05 && p.T <= 16384) return kHalves;
+    } else if (d_qk == 64 ? rounds <= 4.2 || (len <= 320 && rounds <= 7.5)
+                          : d_qk == 128 ? rounds <= 0.75 || (len <= 350 && rounds <= 9)
+                                        : rounds <= 2.3 || (len <= 350 && rounds <= 6)) {
+      return kHalves;
+    }
+  }
   if (rounds <= 2) return kSingles;
   if (p.T > (p.g % 2 || d_qk == 64 ? 16384 : 8192)) return kQueues;
   if (p.g % 2) return rounds <= 3.5 || (len <= 128 && rounds <= 5.5) ? kDirect : kQueues;
@@ -606,8 +629,14 @@ static int launch_fwd_t(const FwdParams& p, int tile_rows, int n_cu, hipStream_t
     return way == kSingles ? launch_fwd_hp<DQK, DV, 1, 1>(p, true, n_cu, s, ev0, ev1)
                            : launch_fwd_hp<DQK, DV, 2, 1>(p, way == kDirect, n_cu, s, ev0, ev1);
   }
-  if (tile_rows == 256)
-    return launch_fwd_hp<DQK, DV, 1, 2>(p, fwd_way(p, DQK, (int64_t)p.n_tiles * p.Hq, n_cu) != kQueues, n_cu, s, ev0, ev1);
+  if (tile_rows == 256) {
+    const FwdWay way = fwd_way(p, DQK, (int64_t)p.n_tiles * p.Hq, n_cu);
+    if (way != kHalves) return launch_fwd_hp<DQK, DV, 1, 2>(p, way != kQueues, n_cu, s, ev0, ev1);
+    FwdParams halved = p;
+    halved.n_tiles *= 2;
+    halved.halves = 1;
+    return launch_fwd_hp<DQK, DV, 1, 1>(halved, true, n_cu, s, ev0, ev1);
+  }
   return launch_fwd_hp<DQK, DV, 1, 1>(p, false, n_cu, s, ev0, ev1);
 }
 
