@@ -1314,34 +1314,65 @@ size_t bwd_partial_floats(int T, int Hkv, int g, int dim) {
   return n_split > 1 ? (size_t)n_split * (size_t)T * (size_t)Hkv * (size_t)dim : 0;
 }
 
-// D[h,r] = sum_x dO[r,h,x] O[r,h,x], LSE2 = LSE*log2(e); resets both scheduler counters.
-template <int DV>
-__global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p) {
-  constexpr int LPR = DV / 8;  // lanes per (row, head): 16 bytes of O and dO each
-  if (blockIdx.x == 0 && threadIdx.x < kNumXcd) {
-    if (p.counter) p.counter[threadIdx.x * kCounterStride] = 0;
-    if (p.counter_dq) p.counter_dq[threadIdx.x * kCounterStride] = 0;
+// D[h,r] = sum_x dO[r,h,x] O[r,h,x], LSE2 = LSE*log2(e); resets both scheduler counters.  HBM-bound: O and dO are read
+// once.  A workgroup takes PAIRS (row, head) pairs: 1 to 8 heads (the largest power of two up to Hq) of as many rows as
+// make up the rest, DV / 8 lanes of 16 bytes a pair.  Eight passes' loads are under way at a time, and the lanes' sums are
+// added up through LDS by a thread a pair, which then has consecutive rows beside it: D, LSE and LSE2 in whole lines.
+// With 256 pairs a workgroup against one part of a pair a thread (and 4-byte accesses), us: 8192 tokens, 32 heads of 128:
+// 27.4 -> 24.2; 24 heads: 24.7 -> 16.8; 32768 tokens, 32 heads: 108 -> 99 (5.4 TB/s); 65536, 64 heads: 421 -> 395.  Up to
+// kPreSmall pairs 64 a workgroup, or too few loads are under way: 2048 tokens, 32 heads: 7.96 -> 6.88 (256 pairs: 8.12).
+constexpr int64_t kPreSmall = 131072;
+inline int prepass_heads_log2(int Hq) { return Hq >= 8 ? 3 : Hq >= 4 ? 2 : Hq >= 2 ? 1 : 0; }
+template <int DV, int PAIRS>
+__global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p, int heads_log2) {
+  constexpr int LPR = DV / 8, PER_PASS = kThreads / LPR, PASSES = PAIRS / PER_PASS, BATCH = PASSES < 8 ? PASSES : 8;
+  constexpr int PAIRS_LOG2 = __builtin_ctz(PAIRS);
+  static_assert(PAIRS <= kThreads && PAIRS % PER_PASS == 0 && PASSES % BATCH == 0, "a thread a pair at the end");
+  __shared__ float sums[PAIRS * (LPR + 1)];
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid < kNumXcd) {
+    if (p.counter) p.counter[tid * kCounterStride] = 0;
+    if (p.counter_dq) p.counter_dq[tid * kCounterStride] = 0;
   }
-  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t rh = gid / LPR;
-  const int part = (int)(gid % LPR);
-  const bool valid = rh < (int64_t)p.T * p.Hq;
-  float acc = 0.f;
-  if (valid) {
-    const int64_t r = rh / p.Hq;
-    const int h = (int)(rh % p.Hq);
-    const int64_t off = r * p.o_st + (int64_t)h * p.o_sh + 8 * part;
-    const u32x4 a = *(const u32x4*)(p.o + off);
-    const u32x4 b = *(const u32x4*)(p.d_o + off);
+  const int heads = 1 << heads_log2, rows_log2 = PAIRS_LOG2 - heads_log2, rows = 1 << rows_log2;
+  const int head_blocks = (p.Hq + heads - 1) >> heads_log2;
+  const int h0 = (int)(blockIdx.x % (unsigned)head_blocks) << heads_log2;
+  const int64_t r0 = (int64_t)(blockIdx.x / (unsigned)head_blocks) << rows_log2;
+  const int part = tid % LPR;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc += bf16_lo(a[i]) * bf16_lo(b[i]) + bf16_hi(a[i]) * bf16_hi(b[i]);
+  for (int first = 0; first < PASSES; first += BATCH) {
+    u32x4 a[BATCH], b[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int pair = (first + i) * PER_PASS + tid / LPR;  // heads innermost
+      const int64_t r = min(r0 + (pair >> heads_log2), (int64_t)p.T - 1);  // beyond the end: the last one, not stored
+      const int h = min(h0 + (pair & (heads - 1)), p.Hq - 1);
+      const int64_t off = r * p.o_st + (int64_t)h * p.o_sh + 8 * part;
+      a[i] = __builtin_nontemporal_load((const u32x4*)(p.o + off));
+      b[i] = *(const u32x4*)(p.d_o + off);
+    }
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int pair = (first + i) * PER_PASS + tid / LPR;
+      float acc = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc += bf16_lo(a[i][k]) * bf16_lo(b[i][k]) + bf16_hi(a[i][k]) * bf16_hi(b[i][k]);
+      sums[((((pair & (heads - 1)) << rows_log2) + (pair >> heads_log2)) * (LPR + 1)) + part] = acc;
+    }
   }
+  __syncthreads();
+  if (PAIRS < kThreads && tid >= PAIRS) return;
+  float s[LPR];
 #pragma unroll
-  for (int m = LPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-  if (valid && part == 0) {
-    const int64_t r = rh / p.Hq;
-    const int h = (int)(rh % p.Hq);
-    p.D[(int64_t)h * p.T + r] = acc;
+  for (int i = 0; i < LPR; ++i) s[i] = sums[tid * (LPR + 1) + i];
+#pragma unroll
+  for (int m = LPR / 2; m >= 1; m >>= 1)
+#pragma unroll
+    for (int i = 0; i < m; ++i) s[i] += s[i + m];
+  const int h = h0 + (tid >> rows_log2);
+  const int64_t r = r0 + (tid & (rows - 1));
+  if (h < p.Hq && r < p.T) {
+    p.D[(int64_t)h * p.T + r] = s[0];
     p.lse2[(int64_t)h * p.T + r] = p.lse[(int64_t)h * p.T + r] * kLog2e;
   }
 }
@@ -1367,9 +1398,9 @@ static bool eight_waves(int d, const BwdParams& p) {
 // unit; heads: query heads an item loops over; len: tokens a sample.  Time of the backward, two launches / one, T = 512 to
 // 50000; samples of 60, 250, 800, 3000 (log-normal) and one sample of .4 or .5 of the pack among short ones:
 //   one head     interleaved.  To 1 round 1.3 to 1.75; to 3: 1.1 to 1.8.  Dispatched dK/dV first .94 to 1.6.
-//     d = 64     to 7.5: 1.00 to 1.36; 8.2 to 12.9, len >= 900: .97 to 1.03; len <= 320, to 19: 1.01 to 1.08
-//     d = 128    len 150 to 1500, to 15: 1.01 to 1.20; 18 to 25: .95 to 1.04
-//                shorter, to 8: 1.02 to 1.18; 8.6 to 12.7: .95 to 1.01; longer, to 9: 1.00 to 1.10; 12.5: .98 to 1.06
+//     d = 64     to 5.5: 1.01 to 1.36; 5.9 to 12.9, len >= 900: .97 to 1.06; len <= 320, to 19: 1.01 to 1.08
+//     d = 128    to 6.5: 1.02 to 1.20; 8.5 to 12: .97 (a sample of .5 to .7, len 1400 to 3000) to 1.08
+//                len 150 to 350, to 15: 1.02 to 1.12; 18 to 25: .99 to 1.04; shorter, to 8: 1.02 to 1.18; to 12.7: .95 to 1.01
 //   more heads   dK/dV first.  To 1 round 1.16 to 1.9.  Interleaved, two heads: .84 to 1.5 (as many dQ items as dK/dV, so
 //                every second group of a die, and these go to the same of its shader engines); from four: .90 to 1.1
 //     two        to 4: 1.03 to 1.63; 4.2: .99 to 1.04; len <= 320, to 5: 1.05 to 1.08
@@ -1382,8 +1413,7 @@ static Launches one_launch(int d, const BwdParams& p) {
   const int heads = p.g / p.n_split;
   const double rounds = (double)p.n_tiles * p.Hkv * p.n_split / 256, len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
   if (heads == 1) {
-    const bool one = d == 64 ? rounds <= 7.5 || (len <= 320 && rounds <= 19)
-                             : rounds <= 8 || (len >= 150 && rounds <= (len <= 1500 ? 15 : 9));
+    const bool one = d == 64 ? rounds <= (len <= 320 ? 19 : 5.5) : rounds <= (len < 150 ? 8 : len <= 350 ? 15 : 6.5);
     return !one ? kTwo : p.Hq > 1 ? kOneInterleaved : kOne;
   }
   if (heads == 2) return rounds <= 4 || (len <= 320 && rounds <= 5) ? kOne : kTwo;
@@ -1452,9 +1482,13 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int64_t pre_threads = (int64_t)p.T * p.Hq * (DV / 8);
-  const unsigned pre_grid = (unsigned)((pre_threads + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL((bwd_prepass_kernel<DV>), dim3(pre_grid ? pre_grid : 1), dim3(kThreads), 0, s, p);
+  {
+    const bool small = (int64_t)p.T * p.Hq <= kPreSmall;
+    const int hl = prepass_heads_log2(p.Hq), rows = (small ? 64 : 256) >> hl;
+    const dim3 grid((unsigned)(((int64_t)p.T + rows - 1) / rows * ((p.Hq + (1 << hl) - 1) >> hl)));
+    if (small) hipLaunchKernelGGL((bwd_prepass_kernel<DV, 64>), grid, dim3(kThreads), 0, s, p, hl);
+    else hipLaunchKernelGGL((bwd_prepass_kernel<DV, 256>), grid, dim3(kThreads), 0, s, p, hl);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
   if constexpr (DQK == DV) {
