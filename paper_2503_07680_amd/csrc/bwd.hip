@@ -62,7 +62,7 @@ __device__ __forceinline__ void prof_write(const ProfAcc& a, hbp_profile_rec* pr
 // HALVES = 2 (see bwd_both_kernel): the workgroup has eight wavefronts, four for each of two neighbouring query heads of
 // the same tile, and takes the launch's item `block` alone.  SHARED: both heads read the same kv head and work off the
 // same tiles in LDS (half the copies); otherwise each half has its own.
-template <int DQK, int DV, int HALVES = 1, bool SHARED = false>
+template <int DQK, int DV, int HALVES = 1, bool SHARED = false, bool DIRECT = HALVES == 2>
 __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
   constexpr int BM = 128, BN = 64;
   constexpr int KRB = DQK * 2, VRB = DV * 2;
@@ -121,13 +121,13 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, h;
-    if constexpr (HALVES == 1) {
+    if constexpr (!DIRECT) {
       if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
     } else {
-      const Taken tk = SHARED ? direct_item_inline(wq.n_tiles, wq.Hkv, wq.per_kv, 0, 0, block)
+      const Taken tk = SHARED || HALVES == 1 ? direct_item_inline(wq.n_tiles, wq.Hkv, wq.per_kv, 0, 0, block)
                               : direct_item_inline(wq.n_tiles, (p.Hq + 1) / 2, 1, 0, 0, block);
       tile_idx = __builtin_amdgcn_readfirstlane(tk.tile_idx);
-      h = 2 * __builtin_amdgcn_readfirstlane(tk.head) + half;
+      h = HALVES * __builtin_amdgcn_readfirstlane(tk.head) + half;
     }
     prof_begin(pa, p.prof_dq, tid);
 
@@ -371,7 +371,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
       }
     }
     prof_end(pa, p.prof_dq, tid);
-    if constexpr (HALVES == 2) break;
+    if constexpr (DIRECT) break;
   }
   prof_write(pa, p.prof_dq, tid);
 }
@@ -381,8 +381,9 @@ __global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(co
 }
 
 // ----------------------------------------------------------------------------------- dK, dV
-template <int DQK, int DV>
-__global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p) {
+// DIRECT: the launch's item `block` and no other (see bwd_both4_kernel).  n_resident: workgroups under way at a time.
+template <int DQK, int DV, bool DIRECT = false>
+__device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_resident) {
   constexpr int BN = 128, BQ = 64;
   constexpr int QRB = DQK * 2, ORB = DV * 2;
   constexpr int Q_TILE = BQ * QRB, O_TILE = BQ * ORB;
@@ -444,7 +445,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   // is worth 3 % of the launch.  131072 tokens, 64/8 heads, d = 128, ms: loop at byte 40: 288.0, at 0: 292.3,
   // at 16: 294.6, at 24: 294.6, at 56: 294.5 (no other size was measured, nor heads of 64 and 192, which have no pad).
   // The launch's time is checked again whenever the code in front changes.
-  if constexpr (DQK == 128) asm volatile(".rept 11\n s_nop 0\n .endr");
+  if constexpr (DQK == 128) asm volatile(".rept 15\n s_nop 0\n .endr");
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
   // are cut into n_split runs of g_item heads, each an item of its own.
@@ -453,7 +454,13 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     int tile_idx, vh;
-    if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
+    if constexpr (DIRECT) {
+      const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
+      tile_idx = __builtin_amdgcn_readfirstlane(tk.tile_idx);
+      vh = __builtin_amdgcn_readfirstlane(tk.head);
+    } else {
+      if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
+    }
     const int kh = vh / p.n_split, part = vh - kh * p.n_split;
     const int head0 = vh * g_item;  // first query head of the item
     prof_begin(pa, p.prof, tid);
@@ -493,7 +500,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
       // the end; that set of w tiles ends together, the next one starts together, and so on in turns.  The
       // order is a function of the tile number alone, so the results do not depend on timing.
       // (With fewer than 8 workgroups per kv head there is little to share and the plain order is kept.)
-      const int w_share = (int)gridDim.x / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);  // heads in work at a time
+      const int w_share = n_resident / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);  // heads in work at a time
       int skip = w_share >= 8 && ((tl.tile / w_share) & 1) ? (tl.tile % w_share) * (BN / BQ) : 0;
       skip = max(0, min(skip, nqb - 1));
       const int first_blk = nqb - 1 - skip;
@@ -832,8 +839,20 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p
       }
     }
     prof_end(pa, p.prof, tid);
+    if constexpr (DIRECT) break;
   }
   prof_write(pa, p.prof, tid);
+}
+template <int DQK, int DV>
+__global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p) {
+  dkdv_items<DQK, DV>(p, 0, (int)gridDim.x);
+}
+// dK/dV and dQ in one launch at head size 192: workgroups of four wavefronts, an item of either each, dK/dV first (as
+// many dQ items as dK/dV: in turn they would keep to half of a die's shader engines each).
+template <int DQK, int DV>
+__global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams p, int n_dkdv, int n_resident) {
+  if ((int)blockIdx.x < n_dkdv) dkdv_items<DQK, DV, true>(p, (int)blockIdx.x, n_resident);
+  else dq_items<DQK, DV, 1, false, true>(p, (int)blockIdx.x - n_dkdv);
 }
 
 // ------------------------------------------------------------------- dK, dV, eight wavefronts
@@ -1420,6 +1439,13 @@ static Launches one_launch(int d, const BwdParams& p) {
   const double most = heads <= 5 ? (d == 64 ? 2.9 : 4) : 2.7;
   return heads <= 8 && (rounds <= most || (len <= 100 && rounds <= 12)) ? kOne : kTwo;
 }
+// The same at head size 192 (bwd_both4_kernel): two launches / one, T = 512 to 16384, 8, 16 and 128 heads and 12/4:  to 1
+// round 1.2 to 1.7; to 3: 1.04 to 1.77; to 4: 1.02 to 1.2; 4.2 to 5: .99 to 1.13; 6 to 10: .96 to 1.1; more: .95 to 1.0.
+// Items of several heads were not measured.
+static bool one_launch4(const BwdParams& p) {
+  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || (double)p.n_q_tiles * p.Hq > 64 * 512) return false;
+  return p.g == p.n_split && (double)p.n_tiles * p.Hkv * p.n_split / 256 <= 4;
+}
 template <int DQK, int DV>
 constexpr int dkdv8_lds() {
   constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + (DQK > 64 ? 128 * DQK * 2 : 0) + 2 * 3 * 1024;
@@ -1461,6 +1487,21 @@ static int launch_both(BwdParams p, int n_resident, bool interleave, hipStream_t
 }
 
 template <int DQK, int DV>
+static int launch_both4(const BwdParams& p, int n_resident, hipStream_t s) {
+  constexpr int lds = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);  // as dK/dV; dQ has no row sums there
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)bwd_both4_kernel<DQK, DV>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return (int)e;
+    attr_set = true;
+  }
+  const int n_dkdv = p.n_tiles * p.Hkv * p.n_split, n_dq = p.n_q_tiles * p.Hq;
+  hipLaunchKernelGGL((bwd_both4_kernel<DQK, DV>), dim3(n_dkdv + n_dq), dim3(kThreads), lds, s, p, n_dkdv, n_resident);
+  return (int)hipGetLastError();
+}
+
+template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
   constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
   constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
@@ -1471,6 +1512,8 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
     // a call that asks for records or events of either kernel keeps two launches (and gets the same bits)
     both = way != kTwo && !p.prof && !p.prof_dq && !ev[0] && !ev[2];
     interleave = way == kOneInterleaved;
+  } else {
+    both = one_launch4(p) && !p.prof && !p.prof_dq && !ev[0] && !ev[2];
   }
   static bool attr_set = false;
   if (!attr_set) {
@@ -1497,6 +1540,9 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
                                    : launch_both<DQK, DV, false>(p, grid_dkdv, interleave, s);
       if (err) return err;
     }
+  } else if (both) {
+    const int err = launch_both4<DQK, DV>(p, grid_dkdv, s);
+    if (err) return err;
   }
   if (grid_dkdv > 0) {
     if (ev[0] && hipEventRecord(ev[0], s) != hipSuccess) return (int)hipErrorInvalidValue;

@@ -22,3 +22,12 @@ def test_the_kernel_with_both(d, shared):
     assert near == []
     regs = int(re.search(r"\.name:\s+%s\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)" % name, text).group(1))
     assert regs <= 256
+
+
+def test_the_kernel_with_both_at_head_size_192():
+    text = backward_asm()
+    name = next(k for k in kernel_metadata(text) if "bwd_both4_kernelILi192E" in k)
+    ins = kernel_instructions(text, name)
+    assert early_reads_of_asm_mfma_results(ins) == [] and late_scalars_of_copies(ins) == []
+    assert not any(l.startswith("scratch_") for l in ins)
+    assert int(re.search(r"\.name:\s+%s\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)" % name, text).group(1)) <= 512

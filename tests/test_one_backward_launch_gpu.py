@@ -74,3 +74,20 @@ def test_rows_with_padding():
     case = Case([700, 129, 64, 31], 924, 8, 2, 128, 128, seed=404, name="one-launch-pad")
     pa, dev, out = run(case, row_pad=64)
     compare(case, pa, out)
+
+
+@pytest.mark.parametrize("Hq,Hkv,times", [(1, 1, 1), (3, 1, 1), (8, 8, 1), (12, 4, 1), (16, 16, 2), (128, 128, 1), (16, 8, 1)])
+def test_head_size_192(Hq, Hkv, times):  # the last: two heads an item, two launches
+    lengths = (EDGES if Hq < 128 else [129, 64, 300, 1, 31]) * times
+    case = Case(lengths, sum(lengths), Hq, Hkv, 192, 128, seed=405, name="one-launch-192-%d-%d" % (Hq, Hkv))
+    pa, dev, out = run(case)
+    g = Hq // Hkv
+    compare(case, pa, out, q_heads=sorted(set(range(g)) | set(range(Hq - g, Hq))))
+    check_dv_identity(case, pa, dev, out)
+
+
+@pytest.mark.parametrize("times", [64, 66])  # four rounds, and more
+def test_head_size_192_on_either_side_of_the_line(times):
+    case = Case([60] * times, 60 * times, 16, 16, 192, 128, seed=406, name="one-launch-192-line-%d" % times)
+    pa, dev, out = run(case)
+    compare(case, pa, out, q_heads=[0, 15])
