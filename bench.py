@@ -24,11 +24,12 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA (published)
 
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic_table.md")
-DOMINANT_KERNEL_SOURCES = ("bwd.hip", "common.hpp")   # what the backward key-tile kernel is compiled from
+# what the backward key-tile kernel is compiled from, and the rules that choose it
+DOMINANT_KERNEL_SOURCES = ("bwd.hip", "common.hpp", "attn_rules.hpp")
 
 
 def kernel_sources_digest() -> str:
-    """First 12 hex digits of the SHA-256 over the dominant kernel's source files: the key that ties a
+    """First 12 hex digits of the SHA-256 over the dominant kernel's source files and launch rules: the key that ties a
     measured traffic figure to the build it was measured on."""
     import hashlib
     h = hashlib.sha256()

@@ -8,7 +8,7 @@
 
 namespace {
 
-constexpr int kNumCU = 256;          // MI355X: 8 accelerator dies x 32 compute units
+using hbp::kNumCU;
 constexpr size_t kSetBytes = hbp::kNumXcd * hbp::kCounterStride * sizeof(int32_t);
 constexpr size_t kCounterBytes = 2 * kSetBytes;  // two sets of 8 per-die counters, 128 bytes apart
 static_assert(kCounterBytes == 2048, "callers keep workspaces of this size");
@@ -293,7 +293,7 @@ extern "C" hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void*
   p.prof = profile;
 
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  if (hbp::launch_fwd(desc->d_qk, desc->d_v, p, desc->fwd_tile_rows ? desc->fwd_tile_rows : kTileRows, kNumCU, hs, g_events[HBP_FWD][0], g_events[HBP_FWD][1]) != 0) return HBP_ERR_DEVICE;
+  if (hbp::launch_fwd(desc->d_qk, desc->d_v, p, desc->fwd_tile_rows ? desc->fwd_tile_rows : kTileRows, hs, g_events[HBP_FWD][0], g_events[HBP_FWD][1]) != 0) return HBP_ERR_DEVICE;
   return HBP_OK;
 }
 
@@ -392,8 +392,8 @@ hbp_status bwd_impl(const hbp_attn_desc* desc, const void* q, const void* k, con
   const int64_t items_dkdv = (int64_t)n_kv_tiles * p.Hkv * p.n_split, items_dq = (int64_t)n_q_tiles * p.Hq;
   const int grid_dkdv = grid_for(items_dkdv, 1), grid_dq = grid_for(items_dq, 2);
   const int dq_per_cu = desc->d_qk <= 128 ? 2 : 1;
-  if (hbp::direct_items(items_dkdv, kNumCU, p.prof)) p.counter = nullptr;
-  if (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq)) p.counter_dq = nullptr;
+  if (hbp::direct_items(items_dkdv, kNumCU, p.prof != nullptr)) p.counter = nullptr;
+  if (hbp::direct_items(items_dq, (int64_t)kNumCU * dq_per_cu, p.prof_dq != nullptr)) p.counter_dq = nullptr;
   hipEvent_t ev[4] = {g_events[HBP_BWD][0], g_events[HBP_BWD][1], g_events[HBP_BWD_DQ][0], g_events[HBP_BWD_DQ][1]};
   if (hbp::launch_bwd(desc->d_qk, desc->d_v, p, grid_dq, grid_dkdv, static_cast<hipStream_t>(stream), ev) != 0)
     return HBP_ERR_DEVICE;

@@ -1396,56 +1396,6 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
   }
 }
 
-// Eight or four wavefronts a key tile (dK/dV kernel).  Eight pay per step and cost per item, so the line is the mean
-// number of steps an item has: heads of the item x blocks of 64 rows from the tile to its sample's end.  Time of the
-// backward, four / eight, T = 512 to 32768, samples of one size and mixed ones:
-//   d = 128, one head an item    samples of 60: .81 to .97; 250: .90 to .96; 600: .95 to .99; 1000: .98 to 1.01;
-//                                1200: 1.00 to 1.01; 1500: 1.00 to 1.02; 2500: 1.02 to 1.03
-//            two                 60: .92; 150: .98; 290: 1.02; 580: 1.03; 1000: 1.03
-//            three and more      25: 1.01 (four) and 1.11 (eight); 60: 1.00 and 1.10; 250: 1.08; 1000: 1.06
-//   d = 64, one                  25: 1.01; 60: 1.00; 126: .94 to .99; 240: 1.00 to 1.07; 800: 1.03 to 1.08
-// With no more items than compute units the launch is as long as its longest item: eight from 100 tokens a sample on
-// (.995 to 1.39; of 60: .96 to .99).  Where dK/dV and dQ go in one launch there are always eight: see one_launch().
-static bool eight_waves(int d, const BwdParams& p) {
-  const double len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
-  const int heads = p.g / p.n_split;
-  if ((int64_t)p.n_tiles * p.Hkv * p.n_split <= 256) return len >= 100;
-  const double steps = heads * (len / 128 + 1);
-  return d == 64 ? steps >= 2.5 : heads >= 3 || steps >= (heads == 2 ? 6.5 : 10);
-}
-// dK/dV and dQ in one launch (bwd_both_kernel), and with their items interleaved?  `rounds`: dK/dV items to a compute
-// unit; heads: query heads an item loops over; len: tokens a sample.  Time of the backward, two launches / one, T = 512 to
-// 50000; samples of 60, 250, 800, 3000 (log-normal) and one sample of .4 or .5 of the pack among short ones:
-//   one head     interleaved.  To 1 round 1.3 to 1.75; to 3: 1.1 to 1.8.  Dispatched dK/dV first .94 to 1.6.
-//     d = 64     to 5.5: 1.01 to 1.36; 5.9 to 12.9, len >= 900: .97 to 1.06; len <= 320, to 19: 1.01 to 1.08
-//     d = 128    to 6.5: 1.02 to 1.20; 8.5 to 12: .97 (a sample of .5 to .7, len 1400 to 3000) to 1.08
-//                len 150 to 350, to 15: 1.02 to 1.12; 18 to 25: .99 to 1.04; shorter, to 8: 1.02 to 1.18; to 12.7: .95 to 1.01
-//   more heads   dK/dV first.  To 1 round 1.16 to 1.9.  Interleaved, two heads: .84 to 1.5 (as many dQ items as dK/dV, so
-//                every second group of a die, and these go to the same of its shader engines); from four: .90 to 1.1
-//     two        to 4: 1.03 to 1.63; 4.2: .99 to 1.04; len <= 320, to 5: 1.05 to 1.08
-//     to five    to 4: 1.01 to 1.38 (d = 64, 3.1: .99, so to 2.9 there); 4.2 to 5.3: .98 to 1.02; len <= 100, to 12:
-//                1.01 to 1.13
-//     to eight   to 2.7: 1.00 to 1.29; 3.1 to 3.6: .97 to 1.03; len <= 100, to 12: 1.00 to 1.07.  Not measured beyond.
-enum Launches { kTwo, kOne, kOneInterleaved };
-static Launches one_launch(int d, const BwdParams& p) {
-  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || (double)p.n_q_tiles * p.Hq > 64 * 512) return kTwo;  // 49 rounds of dQ measured
-  const int heads = p.g / p.n_split;
-  const double rounds = (double)p.n_tiles * p.Hkv * p.n_split / 256, len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
-  if (heads == 1) {
-    const bool one = d == 64 ? rounds <= (len <= 320 ? 19 : 5.5) : rounds <= (len < 150 ? 8 : len <= 350 ? 15 : 6.5);
-    return !one ? kTwo : p.Hq > 1 ? kOneInterleaved : kOne;
-  }
-  if (heads == 2) return rounds <= 4 || (len <= 320 && rounds <= 5) ? kOne : kTwo;
-  const double most = heads <= 5 ? (d == 64 ? 2.9 : 4) : 2.7;
-  return heads <= 8 && (rounds <= most || (len <= 100 && rounds <= 12)) ? kOne : kTwo;
-}
-// The same at head size 192 (bwd_both4_kernel): two launches / one, T = 512 to 16384, 8, 16 and 128 heads and 12/4:  to 1
-// round 1.2 to 1.7; to 3: 1.04 to 1.77; to 4: 1.02 to 1.2; 4.2 to 5: .99 to 1.13; 6 to 10: .96 to 1.1; more: .95 to 1.0.
-// Items of several heads were not measured.
-static bool one_launch4(const BwdParams& p) {
-  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || (double)p.n_q_tiles * p.Hq > 64 * 512) return false;
-  return p.g == p.n_split && (double)p.n_tiles * p.Hkv * p.n_split / 256 <= 4;
-}
 template <int DQK, int DV>
 constexpr int dkdv8_lds() {
   constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + (DQK > 64 ? 128 * DQK * 2 : 0) + 2 * 3 * 1024;
@@ -1505,16 +1455,8 @@ template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
   constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
   constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
-  bool eight = false, both = false, interleave = false;
-  if constexpr (DQK == DV) {
-    const Launches way = one_launch(DQK, p);
-    eight = grid_dkdv > 0 && (way != kTwo || eight_waves(DQK, p));
-    // a call that asks for records or events of either kernel keeps two launches (and gets the same bits)
-    both = way != kTwo && !p.prof && !p.prof_dq && !ev[0] && !ev[2];
-    interleave = way == kOneInterleaved;
-  } else {
-    both = one_launch4(p) && !p.prof && !p.prof_dq && !ev[0] && !ev[2];
-  }
+  const BwdItems items{PackShape{DQK, p.T, p.n_samples, p.Hq, p.Hkv}, p.n_tiles, p.n_q_tiles, p.n_split};
+  const BwdLaunch how = bwd_launch(items, p.prof || p.prof_dq || ev[0] || ev[2]);
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)bwd_dq_kernel<DQK, DV>,
@@ -1535,24 +1477,24 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
   if constexpr (DQK == DV) {
-    if (both) {
-      const int err = p.g % 2 == 0 ? launch_both<DQK, DV, true>(p, grid_dkdv, interleave, s)
-                                   : launch_both<DQK, DV, false>(p, grid_dkdv, interleave, s);
+    if (how.one) {
+      const int err = p.g % 2 == 0 ? launch_both<DQK, DV, true>(p, grid_dkdv, how.interleaved, s)
+                                   : launch_both<DQK, DV, false>(p, grid_dkdv, how.interleaved, s);
       if (err) return err;
     }
-  } else if (both) {
+  } else if (how.one) {
     const int err = launch_both4<DQK, DV>(p, grid_dkdv, s);
     if (err) return err;
   }
   if (grid_dkdv > 0) {
     if (ev[0] && hipEventRecord(ev[0], s) != hipSuccess) return (int)hipErrorInvalidValue;
     if constexpr (DQK == DV) {
-      if (eight && !both) {
+      if (how.eight && !how.one) {
         const int err = launch_dkdv8<DQK, DV>(p, grid_dkdv, s);
         if (err) return err;
       }
     }
-    if (!eight && !both)
+    if (!how.eight && !how.one)
       hipLaunchKernelGGL((bwd_dkdv_kernel<DQK, DV>), dim3(grid_dkdv), dim3(kThreads), lds_dkdv, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
@@ -1565,7 +1507,7 @@ static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStrea
     }
     if (ev[1] && hipEventRecord(ev[1], s) != hipSuccess) return (int)hipErrorInvalidValue;
   }
-  if (grid_dq > 0 && !both) {
+  if (grid_dq > 0 && !how.one) {
     if (ev[2] && hipEventRecord(ev[2], s) != hipSuccess) return (int)hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_dq_kernel<DQK, DV>), dim3(grid_dq), dim3(kThreads), lds_dq, s, p);
     e = hipGetLastError();

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_rules.hpp"
 #include "hbp.h"
 
 namespace hbp {
@@ -385,7 +386,6 @@ __device__ __forceinline__ uint32_t xcc_id_reg() {
 // 16 of them for 128 kv heads, only two workgroups would).  A workgroup serves its own die's queue
 // first and then steals from the others, so every item is done whatever the head count and the tail
 // stays balanced.  Counters are 128 bytes apart.
-constexpr int kNumXcd = 8;
 constexpr int kCounterStride = 32;  // in int32
 constexpr int kHeadGroup = 2;  // measured on 128 kv heads: 1 and 2 alike, 4 is 2 % slower, all 16 at once 12 %
 
@@ -559,21 +559,6 @@ struct BwdParams {
   float *dk_part, *dv_part;
 };
 
-// A kernel whose items all fit on the chip at once gets one workgroup an item and no queue: every item starts
-// at once whatever its order, and the launch that resets the counters (5 us of the stream's time) and the
-// atomic in front of an item fall away.  Training step of a 1024-token pack with 4 heads of 64: 46.0 -> 36.6 us;
-// of 5497 tokens with 8 heads: 119 -> 110.  The forward goes further (fwd_way).  Profile records are one per resident
-// workgroup, so a call that asks for them keeps the queues.
-inline bool direct_items(int64_t n_items, int64_t resident, const void* prof) { return !prof && n_items <= resident; }
-
-// In how many parts the `units` schedulable units of a kv head (query heads, or pairs of them) are
-// dealt out: the smallest divisor of units that gives every die a queue, else units itself.
-inline int heads_split(int n_kv_heads, int units) {
-  for (int s = 1; s <= units; ++s)
-    if (units % s == 0 && n_kv_heads * s >= 8) return s;
-  return units;
-}
-
 struct CeParams {  // packed cross-entropy
   const uint16_t* logits;
   int64_t stride_t;  // elements
@@ -593,12 +578,11 @@ constexpr int kCeMaxWorkgroups = 2048;
 
 // launchers implemented in the .hip files; return hipError_t as int
 // ev0/ev1: optional events recorded around the persistent main kernel
-// n_cu: compute units to fill (the kernel picks its own workgroup shape and grid)
-int launch_fwd(int d_qk, int d_v, const FwdParams& p, int tile_rows, int n_cu, hipStream_t s, hipEvent_t ev0,
-               hipEvent_t ev1);
+int launch_fwd(int d_qk, int d_v, const FwdParams& p, int tile_rows, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // ev: {dkdv start, dkdv stop, dq start, dq stop}, entries may be null
 int launch_bwd(int d_qk, int d_v, const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev);
 size_t bwd_partial_floats(int T, int Hkv, int g, int dim);  // per tensor; 0 when the dK/dV kernel needs no partial sums
+// n_cu: compute units to fill (the kernel picks its own workgroup shape and grid)
 int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 
 }  // namespace hbp

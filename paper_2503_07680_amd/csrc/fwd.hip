@@ -551,7 +551,7 @@ __global__ void zero_counters_kernel(int32_t* c) {
 }
 
 template <int DQK, int DV, int HP, int TP>
-static int launch_fwd_hp(FwdParams p, bool direct, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+static int launch_fwd_hp(FwdParams p, bool direct, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2);
   static bool attr_set = false;
   if (!attr_set) {
@@ -560,9 +560,9 @@ static int launch_fwd_hp(FwdParams p, bool direct, int n_cu, hipStream_t s, hipE
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = (int64_t)n_cu * (2 / (HP * TP));
+  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = kNumCU * (2 / (HP * TP));
   const int grid = (int)(direct || n_items < cap ? n_items : cap);
-  if (direct || direct_items(n_items, cap, p.prof)) p.counter = nullptr;
+  if (direct) p.counter = nullptr;
   p.n_split = heads_split(p.Hkv, p.g / HP);  // HP = 2: items are pairs of heads
   if (p.counter) {
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, p.counter);
@@ -576,75 +576,25 @@ static int launch_fwd_hp(FwdParams p, bool direct, int n_cu, hipStream_t s, hipE
   return (int)e;
 }
 
-// Launches of few rounds: one workgroup an item, dispatched by the hardware in the worklist's order (kDirect), without the
-// launch that resets the queues' counters (5 us) and without the hand-over between items; and for even groups of heads
-// also one head a workgroup of four wavefronts, two workgroups a compute unit, instead of a pair of heads on one K/V
-// stream (kSingles): a workgroup's prologue and end are then covered by the other one, and the last round is finer.  With
-// more rounds the queues balance better, and long samples need the shared stream.  `rounds`: items (pairs of heads, or
-// 256-row tiles) to a compute unit; `len`: tokens a sample.  Forward, time with queues and pairs / this way, T = 2048 to
-// 32768, 3 to 64 heads:
-//   even, d = 64     singles, to 7: 1.03 to 1.37; to 10, samples of 100 to 250: 1.10 to 1.14
-//   even, d >= 128   singles, to 2: 1.03 to 1.34; samples to 100, to 8: 1.04 to 1.23
-//     kv heads dealt evenly to the dies: pairs, 2 to 4.8: 1.00 to 1.12 (samples of 1600: .98), 5.3: .99; singles there
-//                    gain up to .03 more, but .96 to .99 with a sample of half the pack
-//     else           pairs, 2 to 2.7: 1.00 to 1.10; 3.1: .98; singles, 2.5: .98 to 1.03
-//   odd              256-row tiles, to 3.5: 1.00 to 1.52; 3.6: .99; 4.2 to 4.7: .97 to 1.03; samples to 128, 4.0 to 5.5:
-//                    1.04 to 1.14
-//   odd, kHalves     a workgroup of four wavefronts takes half of a 256-row tile: the longest item's chain of key tiles runs
-//                    without a second wavefront on its SIMD.  Against 256-row tiles, mixed samples and one of .4 or .5:
-//     d = 64         to 4.2: 1.00 to 1.31; 4.5: .97 to 1.09; len to 320, to 7.5: 1.01 to 1.24
-//     d = 128        to .75: 1.02 to 1.23; .8 to 2: .93 to 1.17; len to 350, to 9: 1.02 to 1.42; 11 to 22: .95 to 1.10
-//     d = 192        to 2.3: 1.01 to 1.21; 3 to 4.5: .97 to 1.13; len to 350, to 6: 1.01 to 1.20; 7.4: .99
-//     len to 100     from 1.05 on: 1.10 to 1.45, and packs of that mean with a long sample .97 to 1.02 to T = 16384; with a
-//                    round or less: .97 to 1.03
-// Beyond two rounds only for packs that cannot hold a very long sample beside the short ones (the host knows their mean
-// alone): 9500 tokens with a sample of 7125, 16/8 heads of 128: .96; 20000 with one of 15000, 8 heads of 64: .98.
-enum FwdWay { kQueues, kDirect, kSingles, kHalves };
-static FwdWay fwd_way(const FwdParams& p, int d_qk, int64_t n_items, int n_cu) {
-  if (p.prof) return kQueues;  // records are one per resident workgroup
-  const double rounds = (double)n_items / n_cu, len = (double)p.T / (p.n_samples > 0 ? p.n_samples : 1);
-  if (p.g % 2 && rounds <= 300) {
-    if (len <= 100) {
-      if (rounds > 1.05 && p.T <= 16384) return kHalves;
-    } else if (d_qk == 64 ? rounds <= 4.2 || (len <= 320 && rounds <= 7.5)
-                          : d_qk == 128 ? rounds <= 0.75 || (len <= 350 && rounds <= 9)
-                                        : rounds <= 2.3 || (len <= 350 && rounds <= 6)) {
-      return kHalves;
-    }
-  }
-  if (rounds <= 2) return kSingles;
-  if (p.T > (p.g % 2 || d_qk == 64 ? 16384 : 8192)) return kQueues;
-  if (p.g % 2) return rounds <= 3.5 || (len <= 128 && rounds <= 5.5) ? kDirect : kQueues;
-  if (d_qk == 64) return rounds <= 7 || (len <= 300 && rounds <= 10) ? kSingles : kQueues;
-  if (len <= 100 && rounds <= 8) return kSingles;
-  if (p.Hkv % kNumXcd) return rounds <= 2.7 ? kDirect : kQueues;
-  return rounds <= 4.8 ? kDirect : kQueues;
-}
 // tile_rows: rows per query tile of the worklist, 128 or (odd group sizes only) 256
 template <int DQK, int DV>
-static int launch_fwd_t(const FwdParams& p, int tile_rows, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (p.g % 2 == 0) {
-    if (tile_rows != 128) return (int)hipErrorInvalidValue;
-    const FwdWay way = fwd_way(p, DQK, (int64_t)p.n_tiles * (p.Hq / 2), n_cu);
-    return way == kSingles ? launch_fwd_hp<DQK, DV, 1, 1>(p, true, n_cu, s, ev0, ev1)
-                           : launch_fwd_hp<DQK, DV, 2, 1>(p, way == kDirect, n_cu, s, ev0, ev1);
+static int launch_fwd_t(FwdParams p, int tile_rows, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (tile_rows != 128 && (tile_rows != 256 || p.g % 2 == 0)) return (int)hipErrorInvalidValue;
+  const FwdLaunch how = fwd_launch(PackShape{DQK, p.T, p.n_samples, p.Hq, p.Hkv}, p.n_tiles, tile_rows, p.prof != nullptr);
+  if (how.halves) {
+    p.n_tiles *= 2;
+    p.halves = 1;
   }
-  if (tile_rows == 256) {
-    const FwdWay way = fwd_way(p, DQK, (int64_t)p.n_tiles * p.Hq, n_cu);
-    if (way != kHalves) return launch_fwd_hp<DQK, DV, 1, 2>(p, way != kQueues, n_cu, s, ev0, ev1);
-    FwdParams halved = p;
-    halved.n_tiles *= 2;
-    halved.halves = 1;
-    return launch_fwd_hp<DQK, DV, 1, 1>(halved, true, n_cu, s, ev0, ev1);
-  }
-  return launch_fwd_hp<DQK, DV, 1, 1>(p, false, n_cu, s, ev0, ev1);
+  if (how.hp == 1 && how.tp == 1) return launch_fwd_hp<DQK, DV, 1, 1>(p, how.direct, s, ev0, ev1);
+  return how.hp == 2 ? launch_fwd_hp<DQK, DV, 2, 1>(p, how.direct, s, ev0, ev1)
+                     : launch_fwd_hp<DQK, DV, 1, 2>(p, how.direct, s, ev0, ev1);
 }
 
-int launch_fwd(int d_qk, int d_v, const FwdParams& p, int tile_rows, int n_cu, hipStream_t s,
-               hipEvent_t ev0, hipEvent_t ev1) {
-  if (d_qk == 64 && d_v == 64) return launch_fwd_t<64, 64>(p, tile_rows, n_cu, s, ev0, ev1);
-  if (d_qk == 128 && d_v == 128) return launch_fwd_t<128, 128>(p, tile_rows, n_cu, s, ev0, ev1);
-  if (d_qk == 192 && d_v == 128) return launch_fwd_t<192, 128>(p, tile_rows, n_cu, s, ev0, ev1);
+int launch_fwd(int d_qk, int d_v, const FwdParams& p, int tile_rows, hipStream_t s, hipEvent_t ev0,
+               hipEvent_t ev1) {
+  if (d_qk == 64 && d_v == 64) return launch_fwd_t<64, 64>(p, tile_rows, s, ev0, ev1);
+  if (d_qk == 128 && d_v == 128) return launch_fwd_t<128, 128>(p, tile_rows, s, ev0, ev1);
+  if (d_qk == 192 && d_v == 128) return launch_fwd_t<192, 128>(p, tile_rows, s, ev0, ev1);
   return (int)hipErrorInvalidValue;
 }
 

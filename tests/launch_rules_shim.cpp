@@ -1,0 +1,14 @@
+// The rules that choose an attention call's kernels, for tests without a GPU.
+#include "attn_rules.hpp"
+
+// out: heads or pairs a workgroup (1, 2), 128-row halves a tile (1, 2), without queues?, halves of 256-row tiles?
+extern "C" void fwd_route(int d_qk, int T, int n_samples, int Hq, int Hkv, int n_tiles, int tile_rows, int records, int* out) {
+  const hbp::FwdLaunch l = hbp::fwd_launch(hbp::PackShape{d_qk, T, n_samples, Hq, Hkv}, n_tiles, tile_rows, records != 0);
+  out[0] = l.hp; out[1] = l.tp; out[2] = l.direct; out[3] = l.halves;
+}
+// out: one launch?, interleaved?, eight wavefronts a key tile?, query heads a dK/dV item loops over, dK/dV and dQ items
+extern "C" void bwd_route(int d_qk, int T, int n_samples, int Hq, int Hkv, int n_tiles, int n_q_tiles, int separate, int* out) {
+  const hbp::BwdItems i{hbp::PackShape{d_qk, T, n_samples, Hq, Hkv}, n_tiles, n_q_tiles, hbp::heads_split(Hkv, Hq / Hkv)};
+  const hbp::BwdLaunch l = hbp::bwd_launch(i, separate != 0);
+  out[0] = l.one; out[1] = l.interleaved; out[2] = l.eight; out[3] = i.heads(); out[4] = (int)i.dkdv(); out[5] = (int)i.dq();
+}

@@ -11,13 +11,18 @@ pytestmark = pytest.mark.gpu
 SHORT = [100, 128, 129, 60, 31, 33, 257, 90]
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,e,times", [
-    (32, 8, 64, 64, 1), (32, 8, 64, 64, 5), (32, 8, 64, 64, 12),        # even, head size 64: singles, then queues
-    (32, 8, 128, 128, 2), (32, 8, 128, 128, 4), (32, 8, 128, 128, 9),  # dealt evenly to the dies: singles, pairs, queues
-    (24, 6, 128, 128, 4), (24, 6, 128, 128, 8),                         # not so dealt
-    (16, 8, 192, 128, 3), (16, 8, 192, 128, 12),
-    (24, 8, 128, 128, 5), (24, 24, 64, 64, 9), (24, 24, 192, 128, 9),  # odd groups
-])
+LINES = [  # Hq, Hkv, d_qk, d_v, copies of SHORT, what the forward launches (checked without a GPU: test_launch_rules_host.py)
+    (32, 8, 64, 64, 1, "singles"), (32, 8, 64, 64, 14, "singles"), (32, 8, 64, 64, 15, "pairs queued"),
+    # kv heads dealt evenly to the dies, and not
+    (32, 8, 128, 128, 2, "singles"), (32, 8, 128, 128, 4, "pairs"), (32, 8, 128, 128, 9, "pairs queued"),
+    (24, 6, 128, 128, 4, "pairs"), (24, 6, 128, 128, 8, "pairs queued"),
+    (16, 8, 192, 128, 3, "singles"), (16, 8, 192, 128, 12, "pairs queued"),
+    # odd groups
+    (24, 8, 128, 128, 5, "halves"), (24, 24, 64, 64, 9, "256-row tiles queued"), (24, 24, 192, 128, 9, "256-row tiles queued"),
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,e,times", [x[:5] for x in LINES])
 def test_either_side_of_the_lines(Hq, Hkv, d, e, times):
     lengths = SHORT * times
     case = Case(lengths, sum(lengths), Hq, Hkv, d, e, seed=311, name="rounds-%d-%d-%d-%d" % (Hq, Hkv, d, times))

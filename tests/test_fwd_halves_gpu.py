@@ -39,12 +39,17 @@ def test_edges_of_halves(d, e, Hq, Hkv):
     check_same(case)
 
 
-@pytest.mark.parametrize("lengths,Hq,Hkv,d,e", [
-    ([300] * 66, 16, 16, 64, 64), ([300] * 62, 16, 16, 64, 64),      # short samples, head size 64: to 7.5 rounds
-    ([700] * 24, 16, 16, 64, 64), ([700] * 22, 16, 16, 64, 64),      # others: to 4.2
-    ([60] * 100, 24, 24, 128, 128), ([60] * 280, 24, 24, 128, 128),  # very short ones: by the pack's size
-    ([200] * 90, 24, 8, 128, 128), ([200] * 100, 24, 8, 128, 128),   # head size 128: to 9
-    ([300, 200] * 20, 24, 24, 192, 128), ([300, 200] * 24, 24, 24, 192, 128),  # head size 192: to 6
-])
+LINES = [  # lengths, Hq, Hkv, d_qk, d_v, what the forward launches (checked without a GPU: test_launch_rules_host.py)
+    ([300] * 60, 16, 16, 64, 64, "halves"), ([300] * 62, 16, 16, 64, 64, "256-row tiles queued"),  # short samples: to 7.5 rounds
+    ([700] * 22, 16, 16, 64, 64, "halves"), ([700] * 24, 16, 16, 64, 64, "256-row tiles queued"),  # others: to 4.2
+    # very short ones: by the pack's size
+    ([60] * 100, 24, 24, 128, 128, "halves"), ([60] * 280, 24, 24, 128, 128, "256-row tiles queued"),
+    ([200] * 90, 24, 8, 128, 128, "halves"), ([200] * 100, 24, 8, 128, 128, "256-row tiles queued"),  # head size 128: to 9
+    # head size 192: to 6
+    ([300, 200] * 20, 24, 24, 192, 128, "halves"), ([300, 200] * 24, 24, 24, 192, 128, "256-row tiles queued"),
+]
+
+
+@pytest.mark.parametrize("lengths,Hq,Hkv,d,e", [x[:5] for x in LINES])
 def test_either_side_of_the_lines(lengths, Hq, Hkv, d, e):
     check_same(Case(lengths, sum(lengths), Hq, Hkv, d, e, seed=502, name="halves-line"))

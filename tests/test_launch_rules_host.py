@@ -1,0 +1,37 @@
+"""The GPU tests that stand on either side of a line between two ways to launch say which way each of their packs takes;
+here the library's rules are asked, without a GPU, so that a line that moves shows in the tests that it empties."""
+import launch_rules as rules
+import test_fwd_few_rounds_gpu as few_rounds
+import test_fwd_halves_gpu as halves
+import test_one_backward_launch_gpu as one_launch
+
+
+def check(got, want, packs):
+    assert got == want, [(p, g, w) for p, g, w in zip(packs, got, want) if g != w]
+
+
+def test_the_forwards_lines():
+    packs = [(few_rounds.SHORT * times, Hq, Hkv, d) for Hq, Hkv, d, _, times, _ in few_rounds.LINES]
+    packs += [x[:4] for x in halves.LINES]
+    check([rules.forward(*p) for p in packs], [x[-1] for x in few_rounds.LINES + halves.LINES], packs)
+    # every way of either kind of group is there, and records keep the queues
+    assert {x[-1] for x in few_rounds.LINES} >= {"singles", "pairs", "pairs queued"}
+    assert all(rules.forward(*p, records=True).endswith(" queued") for p in packs)
+
+
+def test_the_edges_of_halves_are_halves():
+    for d, Hq, Hkv in [(d, *h) for d in (64, 128, 192) for h in ((1, 1), (3, 1), (5, 5), (8, 8), (16, 16), (24, 8))]:
+        assert rules.forward(halves.EDGES, Hq, Hkv, d) == "halves"
+
+
+def test_the_backwards_lines():
+    packs = [([n] * times, Hq, Hkv, d) for Hq, Hkv, d, n, times, _ in one_launch.LINES]
+    packs += [([60] * times, 16, 16, 192) for times, _ in one_launch.LINES_192]
+    check([rules.backward(*p)[0] for p in packs], [x[-1] for x in one_launch.LINES + one_launch.LINES_192], packs)
+    assert all("one launch" not in rules.backward(*p, records=True)[0] for p in packs)
+
+
+def test_heads_split():
+    # query heads that an item of the key-tile kernel loops over: every die gets a queue
+    want = {(32, 8): 4, (8, 1): 1, (16, 4): 2, (64, 8): 8, (6, 2): 1, (12, 3): 1, (128, 128): 1, (40, 4): 5}
+    assert {k: rules.backward([500], *k, 128)[1] for k in want} == want

@@ -53,14 +53,17 @@ def test_few_items(d, lengths):
     compare(case, pa, out)
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,n,times", [
-    (24, 24, 64, 300, 27), (24, 24, 64, 300, 68),     # one head, short samples: interleaved to 19 rounds, then two
-    (24, 24, 128, 60, 82), (24, 24, 128, 60, 90),     # one head, very short samples: to 8
-    (16, 8, 128, 60, 155), (16, 8, 128, 60, 165),     # two heads: to 5
-    (32, 8, 128, 100, 370), (32, 8, 128, 101, 130),   # four heads: short samples to 12, others to 4
-    (48, 8, 128, 130, 40), (48, 8, 128, 130, 45),     # six heads: to 2.7
-    (72, 8, 64, 64, 8),                                # nine: two launches
-])
+LINES = [  # Hq, Hkv, d, tokens a sample, samples, what the backward launches (checked without a GPU: test_launch_rules_host.py)
+    (24, 24, 64, 300, 67, "one launch interleaved"), (24, 24, 64, 300, 68, "eight waves"),  # one head, short samples: to 19 rounds
+    (24, 24, 128, 60, 85, "one launch interleaved"), (24, 24, 128, 60, 90, "four waves"),   # one head, very short ones: to 8
+    (16, 8, 128, 60, 155, "one launch"), (16, 8, 128, 60, 165, "four waves"),                # two heads: to 5
+    (32, 8, 128, 100, 370, "one launch"), (32, 8, 128, 101, 130, "eight waves"),             # four heads: to 12, others to 4
+    (48, 8, 128, 130, 40, "one launch"), (48, 8, 128, 130, 45, "eight waves"),               # six heads: to 2.7
+    (72, 8, 64, 64, 8, "four waves"),                                                        # nine: two launches
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,n,times", [x[:5] for x in LINES])
 def test_either_side_of_the_lines(Hq, Hkv, d, n, times):
     lengths = [n] * times
     case = Case(lengths, sum(lengths), Hq, Hkv, d, d, seed=403, name="one-launch-line-%d-%d-%d" % (Hq, n, times))
@@ -86,7 +89,10 @@ def test_head_size_192(Hq, Hkv, times):  # the last: two heads an item, two laun
     check_dv_identity(case, pa, dev, out)
 
 
-@pytest.mark.parametrize("times", [64, 66])  # four rounds, and more
+LINES_192 = [(64, "one launch"), (66, "four waves")]  # four rounds, and more
+
+
+@pytest.mark.parametrize("times", [x[0] for x in LINES_192])
 def test_head_size_192_on_either_side_of_the_line(times):
     case = Case([60] * times, 60 * times, 16, 16, 192, 128, seed=406, name="one-launch-192-line-%d" % times)
     pa, dev, out = run(case)
