@@ -16,6 +16,7 @@
 // The weighted token losses go to a workspace array and are summed by one workgroup in a fixed order,
 // so the loss is bit-stable from run to run.
 #include "common.hpp"
+#include "loss_rules.hpp"
 
 namespace hbp {
 
@@ -562,22 +563,6 @@ __global__ __launch_bounds__(kCeThreads) void ce_reduce_kernel(const CeParams p)
   if (tid == 0) *p.loss_out = acc;
 }
 
-// The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
-// the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
-// many and with one more.  With the gradient: V = 32000: 30.5 / 65.5 / 190 and 34.1 / 65.8 / 193; 45056: 41.1 / 86.8 /
-// 267 and 44.3 / 87.1 / 270; 28672: 30.4 / 57.2 / 174 and 28.0 / 60.0 / 174; 16384: 19.2 / 35.7 / 103 and 19.3 / 38.5 /
-// 104.
-// Without it a workgroup has a row under way whatever its work is, so fewer are enough.  With 1 / 2 / 4 of 256 threads,
-// V = 4096: 9.9 / 9.7 / 8.9, 16.0 / 13.4 / 11.8 and 37 / 28 / 23; 8000: 10.6 / 10.5 / 9.8, 17 / 15 / 14, 41 / 32 / 29 (8:
-// 13.3 and 14.7 at T = 2500); with 1 / 2 of 512, V = 32000: 16.0 / 18.1, 26.6 / 29.3, 68 / 70; 65536: 24.6 / 29.7, 43.5 /
-// 49.0, 130 / 129.
-constexpr int ce_most_per_cu(int nt, int nch, bool with_grad) {
-  if (!with_grad) return nt == 256 ? 4 : 1;
-  if (nt == 256) return nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
-  if (nt == 512) return nch <= 5 ? 4 : nch <= 7 ? 3 : 2;
-  return 2;
-}
-
 // Workgroups resident at once per compute unit.  The main kernel's grid is that times the compute
 // units: a persistent loop over rows; a second batch of workgroups would start with an empty pipeline.
 template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
@@ -586,7 +571,7 @@ static int main_per_cu(int lds) {
   if (per_cu == 0) {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ce_main_kernel<NT, NCH, HOLD, WITH_GRAD>, NT, 0) != hipSuccess || n < 1) n = 1;
-    constexpr int kMost = ce_most_per_cu(NT, NCH, WITH_GRAD);
+    constexpr int kMost = ce_most_per_cu(NT, NCH, HOLD, WITH_GRAD);
     per_cu = n < kMost ? n : kMost;
   }
   constexpr int kLds = 160 * 1024, kStatic = 4 * 1024;  // LDS of a compute unit; the kernel's own arrays

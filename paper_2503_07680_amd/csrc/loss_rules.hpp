@@ -1,0 +1,29 @@
+// Launch shape of the packed cross-entropy: a plain host function, without HIP, so that a test without a GPU can ask it.
+#pragma once
+
+namespace hbp {
+
+// The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
+// the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
+// many and with one more.  With the gradient: V = 32000: 30.5 / 65.5 / 190 and 34.1 / 65.8 / 193; 45056: 41.1 / 86.8 /
+// 267 and 44.3 / 87.1 / 270; 28672: 30.4 / 57.2 / 174 and 28.0 / 60.0 / 174; 16384: 19.2 / 35.7 / 103 and 19.3 / 38.5 /
+// 104.
+// Without it a workgroup has a row under way whatever its work is, so fewer are enough.  With 1 / 2 / 4 of 256 threads,
+// V = 4096: 9.9 / 9.7 / 8.9, 16.0 / 13.4 / 11.8 and 37 / 28 / 23; 8000: 10.6 / 10.5 / 9.8, 17 / 15 / 14, 41 / 32 / 29 (8:
+// 13.3 and 14.7 at T = 2500); with 1 / 2 of 512, V = 32000: 16.0 / 18.1, 26.6 / 29.3, 68 / 70; 65536: 24.6 / 29.7, 43.5 /
+// 49.0, 130 / 129.
+// A row that is streamed (hold false) has nothing under way over its reduction: two workgroups a unit, with the gradient
+// and without.  Without it, one / two of 1024 threads, 30 % of the rows without a loss: V = 163848: T = 600: 30 / 28, 2500:
+// 141 / 115, 8192: 403 / 333; 262144: T = 600: 49 / 42, 4096: 324 / 268; 400000: T = 2500: 313 / 258.  One is faster where
+// the rows with a loss then go one to a unit (257 to 360 rows: T = 300: 19 / 26, 25 / 36, 33 / 50) or evenly two (T = 600,
+// all with a loss, V = 202048: 48 / 54); the host does not know how many have one, and with one in every row T = 300 takes
+// 30 / 26, 42 / 35, 58 / 48.
+constexpr int ce_most_per_cu(int nt, int nch, bool hold, bool with_grad) {
+  if (!hold) return 2;
+  if (!with_grad) return nt == 256 ? 4 : 1;
+  if (nt == 256) return nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
+  if (nt == 512) return nch <= 5 ? 4 : nch <= 7 ? 3 : 2;
+  return 2;
+}
+
+}  // namespace hbp

@@ -1,4 +1,4 @@
-"""Which kernels an attention call on a pack launches, from the library's own rules (`attn_rules.hpp`, compiled here with
+"""Which kernels a call launches, from the library's own rules (`attn_rules.hpp`, `loss_rules.hpp`, compiled here with
 g++): the tests that claim to reach a kernel say which, and a test without a GPU checks that they still do."""
 import ctypes
 import os
@@ -45,3 +45,8 @@ def backward(lengths, Hq, Hkv, d, records=False):
     one, interleaved, eight, heads, items, _ = out
     return ("one launch interleaved" if one and interleaved else "one launch" if one else "eight waves" if eight else "four waves",
             heads, items)
+
+
+def cross_entropy_per_cu(threads, chunks, hold, with_grad):
+    """The most workgroups a compute unit gets."""
+    return _load().ce_per_cu(threads, chunks, int(hold), int(with_grad))

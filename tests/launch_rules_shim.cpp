@@ -1,5 +1,6 @@
-// The rules that choose an attention call's kernels, for tests without a GPU.
+// The rules that choose a call's kernels and launches, for tests without a GPU.
 #include "attn_rules.hpp"
+#include "loss_rules.hpp"
 
 // out: heads or pairs a workgroup (1, 2), 128-row halves a tile (1, 2), without queues?, halves of 256-row tiles?
 extern "C" void fwd_route(int d_qk, int T, int n_samples, int Hq, int Hkv, int n_tiles, int tile_rows, int records, int* out) {
@@ -11,4 +12,7 @@ extern "C" void bwd_route(int d_qk, int T, int n_samples, int Hq, int Hkv, int n
   const hbp::BwdItems i{hbp::PackShape{d_qk, T, n_samples, Hq, Hkv}, n_tiles, n_q_tiles, hbp::heads_split(Hkv, Hq / Hkv)};
   const hbp::BwdLaunch l = hbp::bwd_launch(i, separate != 0);
   out[0] = l.one; out[1] = l.interleaved; out[2] = l.eight; out[3] = i.heads(); out[4] = (int)i.dkdv(); out[5] = (int)i.dq();
+}
+extern "C" int ce_per_cu(int threads, int chunks, int hold, int with_grad) {
+  return hbp::ce_most_per_cu(threads, chunks, hold != 0, with_grad != 0);
 }
