@@ -107,14 +107,17 @@ struct BwdItems {
 //            two                 60: .92; 150: .98; 290: 1.02; 580: 1.03; 1000: 1.03
 //            three and more      25: 1.01 (four) and 1.11 (eight); 60: 1.00 and 1.10; 250: 1.08; 1000: 1.06
 //   d = 64, one                  25: 1.01; 60: 1.00; 126: .94 to .99; 240: 1.00 to 1.07; 800: 1.03 to 1.08
-// With no more items than compute units the launch is as long as its longest item: eight from 100 tokens a sample on
-// (.995 to 1.39; of 60: .96 to .99).  Where dK/dV and dQ go in one launch there are always eight: see one_launch().
+//            nine and more, no more items than compute units, d = 64 and 128: samples of 30 to 90: 1.12 to 1.25
+// One or two heads with no more items than compute units: the launch is as long as its longest item, so eight from 100
+// tokens a sample on (.995 to 1.39; of 60: .96 to .99).  Only a call without query tiles comes there: with them such a pack
+// has one launch for dK/dV and dQ, always of eight (see one_launch).
 inline bool eight_waves(const BwdItems& p) {
   const double len = p.pack.mean_len();
   const int heads = p.heads(), d = p.pack.d_qk;
+  if (heads >= 3) return true;
   if (p.dkdv() <= kNumCU) return len >= 100;
   const double steps = heads * (len / 128 + 1);
-  return d == 64 ? steps >= 2.5 : heads >= 3 || steps >= (heads == 2 ? 6.5 : 10);
+  return steps >= (d == 64 ? 2.5 : heads == 2 ? 6.5 : 10);
 }
 // dK/dV and dQ in one launch (bwd_both_kernel), and with their items interleaved?  `rounds`: dK/dV items to a compute
 // unit; heads: query heads an item loops over; len: tokens a sample.  Time of the backward, two launches / one, T = 512 to

@@ -59,7 +59,7 @@ LINES = [  # Hq, Hkv, d, tokens a sample, samples, what the backward launches (c
     (16, 8, 128, 60, 155, "one launch"), (16, 8, 128, 60, 165, "four waves"),                # two heads: to 5
     (32, 8, 128, 100, 370, "one launch"), (32, 8, 128, 101, 130, "eight waves"),             # four heads: to 12, others to 4
     (48, 8, 128, 130, 40, "one launch"), (48, 8, 128, 130, 45, "eight waves"),               # six heads: to 2.7
-    (72, 8, 64, 64, 8, "four waves"),                                                        # nine: two launches
+    (72, 8, 64, 64, 8, "eight waves"), (72, 8, 128, 64, 40, "eight waves"),                  # nine: two launches
 ]
 
 
