@@ -50,8 +50,17 @@ struct PackShape {
 //     d = 192        to 2.3: 1.01 to 1.21; 3 to 4.5: .97 to 1.13; len to 350, to 6: 1.01 to 1.20; 7.4: .99
 //     len to 100     from 1.05 on: 1.10 to 1.45, and packs of that mean with a long sample .97 to 1.02 to T = 16384; with a
 //                    round or less: .97 to 1.03
-// Beyond two rounds only for packs that cannot hold a very long sample beside the short ones (the host knows their mean
-// alone): 9500 tokens with a sample of 7125, 16/8 heads of 128: .96; 20000 with one of 15000, 8 heads of 64: .98.
+// The host knows the samples' mean length alone, and beyond two rounds a very long sample beside short ones loses by every
+// way but the queues: 9500 tokens with a sample of 7125, 16/8 heads of 128: .96.  kDirect and kSingles therefore end at
+// T = 8192 or 16384.  kHalves does not: beyond 2.5 rounds, T = 18000 to 48000, against 256-row tiles with queues, without a
+// long sample / with one of .3 / of .4 or .5 / of .65 or .7 of the pack
+//   d = 64, 8 heads          1.05 to 1.31 / 1.04 to 1.28 / .96 to 1.23 / .95 to 1.06
+//           4                1.14 to 1.33 / 1.17 to 1.28 / 1.03 to 1.26 / .95 to 1.19
+//           6/2              1.06 to 1.37 / 1.02 to 1.28 / .92 to 1.23 / .93 to 1.20
+//   d = 128, 8, 12, 16 heads 1.03 to 1.23 / .95 to 1.13 / .95 to 1.06 / .96 to .98 (the losses from 4.5 rounds on)
+//            9/3             1.13 to 1.23 / 1.09 to 1.15 / 1.08 to 1.21 / not measured
+//   d = 192, 12/4            1.11 and 1.12 / 1.05 / 1.03 / not measured
+// A bound on T there would lose the first two columns for what the last two lose.
 enum FwdWay { kQueues, kDirect, kSingles, kHalves };
 inline FwdWay fwd_way(const PackShape& p, int64_t n_items, bool records) {
   if (records) return kQueues;  // records are one per resident workgroup
@@ -134,7 +143,7 @@ inline bool eight_waves(const BwdItems& p) {
 //     to eight   to 2.7: 1.00 to 1.29; 3.1 to 3.6: .97 to 1.03; len <= 100, to 12: 1.00 to 1.07.  Not measured beyond.
 enum Launches { kTwo, kOne, kOneInterleaved };
 inline Launches one_launch(const BwdItems& p) {
-  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 64 * 512) return kTwo;  // 49 rounds of dQ measured
+  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 49 * 512) return kTwo;  // measured to 49 rounds of dQ
   const int heads = p.heads(), d = p.pack.d_qk;
   const double rounds = (double)p.dkdv() / kNumCU, len = p.pack.mean_len();
   if (heads == 1) {
@@ -149,7 +158,7 @@ inline Launches one_launch(const BwdItems& p) {
 // round 1.2 to 1.7; to 3: 1.04 to 1.77; to 4: 1.02 to 1.2; 4.2 to 5: .99 to 1.13; 6 to 10: .96 to 1.1; more: .95 to 1.0.
 // Items of several heads were not measured.
 inline bool one_launch4(const BwdItems& p) {
-  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 64 * 512) return false;
+  if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 49 * 512) return false;
   return p.heads() == 1 && (double)p.dkdv() / kNumCU <= 4;
 }
 // The launches: one for dK/dV and dQ or two; eight: the dK/dV kernel of eight wavefronts (in a launch of its own).
