@@ -441,11 +441,6 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
     *(u32x4*)(smem + i) = u32x4{0, 0, 0, 0};
   __syncthreads();
 
-  // Pads the code in front of the loops: where the step loop (16.5 KB) lies within a 64-byte instruction cache line
-  // is worth 3 % of the launch.  131072 tokens, 64/8 heads, d = 128, ms: loop at byte 40: 288.0, at 0: 292.3,
-  // at 16: 294.6, at 24: 294.6, at 56: 294.5 (no other size was measured, nor heads of 64 and 192, which have no pad).
-  // The launch's time is checked again whenever the code in front changes.
-  if constexpr (DQK == 128) asm volatile(".rept 15\n s_nop 0\n .endr");
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
   // are cut into n_split runs of g_item heads, each an item of its own.

@@ -122,26 +122,6 @@ def test_asm_mfma_kernels_have_no_vgpr_spills():
         assert "v_accvgpr_mov" not in body, name
 
 
-def test_the_step_loop_of_the_key_tile_kernel_lies_where_it_is_fastest():
-    """Byte 40 of a 64-byte instruction cache line (elsewhere the 131072-token launch is up to 3 % longer): the pad
-    in front of the loop has to be set again when the code before it changes."""
-    llvm = os.path.join(os.path.dirname(os.path.realpath(B._hipcc())), "..", "llvm", "bin")
-    with tempfile.TemporaryDirectory() as tmp:
-        obj = os.path.join(tmp, "bwd.o")
-        subprocess.run([B._hipcc()] + B.HIP_FLAGS + ["--cuda-device-only", "--no-gpu-bundle-output", "-c",
-                                                     os.path.join(B.CSRC, "bwd.hip"), "-o", obj],
-                       check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-        text = subprocess.run([os.path.join(llvm, "llvm-objdump"), "-d", "--no-show-raw-insn", obj], check=True,
-                              stdout=subprocess.PIPE).stdout.decode()
-    body = next(b for b in re.split(r"\n(?=[0-9a-f]{16} <)", text) if "bwd_dkdv_kernelILi128ELi128E" in b[:120])
-    loops = []
-    for words, at in re.findall(r"s_branch (\d+)\s+// ([0-9A-F]{12}):", body):
-        back = 65536 - int(words)
-        if 3000 < back < 6000:                   # words: the loop is 16.5 KB, the one over items 26 KB
-            loops.append(int(at, 16) + 4 - 4 * back)
-    assert [head % 64 for head in loops] == [40]
-
-
 def test_the_forward_kernels_keep_their_registers():
     """What the forward takes in front of its loops comes out of its loops' registers: with a look-up of the tile
     order in it the head size 128 forms had gone from 246 and 250 registers to 252 and 256, and the one form with
