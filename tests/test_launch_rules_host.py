@@ -1,6 +1,7 @@
 """The GPU tests that stand on either side of a line between two ways to launch say which way each of their packs takes;
 here the library's rules are asked, without a GPU, so that a line that moves shows in the tests that it empties."""
 import launch_rules as rules
+import test_dkdv_eight_waves_gpu as eight_waves
 import test_fwd_few_rounds_gpu as few_rounds
 import test_fwd_halves_gpu as halves
 import test_one_backward_launch_gpu as one_launch
@@ -29,6 +30,16 @@ def test_the_backwards_lines():
     packs += [([60] * times, 16, 16, 192) for times, _ in one_launch.LINES_192]
     check([rules.backward(*p)[0] for p in packs], [x[-1] for x in one_launch.LINES + one_launch.LINES_192], packs)
     assert all("one launch" not in rules.backward(*p, records=True)[0] for p in packs)
+
+
+def test_the_line_between_eight_and_four_wavefronts():
+    packs = [x[:4] for x in eight_waves.LINES]
+    check([rules.backward(*p)[0] for p in packs], [x[-1] for x in eight_waves.LINES], packs)
+    # the small packs have one launch, and the kernel of eight in a launch of its own with records
+    small = [(eight_waves.EDGES, Hq, Hkv, d) for d in (64, 128) for Hq, Hkv in ((1, 1), (2, 1), (3, 1), (4, 1), (8, 2))]
+    small += [([n], 2, 2, d) for d in (64, 128) for n in (100, 577)] + [([8300, 97], 16, 8, 128), ([1500, 129, 31], 6, 2, 64)]
+    assert all(rules.backward(*p)[0].startswith("one launch") for p in small)
+    assert all(rules.backward(*p, records=True)[0] == "eight waves" for p in small)
 
 
 def test_items_of_three_heads_and_more_have_eight_wavefronts():
