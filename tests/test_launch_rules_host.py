@@ -5,6 +5,7 @@ import test_dkdv_eight_waves_gpu as eight_waves
 import test_fwd_few_rounds_gpu as few_rounds
 import test_fwd_halves_gpu as halves
 import test_one_backward_launch_gpu as one_launch
+import test_race_hunt_gpu as race_hunt
 
 
 def check(got, want, packs):
@@ -63,3 +64,19 @@ def test_streamed_rows_of_the_cross_entropy_keep_two_workgroups_a_unit():
     assert rules.cross_entropy_per_cu(1024, 1, hold=False, with_grad=False) == 2
     assert rules.cross_entropy_per_cu(1024, 1, hold=False, with_grad=True) == 2
     assert [rules.cross_entropy_per_cu(*x, hold=True, with_grad=False) for x in ((256, 8), (512, 20), (1024, 20))] == [4, 1, 1]
+
+
+def test_the_race_hunt_reaches_every_kernel():
+    cases = race_hunt.CASES
+    packs = [c[:4] for c in cases]
+    check([rules.forward(*p) for p in packs], [c[5] for c in cases], packs)
+    check([rules.backward(*p)[0] for p in packs], [c[6] for c in cases], packs)
+    fwd, bwd = {(c[3], c[5]) for c in cases}, {(c[3], c[6]) for c in cases}
+    for d in (64, 128, 192):
+        assert fwd >= {(d, w) for w in ("singles", "halves", "256-row tiles", "pairs queued", "256-row tiles queued")}
+        assert bwd >= {(d, w) for w in ("one launch", "four waves")}
+    assert (128, "pairs") in fwd and bwd >= {(d, w) for d in (64, 128) for w in ("one launch interleaved", "eight waves")}
+    # items handed over from queues: more of them than workgroups are resident, in the plain call, in either kind of group
+    for d, ways in ((64, ("eight waves", "four waves")), (128, ("eight waves", "four waves")), (192, ("four waves",))):
+        for way in ways:
+            assert any(c[3] == d and c[6] == way and rules.backward(*c[:4])[2] > 256 for c in cases), (d, way)
