@@ -138,8 +138,9 @@ hbp_status hbp_workspace_bytes(const hbp_attn_desc* desc, int32_t which, size_t*
 /* Optional per-workgroup record written by the persistent kernels when `profile` != NULL
  * (device memory, hbp_profile_capacity() records). ticks are the 100 MHz constant clock.
  * A kernel asked for records always takes its items from queues.  Without them, a kernel whose items all fit on the
- * chip at once runs one workgroup an item, and dK/dV and dQ of a pack of few rounds go in one launch, so the records of
- * such a pack describe other launches than the plain ones (the results are the same bits). */
+ * chip at once runs one workgroup an item, the forward of a pack of few rounds too (some of them with half the wavefronts a
+ * workgroup), and dK/dV and dQ of such a pack go in one launch, so its records describe other launches than the plain ones
+ * (the results are the same bits). */
 typedef struct {
   uint32_t hw_id;      /* raw HW_ID register of the workgroup's first wave (CU, SE, ...)  */
   uint32_t xcc_id;     /* raw XCC_ID register (accelerator die)                           */
@@ -191,8 +192,10 @@ hbp_status hbp_varlen_attn_fwd(const hbp_attn_desc* desc, const void* q, const v
  * Three launches on `stream`: a pre-pass (D), the persistent key-tile kernel (dK/dV accumulated in
  * registers over the query blocks and over the query heads of each kv head; followed by a small
  * reduce kernel when there are fewer than 8 kv heads, see hbp_workspace_bytes) and the persistent
- * query-tile kernel (dQ; it recomputes S and dP).  No atomics: every output element is written
- * once, results are bit-stable.
+ * query-tile kernel (dQ; it recomputes S and dP); the last two are one launch for a pack of few rounds.  No atomics: every output element is written
+ * once, and a call repeated gives the same bits, with records, events or another workspace too.  dK and dV add up in an
+ * order that goes by the pack (its tokens, number of samples, heads and tile lists), so those of one and the same sample
+ * may differ in their last bits from pack to pack (relative 2-norm 2e-5 to 5e-5).
  * q_tiles: the HBP_TILES_QUERY list made with hbp_tile_rows(..., HBP_FWD), served in its order (the
  * forward's list, hbp_order_query_tiles included, unless that was planned with a larger desc->fwd_tile_rows, which the backward ignores);
  * kv_tiles: the HBP_TILES_KEY list made with hbp_tile_rows(..., HBP_BWD).
