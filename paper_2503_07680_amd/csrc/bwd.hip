@@ -858,13 +858,21 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams 
 //
 // A lone wave per SIMD (the kernel above) issues one instruction every 5 to 6 clocks, and a step has about 6 an MFMA:
 // it is bound by its own instruction stream, the matrix pipe 57 % busy.  Two waves of half the rows fill each other's
-// gaps (65 %), and the fewer clocks of a step matter most where the card is not at its power limit.  What makes room
+// gaps: 67 % busy, 16 % fewer clocks a launch (32768 tokens with a sample of 16384; 70 % at 131072 tokens).  That makes the
+// launch only 3 to 5 % shorter, since the card, at its power limit, then clocks 1.74 GHz instead of 1.93; the fewer clocks
+// of a step matter most where it is not.  What makes room
 // for the second wave in 256 registers a lane: the scores of 32 rows alone in flight, their own four stages following
 // each other (S | dP and the probabilities | dV and dS | dK), and at head size 128 the K fragments read from LDS in
 // every step.  dK/dV kernel, four waves -> eight, us: 8192 tokens, 32/8 heads of 128: 184 -> 159; 32768 tokens with a
 // sample of 16384: 4062 -> 3869, 8/1 heads 1067 -> 1039; 131072 tokens, 64/8 heads, ms: 291 -> 277; 5497 tokens, 8 heads
 // of 64: 49.3 -> 42.5; 1024 tokens, 4 heads of 64: 14.8 -> 13.5.
 // The exchange at the end costs an item 1.9 us: see eight_waves() for where the line lies.
+//
+// At head size 128 it spills 17 vector and 85 scalar registers: 80 bytes of scratch a lane, none of it touched between the
+// first and the last MFMA, and two reads of a spilled scalar in three steps.  An item writes and reads again 22 KB that way,
+// 178 MB of a launch's writes instead of 131 (32768 tokens, 32/8 heads; 1.3 % of its traffic).  Most of it makes room
+// for the profile records' state, which is held over every item whether records are asked for or not: without it 7 and 63
+// (32 bytes).
 //
 // Tried here and slower or the same: V in LDS too (the LDS pipe, busy in half the clocks, costs power: +2 %); the two
 // groups half a step apart (+2 %); s_setprio around the MFMA chains; copies with a wait of their own in mid-step.

@@ -451,7 +451,8 @@ __device__ __forceinline__ Taken direct_item_inline(int n_tiles, int Hkv, int pe
 // instructions.  Forward, us, take_item -> two functions: 5515 tokens with a sample of 4017, 12/3 heads of 128: 99.2 ->
 // 94.7; 16000 tokens, 8/1 heads: 193.6 -> 186.7; 7000 tokens, 12/3 heads: 121.7 -> 117.2; 12000 tokens, 24 heads: 286.6
 // -> 287.2; 30000 tokens, 8 heads of 64: 151.4 -> 152.5.  The backward kernels keep take_item: with two functions the
-// training step of 131072 tokens, 64/8 heads, went from 613.0 to 621.4 ms.
+// training step of 131072 tokens, 64/8 heads, went from 613.0 to 621.4 ms (with the dK/dV kernel of four wavefronts; the one
+// of eight was not measured with two).
 __device__ __attribute__((noinline)) Taken queued_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
                                                         int q_tried, int steal_stride) {
   return queued_item_inline(counters, n_tiles, Hkv, per_kv, q_cur, q_tried, steal_stride);

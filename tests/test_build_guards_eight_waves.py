@@ -54,3 +54,9 @@ def test_the_eight_wave_kernel(d):
     assert not any("v_accvgpr_mov" in l for l in ins)
     regs = int(re.search(r"\.name:\s+%s\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)" % name, text).group(1))
     assert regs <= 256  # two wavefronts per SIMD
+    # What is parked in scratch is written and read again by every item, in front of and behind its steps: no more of it
+    # than there is (vector registers, scalar registers, bytes a lane).
+    block = next(b for b in re.findall(r"  - \.agpr_count:.*?\.wavefront_size:", text, re.S) if name in b)
+    spills = [int(re.search(r"\.%s:\s+(\d+)" % k, block).group(1))
+              for k in ("vgpr_spill_count", "sgpr_spill_count", "private_segment_fixed_size")]
+    assert all(a <= b for a, b in zip(spills, {64: (0, 78, 0), 128: (17, 85, 80)}[d])), spills
