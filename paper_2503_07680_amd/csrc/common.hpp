@@ -93,16 +93,21 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // half-waves exchange every second group of four, so that a lane ends up with 8 consecutive dims and
 // writes 16 bytes at a time (two stores per block instead of four).  Called by all lanes (the exchange
 // needs both halves); only lanes with `valid` store.
+// pack_block_half: elements 8 bp .. 8 bp + 7 of the lane's column, the lower half-wave with dims 16bp + 0..7, the upper with
+// 16bp + 8..15.
+__device__ __forceinline__ u32x4 pack_block_half(const f32x16& acc, float scale, int bp) {
+  const int e = 8 * bp;  // elements e..e+3: dims 16bp + 4hh + v; e+4..e+7: dims 16bp + 8 + 4hh + v
+  const uint32_t y0 = pack_bf16(acc[e] * scale, acc[e + 1] * scale), y1 = pack_bf16(acc[e + 2] * scale, acc[e + 3] * scale);
+  const uint32_t x0 = pack_bf16(acc[e + 4] * scale, acc[e + 5] * scale), x1 = pack_bf16(acc[e + 6] * scale, acc[e + 7] * scale);
+  const auto s0 = __builtin_amdgcn_permlane32_swap(y0, x0, false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(y1, x1, false, false);
+  return u32x4{s0[0], s1[0], s0[1], s1[1]};
+}
 __device__ __forceinline__ void store_block_bf16(uint16_t* row, const f32x16& acc, float scale, int hh, bool valid) {
 #pragma unroll
   for (int bp = 0; bp < 2; ++bp) {
-    const int e = 8 * bp;  // elements e..e+3: dims 16bp + 4hh + v; e+4..e+7: dims 16bp + 8 + 4hh + v
-    const uint32_t y0 = pack_bf16(acc[e] * scale, acc[e + 1] * scale), y1 = pack_bf16(acc[e + 2] * scale, acc[e + 3] * scale);
-    const uint32_t x0 = pack_bf16(acc[e + 4] * scale, acc[e + 5] * scale), x1 = pack_bf16(acc[e + 6] * scale, acc[e + 7] * scale);
-    const auto s0 = __builtin_amdgcn_permlane32_swap(y0, x0, false, false);
-    const auto s1 = __builtin_amdgcn_permlane32_swap(y1, x1, false, false);
-    // lower half-wave: dims 16bp + 0..7, upper: 16bp + 8..15
-    if (valid) *(u32x4*)(row + 16 * bp + 8 * hh) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+    const u32x4 x = pack_block_half(acc, scale, bp);
+    if (valid) *(u32x4*)(row + 16 * bp + 8 * hh) = x;
   }
 }
 
@@ -314,6 +319,79 @@ __device__ __forceinline__ void wait_async_loads() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt left at their maxima
 }
 
+// A wavefront's own 32 rows of a [rows][D] operand, taken through LDS in whole rows: the fragments of an MFMA operand have a
+// row a lane, and read from global memory that way a load touches 32 rows at 32 bytes each, which holds the compute unit's
+// address path about 64 clocks a load instead of 16 (what counts is whether neighbouring lanes read the same line: 8 rows at
+// 128 bytes with neighbouring lanes in different rows gain nothing).  The same bytes read in whole rows, 8192 tokens, 32/8
+// heads of 128: from an item's identity to its first product 3.0 -> 1.9 us in the forward, 3.6 -> 2.0 in the dQ items of the
+// common launch.  The rows are swizzled like those of a tile.  Nobody else touches `lds`, so the wavefront waits for its
+// copies and needs no barrier.
+template <int D>
+struct RowStage {
+  static constexpr int RB = D * 2, BYTES = 32 * RB, N = BYTES / 1024;  // copies (or stores) of 1 KiB
+  // row and byte inside its row that LDS position i * 1024 + lane * 16 holds
+  static __device__ __forceinline__ void place(int i, int lane, int& row, int& byte) {
+    const int pos = i * 1024 + lane * 16;
+    row = pos / RB;
+    byte = swz<D>((pos % RB) / 16, row) * 16;
+  }
+  // The lane again, opaque to the optimiser, for each of the functions below: their addresses are rebuilt for every item and
+  // not held across its loops.
+  static __device__ __forceinline__ int fresh(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+  }
+  // g: the first row (wave-uniform); rows >= rows_valid (at least 1) re-read the last valid one
+  static __device__ __forceinline__ void copy_in(const uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane) {
+    lane = fresh(lane);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      int row, byte;
+      place(i, lane, row, byte);
+      async_copy16(g, (uint32_t)min(row, rows_valid - 1) * stride_bytes + (uint32_t)byte, lds + i * 1024);
+    }
+  }
+  // 16-byte chunk 2 * pair + lane / 32 of row lane % 32
+  static __device__ __forceinline__ uint32_t at(uint32_t lds, int pair, int lane) {
+    return lds + (lane & 31) * RB + swz<D>(2 * pair + (lane >> 5), lane & 31) * 16;
+  }
+  // the D / 16 fragments of the rows as an MFMA operand: lane has row lane % 32, dims 16 c + 8 (lane / 32) .. + 7 in fragment
+  // c; zeros where the lane's row is not valid
+  template <int NC>
+  static __device__ __forceinline__ void fragments(uint32_t lds, int lane, bool valid, Frag (&f)[NC]) {
+    lane = fresh(lane);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      f[c].u = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, c, lane);
+      if (!valid) f[c].u = u32x4{0, 0, 0, 0};
+    }
+  }
+  // The other way: accumulator blocks of 32 dims (see store_block_bf16) into the rows, and the finished rows to global
+  // memory, 1 KiB a store.
+  template <int NB>
+  static __device__ __forceinline__ void put(uint32_t lds, int lane, const f32x16 (&acc)[NB], float scale) {
+    lane = fresh(lane);
+#pragma unroll
+    for (int b = 0; b < 2 * NB; ++b)
+      *(__attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, b, lane) = pack_block_half(acc[b / 2], scale, b % 2);
+  }
+  static __device__ __forceinline__ void copy_out(uint16_t* g, int64_t stride, int rows_valid, uint32_t lds, int lane) {
+    lane = fresh(lane);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      int row, byte;
+      place(i, lane, row, byte);
+      const u32x4 x = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(lds + i * 1024 + lane * 16);
+      if (row < rows_valid) *(u32x4*)((char*)(g + row * stride) + byte) = x;
+    }
+  }
+};
+// all but the last N of this wave's outstanding loads and copies have completed
+template <int N>
+__device__ __forceinline__ void wait_async_but() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "i"(N) : "memory");
+}
+
 // ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives element i%4 of the 8-byte
 // words addressed by lanes i/4, i/4+4, i/4+8, i/4+12 of the group.
 __device__ __forceinline__ s16x4 lds_read_tr16(const char* addr) {
@@ -446,20 +524,12 @@ __device__ __forceinline__ Taken direct_item_inline(int n_tiles, int Hkv, int pe
   return t;
 }
 // Real calls, everything passed and returned by value in registers: inlined into the persistent kernels their
-// temporaries cost them registers they do not have (two of them would spill).  The forward calls one function for
-// either way: with take_item, the one for both, it reloaded 10 more spilled scalars in its hot loop of 1296
-// instructions.  Forward, us, take_item -> two functions: 5515 tokens with a sample of 4017, 12/3 heads of 128: 99.2 ->
-// 94.7; 16000 tokens, 8/1 heads: 193.6 -> 186.7; 7000 tokens, 12/3 heads: 121.7 -> 117.2; 12000 tokens, 24 heads: 286.6
-// -> 287.2; 30000 tokens, 8 heads of 64: 151.4 -> 152.5.  The backward kernels keep take_item: with two functions the
-// training step of 131072 tokens, 64/8 heads, went from 613.0 to 621.4 ms (with the dK/dV kernel of four wavefronts; the one
-// of eight was not measured with two).
+// temporaries cost them registers they do not have (two of them would spill).  The forward's items without queues are a
+// kernel of their own (fwd_direct_kernel), so it calls the function of the queues alone; the backward's kernels have one
+// for both.
 __device__ __attribute__((noinline)) Taken queued_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
                                                         int q_tried, int steal_stride) {
   return queued_item_inline(counters, n_tiles, Hkv, per_kv, q_cur, q_tried, steal_stride);
-}
-__device__ __attribute__((noinline)) Taken direct_item(int n_tiles, int Hkv, int per_kv, int q_cur, int q_tried,
-                                                        int block) {
-  return direct_item_inline(n_tiles, Hkv, per_kv, q_cur, q_tried, block);
 }
 __device__ __attribute__((noinline)) Taken take_item(int32_t* counters, int n_tiles, int Hkv, int per_kv, int q_cur,
                                                       int q_tried, int block) {
@@ -495,8 +565,8 @@ __device__ __forceinline__ void race_fence() {
 
 // Workgroup-wide fetch of the next item: thread 0 takes it, everybody reads it back as scalars.
 // slot: two ints of LDS that nobody else touches between the surrounding barriers.
-// TWO: a function for items with queues and one for items without (see queued_item).
-template <bool TWO = false>
+// QUEUES: there always are queues.
+template <bool QUEUES = false>
 __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int tid, int& q_cur, int& q_tried,
                                           int& tile_idx, int& head) {
   // the slot is addressed as LDS (not through a generic pointer: that becomes flat accesses, each
@@ -507,10 +577,8 @@ __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int t
   if (tid == 0) {
     const int block = (int)blockIdx.x;
     Taken tk;
-    if constexpr (!TWO) tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, block);
-    else if (wq.counters)
-      tk = queued_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, 2 * ((block >> 3) & 3) + 1);
-    else tk = direct_item(wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, block);
+    if constexpr (QUEUES) tk = queued_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, 2 * ((block >> 3) & 3) + 1);
+    else tk = take_item(wq.counters, wq.n_tiles, wq.Hkv, wq.per_kv, q_cur, q_tried, block);
     q_cur = tk.q_cur;
     q_tried = tk.q_tried;
     box[0] = tk.tile_idx;
@@ -521,6 +589,29 @@ __device__ __forceinline__ bool next_item(const WorkQueues& wq, int* slot, int t
   head = __builtin_amdgcn_readfirstlane(box[1]);
   lds_barrier();
   return tile_idx >= 0;
+}
+
+// A work item's tile record and its sample's bounds, all wave-uniform; false: the record names no sample.  The bounds of all
+// samples (up to 63) are read beside the record and not behind it, so an item waits for one read instead of two.
+__device__ __forceinline__ bool load_tile(const hbp_tile* tiles, int idx, const int32_t* cu, int n_samples, int lane,
+                                          hbp_tile& tl, int& s0, int& s1) {
+  asm volatile("" : "+v"(lane));  // the address is not worth a register across the item's loops
+  const int bound = cu[min(lane, n_samples)];
+  const hbp_tile t = tiles[idx];
+  tl.sample = __builtin_amdgcn_readfirstlane(t.sample);
+  tl.tile = __builtin_amdgcn_readfirstlane(t.tile);
+  tl.row_begin = __builtin_amdgcn_readfirstlane(t.row_begin);
+  tl.row_end = __builtin_amdgcn_readfirstlane(t.row_end);
+  s0 = s1 = 0;
+  if (tl.sample < 0 || tl.sample >= n_samples) return false;
+  if (n_samples < kWave) {
+    s0 = __builtin_amdgcn_readlane(bound, tl.sample);
+    s1 = __builtin_amdgcn_readlane(bound, tl.sample + 1);
+  } else {
+    s0 = __builtin_amdgcn_readfirstlane(cu[tl.sample]);
+    s1 = __builtin_amdgcn_readfirstlane(cu[tl.sample + 1]);
+  }
+  return true;
 }
 
 struct FwdParams {

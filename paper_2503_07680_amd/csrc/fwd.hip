@@ -242,6 +242,9 @@ struct FwdWave {
       } else if (PAR == 1) {
         ring[jn % PD] = k_frag(PAR, jn - TOTAL, KADD);
       }
+      // The read goes out in front of the slices: behind one of them it lands late.  (Which way the compiler has it changes
+      // with its choice of registers; 131072 tokens, 64/8 heads of 128: 133.3 ms, 131.2 this way.)
+      __builtin_amdgcn_sched_barrier(0);
       if (do_e) {
         const int lo = j < NC ? j * EA / NC : EA + (j - NC) * (NSL - EA) / NB;
         const int hi = j < NC ? (j + 1) * EA / NC : EA + (j - NC + 1) * (NSL - EA) / NB;
@@ -274,10 +277,49 @@ struct FwdWave {
 // head and share the K/V stream in the same way (every wavefront stops at its own diagonal): the
 // form for odd group sizes, multi-head attention included.  Either way a compute unit holds eight
 // wavefronts.
-template <int DQK, int DV, int HP, int TP>
-__global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(const FwdParams p) {
+//
+// Where a wavefront's rows of Q go through LDS (RowStage), and those of O: beside the tile buffers if that fits (own(): O
+// too), else in the second K and V buffers, which take their first tile once every wavefront has read its rows, and behind
+// them what is left.  Four wavefronts of head size 192 have no room for two workgroups a compute unit that way: they read Q
+// a row a lane.
+template <int DQK, int DV, int NW>
+struct FwdLds {
+  static constexpr int K_TILE = 64 * DQK * 2, V_TILE = 64 * DV * 2, TILES = 2 * (K_TILE + V_TILE), PER_CU = 8 / NW;
+  static constexpr int STAGE = RowStage<DQK>::BYTES, MOST = 160 * 1024 / PER_CU;
+  static constexpr bool kOwn = TILES + NW * STAGE <= MOST;
+  static constexpr int IN_K = K_TILE / STAGE, IN_V = V_TILE / STAGE;  // wavefronts whose rows the second K and V buffers take
+  static constexpr int BEHIND = kOwn ? NW : NW > IN_K + IN_V ? NW - IN_K - IN_V : 0;
+  static constexpr int BYTES = TILES + BEHIND * STAGE;
+  static constexpr bool kStaged = BYTES <= MOST;
+  static constexpr int bytes() { return kStaged ? BYTES : TILES; }
+  static_assert(DV <= DQK, "O's rows fit where Q's were");
+  static __device__ __forceinline__ uint32_t stage(uint32_t lds0, int wave) {
+    if (kOwn) return lds0 + TILES + wave * STAGE;
+    if (wave < IN_K) return lds0 + K_TILE + wave * STAGE;
+    if (wave < IN_K + IN_V) return lds0 + 2 * K_TILE + V_TILE + (wave - IN_K) * STAGE;
+    return lds0 + TILES + (wave - IN_K - IN_V) * STAGE;
+  }
+};
+
+// The kernel's arguments.  AGAIN: opaque to the optimiser, so that they are read again here and not held in scalar registers
+// over an item's loops, where spilled ones came back (38 of 1330 instructions of the loop over pairs of unmasked tiles, head
+// size 128, 256-row tiles).
+typedef const __attribute__((address_space(4))) FwdParams FwdArgs;
+template <bool AGAIN>
+__device__ __forceinline__ FwdArgs* fwd_args() {
+  FwdArgs* a = (FwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  if (AGAIN) asm volatile("" : "+s"(a));
+  return a;
+}
+
+// DIRECT: the workgroup takes one item, by its place in the grid (kv heads, query heads of one, tiles): no function to find
+// it, no divisions and no barriers in front of it (.9 of an item's 20 us at 8192 tokens, 32/8 heads of 128), and without a loop
+// over items 30 registers less: at head size 64 three workgroups of four wavefronts fit a compute unit.
+template <int DQK, int DV, int HP, int TP, bool DIRECT>
+__device__ __forceinline__ void fwd_items() {
   static_assert(HP * TP <= 2, "eight wavefronts per compute unit");
   constexpr int NW = 4 * HP * TP;
+  using Lds = FwdLds<DQK, DV, NW>;
   using W = FwdWave<DQK, DV>;
   constexpr int BM = 128 * TP, BN = W::BN;
   constexpr int KRB = W::KRB, VRB = W::VRB, K_TILE = W::K_TILE, V_TILE = W::V_TILE;
@@ -295,7 +337,7 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
   W w;
   const uint32_t lds0 = lds_address(smem);
   w.hh = hh;
-  w.scale_log2 = p.scale_log2;
+  w.scale_log2 = fwd_args<false>()->scale_log2;
   // per-lane LDS byte offsets of the A operands (row part that does not depend on the 32-key block)
 #pragma unroll
   for (int c = 0; c < NC; ++c) w.koff[c] = lds0 + l32 * KRB + swz<DQK>(2 * c + hh, l32) * 16;
@@ -310,23 +352,30 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
         w.voff[r][eb] = lds0 + 2 * K_TILE + (8 * r + k8) * VRB + swz<DV>(c, 8 * r + k8) * 16 + (s & 1) * 8;
       }
   }
-  const uint32_t k_stride_b = (uint32_t)p.k_st * 2, v_stride_b = (uint32_t)p.v_st * 2;
+  const uint32_t k_stride_b = (uint32_t)fwd_args<false>()->k_st * 2, v_stride_b = (uint32_t)fwd_args<false>()->v_st * 2;
   FullTileLoader<DQK, BN, NW> k_loader;
   FullTileLoader<DV, BN, NW> v_loader;
   k_loader.init(wave, lane, k_stride_b);
   v_loader.init(wave, lane, v_stride_b);
 
+  const bool profiled = !DIRECT && fwd_args<false>()->prof;
   uint32_t n_done = 0;
   uint64_t t_first = 0, t_last = 0, t_busy = 0;
 
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
+    const FwdArgs& p = *fwd_args<!DIRECT>();
     int tile_idx, h;
-    if (!next_item<true>(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
+    if constexpr (DIRECT) {
+      tile_idx = blockIdx.z;
+      h = blockIdx.x * gridDim.y + blockIdx.y;
+    } else {
+      const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, p.g / HP / p.n_split};
+      if (!next_item<true>(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
+    }
     h = h * HP + wave / (4 * TP);  // this wave's head
     uint64_t t0 = 0;
-    if (p.prof && tid == 0) {
+    if (profiled && tid == 0) {
       t0 = wall_clock64();
       if (n_done == 0) t_first = t0;
     }
@@ -337,12 +386,10 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
     // dealt in turn (samples of 60 tokens, 12000 tokens, 24 heads of 128: .84 of the 256-row tiles' speed in plain order,
     // 1.23 this way).
     const int halves = HP * TP == 1 ? p.halves : 0, half = __builtin_popcount(tile_idx) & halves;
-    const hbp_tile tl = p.tiles[tile_idx >> halves];
-    bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
-    int s0 = 0, s1 = 0;
+    hbp_tile tl;
+    int s0, s1;
+    bool ok = load_tile(p.tiles, tile_idx >> halves, p.cu, p.n_samples, lane, tl, s0, s1);
     if (ok) {
-      s0 = p.cu[tl.sample];
-      s1 = p.cu[tl.sample + 1];
       // tiles start a multiple of 32 rows into their sample: each wave then has exactly one key
       // block that crosses its diagonal
       ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
@@ -370,12 +417,18 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
         if (t < nkt)
           v_loader.issue(vbase + (int64_t)t * BN * p.v_st, v_stride_b, n_keys - t * BN, v_lds + (t & 1) * V_TILE, wave, lane);
       };
+      // Q fragments (B operand of S^T = K Q^T): lane holds query l32, dims 16c+8hh..+7
+      const uint32_t stage = Lds::stage(lds0, wave);
+      int rows_left = r1 - (r0 + 32 * rw);
+      if (Lds::kStaged && wave_active)
+        RowStage<DQK>::copy_in(p.q + (int64_t)(r0 + 32 * rw) * p.q_st + (int64_t)h * p.q_sh, (uint32_t)p.q_st * 2, rows_left, stage, lane);
+      asm volatile("" : "+v"(rows_left));  // over the loops in a vector register: scalar ones are short there
       issue_k(0);
       issue_v(0);
-      issue_k(1);
-
-      // Q fragments (B operand of S^T = K Q^T): lane holds query l32, dims 16c+8hh..+7
-      {
+      if constexpr (Lds::kStaged) {
+        wait_async_but<decltype(k_loader)::PER_WAVE + decltype(v_loader)::PER_WAVE>();
+        RowStage<DQK>::fragments(stage, lane, row_valid, w.qf);
+      } else {
         const uint16_t* qp = p.q + (int64_t)my_row * p.q_st + (int64_t)h * p.q_sh + 8 * hh;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -424,7 +477,8 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
       };
 
       wait_async_loads();
-      __syncthreads();  // K(0), V(0), K(1) have landed
+      __syncthreads();  // K(0) and V(0) have landed, and every wavefront has read its rows of Q
+      issue_k(1);       // lands behind the first scores and phase 0
       if (nb > 0) {
         w.first_scores();
         w.preload_k(1);
@@ -518,22 +572,31 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
       // finalise: O = acc / l, LSE = (m + log2 l) * ln 2
       const float l_tot = w.l_run + xor32(w.l_run);
       {
+        const FwdArgs& p = *fwd_args<!DIRECT>();
         const float inv = 1.f / l_tot;
-        uint16_t* op = p.o + (int64_t)my_row * p.o_st + (int64_t)h * p.o_sh;
+        const bool row_valid = l32 < rows_left;
+        if constexpr (Lds::kOwn) {
+          RowStage<DV>::put(stage, lane, w.oacc, inv);
+          RowStage<DV>::copy_out(p.o + (int64_t)__builtin_amdgcn_readfirstlane(my_row) * p.o_st + (int64_t)h * p.o_sh, p.o_st,
+                                 rows_left, stage, lane);
+        } else {
+          uint16_t* op = p.o + (int64_t)my_row * p.o_st + (int64_t)h * p.o_sh;
 #pragma unroll
-        for (int eb = 0; eb < NEB; ++eb) store_block_bf16(op + 32 * eb, w.oacc[eb], inv, hh, row_valid);
+          for (int eb = 0; eb < NEB; ++eb) store_block_bf16(op + 32 * eb, w.oacc[eb], inv, hh, row_valid);
+        }
         if (row_valid && hh == 0)
           p.lse[(int64_t)h * p.T + my_row] = (w.m_run + log2f(l_tot)) * 0.6931471805599453f;
       }
     }
-    if (p.prof && tid == 0) {
+    if constexpr (DIRECT) break;
+    if (profiled && tid == 0) {
       const uint64_t t1 = wall_clock64();
       t_busy += t1 - t0;
       t_last = t1;
       ++n_done;
     }
   }
-  if (p.prof && tid == 0) {
+  if (profiled && tid == 0) {
     hbp_profile_rec r;
     r.hw_id = hw_id_reg();
     r.xcc_id = xcc_id_reg();
@@ -542,38 +605,56 @@ __global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(
     r.first_tick = t_first;
     r.last_tick = t_last;
     r.busy_ticks = t_busy;
-    p.prof[blockIdx.x] = r;
+    fwd_args<false>()->prof[blockIdx.x] = r;
   }
+}
+
+template <int DQK, int DV, int HP, int TP>
+__global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_kernel(const FwdParams) {
+  fwd_items<DQK, DV, HP, TP, false>();
+}
+template <int DQK, int DV, int HP, int TP>
+__global__ __launch_bounds__(kThreads * HP * TP, 2 / (HP * TP)) void fwd_direct_kernel(const FwdParams) {
+  fwd_items<DQK, DV, HP, TP, true>();
 }
 
 __global__ void zero_counters_kernel(int32_t* c) {
   if (threadIdx.x < kNumXcd) c[threadIdx.x * kCounterStride] = 0;
 }
 
-template <int DQK, int DV, int HP, int TP>
-static int launch_fwd_hp(FwdParams p, bool direct, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  constexpr int lds_bytes = 2 * 64 * (DQK * 2 + DV * 2);
+template <int DQK, int DV, int HP, int TP, bool DIRECT>
+static int launch_fwd_hp(FwdParams p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  constexpr auto kernel = DIRECT ? fwd_direct_kernel<DQK, DV, HP, TP> : fwd_kernel<DQK, DV, HP, TP>;
+  constexpr int lds_bytes = FwdLds<DQK, DV, 4 * HP * TP>::bytes();
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute((const void*)fwd_kernel<DQK, DV, HP, TP>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = kNumCU * (2 / (HP * TP));
-  const int grid = (int)(direct || n_items < cap ? n_items : cap);
-  if (direct) p.counter = nullptr;
   p.n_split = heads_split(p.Hkv, p.g / HP);  // HP = 2: items are pairs of heads
-  if (p.counter) {
+  const int64_t n_items = (int64_t)p.n_tiles * (p.Hq / HP), cap = kNumCU * (2 / (HP * TP));
+  dim3 grid((unsigned)(n_items < cap ? n_items : cap));
+  if (DIRECT) {
+    // Tile by tile, longest first, the kv heads innermost: with eight of them, or a multiple, a die has always the same ones.
+    // (Not two of a die's heads at a time as with queues: the others' longest tiles would come last.  8381 tokens, 24 heads of
+    // 128: 219 -> 187 us; 1421 tokens: 22.1 -> 18.2.)
+    grid = dim3((unsigned)(p.Hkv * p.n_split), (unsigned)(p.g / HP / p.n_split), (unsigned)p.n_tiles);
+  } else {
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, p.counter);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }
   if (ev0 && hipEventRecord(ev0, s) != hipSuccess) return (int)hipErrorInvalidValue;
-  hipLaunchKernelGGL((fwd_kernel<DQK, DV, HP, TP>), dim3(grid), dim3(kThreads * HP * TP), lds_bytes, s, p);
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads * HP * TP), lds_bytes, s, p);
   const hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev1 && hipEventRecord(ev1, s) != hipSuccess) return (int)hipErrorInvalidValue;
   return (int)e;
+}
+template <int DQK, int DV, int HP, int TP>
+static int launch_fwd_hp(const FwdParams& p, bool direct, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  direct = direct && p.n_tiles <= 65535;  // the tiles are the grid's third dimension
+  return direct ? launch_fwd_hp<DQK, DV, HP, TP, true>(p, s, ev0, ev1) : launch_fwd_hp<DQK, DV, HP, TP, false>(p, s, ev0, ev1);
 }
 
 // tile_rows: rows per query tile of the worklist, 128 or (odd group sizes only) 256
