@@ -23,26 +23,36 @@ namespace hbp {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// A kernel's first argument.  AGAIN: opaque to the optimiser, so that its members are read again here and not held in scalar
+// registers over an item's loops, where spilled ones came back.
+typedef const __attribute__((address_space(4))) BwdParams BwdArgs;
+template <bool AGAIN>
+__device__ __forceinline__ BwdArgs* bwd_args() {
+  BwdArgs* a = (BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  if (AGAIN) asm volatile("" : "+s"(a));
+  return a;
+}
+
 struct ProfAcc {
   uint32_t n_done = 0;
   uint64_t t_first = 0, t_last = 0, t_busy = 0, t0 = 0;
 };
-__device__ __forceinline__ void prof_begin(ProfAcc& a, const hbp_profile_rec* prof, int tid) {
-  if (prof && tid == 0) {
+__device__ __forceinline__ void prof_begin(ProfAcc& a, bool profiled, int tid) {
+  if (profiled && tid == 0) {
     a.t0 = wall_clock64();
     if (a.n_done == 0) a.t_first = a.t0;
   }
 }
-__device__ __forceinline__ void prof_end(ProfAcc& a, const hbp_profile_rec* prof, int tid) {
-  if (prof && tid == 0) {
+__device__ __forceinline__ void prof_end(ProfAcc& a, bool profiled, int tid) {
+  if (profiled && tid == 0) {
     const uint64_t t1 = wall_clock64();
     a.t_busy += t1 - a.t0;
     a.t_last = t1;
     ++a.n_done;
   }
 }
-__device__ __forceinline__ void prof_write(const ProfAcc& a, hbp_profile_rec* prof, int tid) {
-  if (prof && tid == 0) {
+__device__ __forceinline__ void prof_write(const ProfAcc& a, bool profiled, hbp_profile_rec* prof, int tid) {
+  if (profiled && tid == 0) {
     hbp_profile_rec r;
     r.hw_id = hw_id_reg();
     r.xcc_id = xcc_id_reg();
@@ -62,8 +72,37 @@ __device__ __forceinline__ void prof_write(const ProfAcc& a, hbp_profile_rec* pr
 // HALVES = 2 (see bwd_both_kernel): the workgroup has eight wavefronts, four for each of two neighbouring query heads of
 // the same tile, and takes the launch's item `block` alone.  SHARED: both heads read the same kv head and work off the
 // same tiles in LDS (half the copies); otherwise each half has its own.
+//
+// Where a wavefront's rows of Q and dO go through LDS (RowStage): in the second K and V buffers, which take their first tile
+// once every wavefront has read its rows, and behind the tiles; kBoth: beside each other, else one after the other.
+template <int DQK, int DV, int HALVES, bool SHARED>
+struct DqLds {
+  static constexpr int NW = 4 * HALVES, K_TILE = 64 * DQK * 2, V_TILE = 64 * DV * 2, SETS = SHARED ? 1 : HALVES;
+  static constexpr int TILES = SETS * 2 * (K_TILE + V_TILE), MOST = 160 * 1024 / (HALVES == 1 && DQK <= 128 ? 2 : 1);
+  static constexpr bool kInTiles = DQK == DV;  // else all of them behind the tiles
+  static constexpr int UNIT = RowStage<DQK>::BYTES, UNIT_V = RowStage<DV>::BYTES;
+  static constexpr int IN_K = kInTiles ? K_TILE / UNIT : 0, IN_SET = 2 * IN_K, IN_TILES = SETS * IN_SET;
+  static constexpr bool kBoth = kInTiles ? TILES + (2 * NW - IN_TILES) * UNIT <= MOST : true;
+  static constexpr int UNITS = kBoth ? 2 * NW : NW;
+  static constexpr int BYTES = kInTiles ? TILES + (UNITS > IN_TILES ? UNITS - IN_TILES : 0) * UNIT : TILES + NW * (UNIT + UNIT_V);
+  static_assert(BYTES <= MOST && NW * UNIT <= TILES, "the compute unit's LDS; dQ's rows fit where the tiles were");
+  // lds0: the workgroup's
+  static __device__ __forceinline__ uint32_t unit(uint32_t lds0, int u) {
+    if (u >= IN_TILES) return lds0 + TILES + (u - IN_TILES) * UNIT;
+    const int set = u / (IN_SET ? IN_SET : 1), i = u - set * IN_SET;
+    return lds0 + set * 2 * (K_TILE + V_TILE) + (i < IN_K ? K_TILE + i * UNIT : 2 * K_TILE + V_TILE + (i - IN_K) * UNIT);
+  }
+  static __device__ __forceinline__ uint32_t q_at(uint32_t lds0, int wave) {
+    return kInTiles ? unit(lds0, wave) : lds0 + TILES + wave * (UNIT + UNIT_V);
+  }
+  static __device__ __forceinline__ uint32_t do_at(uint32_t lds0, int wave) {
+    return kInTiles ? unit(lds0, kBoth ? NW + wave : wave) : lds0 + TILES + wave * (UNIT + UNIT_V) + UNIT;
+  }
+};
+
 template <int DQK, int DV, int HALVES = 1, bool SHARED = false, bool DIRECT = HALVES == 2>
-__device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
+__device__ __forceinline__ void dq_items(int block) {
+  using Lds = DqLds<DQK, DV, HALVES, SHARED>;
   constexpr int BM = 128, BN = 64;
   constexpr int KRB = DQK * 2, VRB = DV * 2;
   constexpr int K_TILE = BN * KRB, V_TILE = BN * VRB;
@@ -114,12 +153,14 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
   TileLoader<DV, BN, NW> v_loader;  // same lane pattern as k_loader when the row sizes agree: then only that one is kept
   k_loader.init(cwave, lane);
   if (!kSameRows) v_loader.init(cwave, lane);
-  const uint32_t k_stride_b = (uint32_t)p.k_st * 2, v_stride_b = (uint32_t)p.v_st * 2;
+  const uint32_t k_stride_b = (uint32_t)bwd_args<false>()->k_st * 2, v_stride_b = (uint32_t)bwd_args<false>()->v_st * 2;
 
+  const bool profiled = !DIRECT && bwd_args<false>()->prof_dq;  // items of their own workgroup have no records
   ProfAcc pa;
-  const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / (SHARED ? 2 : 1) / p.n_split_dq};
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
+    const BwdArgs& p = *bwd_args<!DIRECT>();
+    const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / (SHARED ? 2 : 1) / p.n_split_dq};
     int tile_idx, h;
     if constexpr (!DIRECT) {
       if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
@@ -129,14 +170,12 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
       tile_idx = __builtin_amdgcn_readfirstlane(tk.tile_idx);
       h = HALVES * __builtin_amdgcn_readfirstlane(tk.head) + half;
     }
-    prof_begin(pa, p.prof_dq, tid);
+    prof_begin(pa, profiled, wave_in_wg);
 
-    const hbp_tile tl = p.q_tiles[tile_idx];
-    bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
-    int s0 = 0, s1 = 0;
+    hbp_tile tl;
+    int s0, s1;
+    bool ok = load_tile(p.q_tiles, tile_idx, p.cu, p.n_samples, lane, tl, s0, s1);
     if (ok) {
-      s0 = p.cu[tl.sample];
-      s1 = p.cu[tl.sample + 1];
       ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
            tl.row_end <= s1 && tl.row_end - tl.row_begin <= BM;
     }
@@ -144,6 +183,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
       const int r0 = tl.row_begin, r1 = tl.row_end;
       const bool has_head = HALVES == 1 || SHARED || h < p.Hq;  // an odd number of heads: the last pair has one
       if (!has_head) h = p.Hq - 1;
+      if (HALVES == 2) h = __builtin_amdgcn_readfirstlane(h);
       const int kh = h / p.g;
       const int qw0 = r0 - s0 + 32 * wave;
       const int my_row = r0 + 32 * wave + l32;
@@ -171,21 +211,30 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
 #pragma unroll
         for (int slot = 0; slot < NKCP + NVCP; ++slot) issue_slot(kt, slot);
       };
-      issue(0);
-
       Frag qf[NC], dof[NCV];
       float lse2 = INFINITY, Dv = 0.f;  // +inf: rows past the tile end get probability 0
+      if (row_valid) {
+        lse2 = p.lse2[(int64_t)h * p.T + my_row];
+        Dv = p.D[(int64_t)h * p.T + my_row];
+      }
+      const uint32_t lds_all = lds_address(smem_all);
+      const int first_row = r0 + 32 * wave;  // of this wave
       {
-        const uint16_t* qp = p.q + (int64_t)my_row * p.q_st + (int64_t)h * p.q_sh + 8 * hh;
-        const uint16_t* dop = p.d_o + (int64_t)my_row * p.o_st + (int64_t)h * p.o_sh + 8 * hh;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) qf[c].u = row_valid ? *(const u32x4*)(qp + 16 * c) : u32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int c = 0; c < NCV; ++c) dof[c].u = row_valid ? *(const u32x4*)(dop + 16 * c) : u32x4{0, 0, 0, 0};
-        if (row_valid) {
-          lse2 = p.lse2[(int64_t)h * p.T + my_row];
-          Dv = p.D[(int64_t)h * p.T + my_row];
+        const uint16_t* q_rows = p.q + (int64_t)first_row * p.q_st + (int64_t)h * p.q_sh;
+        const uint16_t* do_rows = p.d_o + (int64_t)first_row * p.o_st + (int64_t)h * p.o_sh;
+        const uint32_t q_at = Lds::q_at(lds_all, wave_in_wg), do_at = Lds::do_at(lds_all, wave_in_wg);
+        const int rows = has_head ? r1 - first_row : 0;
+        RowStage<DQK>::copy_in(q_rows, (uint32_t)p.q_st * 2, rows, q_at, lane);
+        if (Lds::kBoth) RowStage<DV>::copy_in(do_rows, (uint32_t)p.o_st * 2, rows, do_at, lane);
+        issue(0);
+        wait_async_but<NKCP + NVCP>();
+        RowStage<DQK>::fragments(q_at, lane, qf);
+        if constexpr (!Lds::kBoth) {
+          wait_lds_reads();
+          RowStage<DV>::copy_in(do_rows, (uint32_t)p.o_st * 2, rows, do_at, lane);
+          wait_async_loads();
         }
+        RowStage<DV>::fragments(do_at, lane, dof);
       }
       // the dP^T accumulator of every block starts at -D of the lane's query (one value per lane): the
       // subtraction in dS = P (dP - D) then comes out of the MFMAs
@@ -364,26 +413,42 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, int block) {
       }
       if (cur_buf) point_offsets_at(0);
 
-      {
-        uint16_t* dqp = p.dq + (int64_t)my_row * p.q_st + (int64_t)h * p.q_sh;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) store_block_bf16(dqp + 32 * db, dqacc[db], p.scale, hh, row_valid);
+      __syncthreads();  // the tiles are no longer read
+      if (wave_active) {
+        const uint32_t at = lds_all + wave_in_wg * Lds::UNIT;
+        RowStage<DQK>::put(at, lane, dqacc, p.scale);
+        RowStage<DQK>::copy_out(p.dq + (int64_t)first_row * p.q_st + (int64_t)h * p.q_sh, (uint32_t)p.q_st * 2, r1 - first_row, at, lane);
       }
     }
-    prof_end(pa, p.prof_dq, tid);
+    prof_end(pa, profiled, wave_in_wg);
     if constexpr (DIRECT) break;
   }
-  prof_write(pa, p.prof_dq, tid);
+  prof_write(pa, profiled, bwd_args<false>()->prof_dq, tid);
 }
 template <int DQK, int DV>
-__global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(const BwdParams p) {
-  dq_items<DQK, DV>(p, 0);
+__global__ __launch_bounds__(kThreads, DQK <= 128 ? 2 : 1) void bwd_dq_kernel(const BwdParams) {
+  dq_items<DQK, DV>(0);
 }
 
 // ----------------------------------------------------------------------------------- dK, dV
+// Where a wavefront's rows of K and V go through LDS (RowStage): behind the tiles, the last wavefront's rows of V where the
+// second Q buffer is, or at head size 192 it would not fit the compute unit's LDS.  (An item of one step, whose idle step
+// multiplies what is there by zero, has no rows for that wavefront: its copies write zeros.)
+template <int DQK, int DV>
+struct DkdvLds {
+  static constexpr int TILES = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
+  static constexpr int K = RowStage<DQK>::BYTES, V = RowStage<DV>::BYTES;
+  static constexpr int bytes() { return TILES + 4 * K + 3 * V; }
+  static_assert(bytes() <= 160 * 1024 && V <= 64 * DQK * 2 && DV <= DQK, "LDS of a compute unit");
+  static __device__ __forceinline__ uint32_t k_at(uint32_t lds0, int wave) { return lds0 + TILES + wave * K; }
+  static __device__ __forceinline__ uint32_t v_at(uint32_t lds0, int wave) {
+    return wave < 3 ? lds0 + TILES + 4 * K + wave * V : lds0 + 64 * DQK * 2;
+  }
+};
+
 // DIRECT: the launch's item `block` and no other (see bwd_both4_kernel).  n_resident: workgroups under way at a time.
 template <int DQK, int DV, bool DIRECT = false>
-__device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_resident) {
+__device__ __forceinline__ void dkdv_items(int block, int n_resident) {
   constexpr int BN = 128, BQ = 64;
   constexpr int QRB = DQK * 2, ORB = DV * 2;
   constexpr int Q_TILE = BQ * QRB, O_TILE = BQ * ORB;
@@ -429,7 +494,7 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
   uint32_t lseoff = lds0 + 2 * Q_TILE + 2 * O_TILE + 16 * hh;
   uint32_t dvoff = lseoff + 2 * BQ * 4;
 
-  const uint32_t q_stride_b = (uint32_t)p.q_st * 2, o_stride_b = (uint32_t)p.o_st * 2;
+  const uint32_t q_stride_b = (uint32_t)bwd_args<false>()->q_st * 2, o_stride_b = (uint32_t)bwd_args<false>()->o_st * 2;
   FullTileLoader<DQK, BQ> q_loader;
   FullTileLoader<DV, BQ> o_loader;
   q_loader.init(wave, lane, q_stride_b);
@@ -441,13 +506,16 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
     *(u32x4*)(smem + i) = u32x4{0, 0, 0, 0};
   __syncthreads();
 
+  using Lds = DkdvLds<DQK, DV>;
+  const bool profiled = !DIRECT && bwd_args<false>()->prof;
   ProfAcc pa;
   // Work item = (key tile, kv head, part of its query heads): with n_split > 1 the g heads of a kv head
   // are cut into n_split runs of g_item heads, each an item of its own.
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
-  const int g_item = p.g / p.n_split;
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
+    const BwdArgs& p = *bwd_args<!DIRECT>();
+    const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
+    const int g_item = p.g / p.n_split;
     int tile_idx, vh;
     if constexpr (DIRECT) {
       const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
@@ -458,14 +526,12 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
     }
     const int kh = vh / p.n_split, part = vh - kh * p.n_split;
     const int head0 = vh * g_item;  // first query head of the item
-    prof_begin(pa, p.prof, tid);
+    prof_begin(pa, profiled, tid);
 
-    const hbp_tile tl = p.tiles[tile_idx];
-    bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
-    int s0 = 0, s1 = 0;
+    hbp_tile tl;
+    int s0, s1;
+    bool ok = load_tile(p.tiles, tile_idx, p.cu, p.n_samples, lane, tl, s0, s1);
     if (ok) {
-      s0 = p.cu[tl.sample];
-      s1 = p.cu[tl.sample + 1];
       ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
            tl.row_end <= s1 && tl.row_end - tl.row_begin <= BN;
     }
@@ -557,17 +623,18 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
 #pragma unroll
         for (int slot = 0; slot < N_COPY; ++slot) issue_copy(slot, buf, std::false_type{});
       };
-      if (n_steps > 0) issue_next(0);
-
       // register-resident B operands of this wave's 32 keys: lane column = key l32
+      const uint32_t k_at = Lds::k_at(lds0, wave), v_at = Lds::v_at(lds0, wave);
+      const int first_key = tl.row_begin + 32 * wave;  // of this wave
+      RowStage<DQK>::copy_in(p.k + (int64_t)first_key * p.k_st + (int64_t)kh * p.k_sh, (uint32_t)p.k_st * 2, tl.row_end - first_key, k_at, lane);
+      RowStage<DV>::copy_in(p.v + (int64_t)first_key * p.v_st + (int64_t)kh * p.v_sh, (uint32_t)p.v_st * 2, tl.row_end - first_key, v_at, lane);
+      if (n_steps > 0) issue_next(0);
+      wait_async_but<NQC + NOC>();  // a wave copies its share of the tiles and, the first two, of the rows' scalars too
+
       Frag knat[NC], vnat[NCV];
       {
-        const uint16_t* kp = p.k + (int64_t)my_key * p.k_st + (int64_t)kh * p.k_sh + 8 * hh;
-        const uint16_t* vp = p.v + (int64_t)my_key * p.v_st + (int64_t)kh * p.v_sh + 8 * hh;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) knat[c].u = key_valid ? *(const u32x4*)(kp + 16 * c) : u32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int c = 0; c < NCV; ++c) vnat[c].u = key_valid ? *(const u32x4*)(vp + 16 * c) : u32x4{0, 0, 0, 0};
+        RowStage<DQK>::fragments(k_at, lane, knat);
+        RowStage<DV>::fragments(v_at, lane, vnat);
 #pragma unroll
         for (int c = 0; c < NCV; ++c) vnat[c].u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
       }
@@ -808,12 +875,12 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
       }
 
       if (p.n_split == 1) {
-        uint16_t* dkp = p.dk + (int64_t)my_key * p.k_st + (int64_t)kh * p.k_sh;
-        uint16_t* dvp = p.dv + (int64_t)my_key * p.v_st + (int64_t)kh * p.v_sh;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) store_block_bf16(dkp + 32 * db, dkt[db], -p.scale, hh, key_valid);
-#pragma unroll
-        for (int eb = 0; eb < NEB; ++eb) store_block_bf16(dvp + 32 * eb, dvt[eb], 1.0f, hh, key_valid);
+        if (wave_active) {  // both through the wave's rows of K
+          RowStage<DQK>::put(k_at, lane, dkt, -p.scale);
+          RowStage<DQK>::copy_out(p.dk + (int64_t)first_key * p.k_st + (int64_t)kh * p.k_sh, (uint32_t)p.k_st * 2, tl.row_end - first_key, k_at, lane);
+          RowStage<DV>::put(k_at, lane, dvt, 1.0f);
+          RowStage<DV>::copy_out(p.dv + (int64_t)first_key * p.v_st + (int64_t)kh * p.v_sh, (uint32_t)p.v_st * 2, tl.row_end - first_key, k_at, lane);
+        }
       } else if (key_valid) {
         // this part's sums, fp32, [part][key][kv head][dim]; the reduce kernel adds the parts up
         const int64_t row = ((int64_t)part * p.T + my_key) * p.Hkv + kh;
@@ -833,21 +900,21 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, int block, int n_
             *(f32x4*)(dvp + 32 * eb + 8 * b) = f32x4{dvt[eb][4 * b], dvt[eb][4 * b + 1], dvt[eb][4 * b + 2], dvt[eb][4 * b + 3]};
       }
     }
-    prof_end(pa, p.prof, tid);
+    prof_end(pa, profiled, tid);
     if constexpr (DIRECT) break;
   }
-  prof_write(pa, p.prof, tid);
+  prof_write(pa, profiled, bwd_args<false>()->prof, tid);
 }
 template <int DQK, int DV>
-__global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams p) {
-  dkdv_items<DQK, DV>(p, 0, (int)gridDim.x);
+__global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(const BwdParams) {
+  dkdv_items<DQK, DV>(0, (int)gridDim.x);
 }
 // dK/dV and dQ in one launch at head size 192: workgroups of four wavefronts, an item of either each, dK/dV first (as
 // many dQ items as dK/dV: in turn they would keep to half of a die's shader engines each).
 template <int DQK, int DV>
-__global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams p, int n_dkdv, int n_resident) {
-  if ((int)blockIdx.x < n_dkdv) dkdv_items<DQK, DV, true>(p, (int)blockIdx.x, n_resident);
-  else dq_items<DQK, DV, 1, false, true>(p, (int)blockIdx.x - n_dkdv);
+__global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams, int n_dkdv, int n_resident) {
+  if ((int)blockIdx.x < n_dkdv) dkdv_items<DQK, DV, true>((int)blockIdx.x, n_resident);
+  else dq_items<DQK, DV, 1, false, true>((int)blockIdx.x - n_dkdv);
 }
 
 // ------------------------------------------------------------------- dK, dV, eight wavefronts
@@ -868,25 +935,26 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams 
 // of 64: 49.3 -> 42.5; 1024 tokens, 4 heads of 64: 14.8 -> 13.5.
 // The exchange at the end costs an item 1.9 us: see eight_waves() for where the line lies.
 //
-// At head size 128 it spills 17 vector and 85 scalar registers: 80 bytes of scratch a lane, none of it touched between the
-// first and the last MFMA, and two reads of a spilled scalar in three steps.  An item writes and reads again 22 KB that way,
-// 178 MB of a launch's writes instead of 131 (32768 tokens, 32/8 heads; 1.3 % of its traffic).  Most of it makes room
-// for the profile records' state, which is held over every item whether records are asked for or not: without it 7 and 63
-// (32 bytes).
+// At head size 128 it spills 7 vector and 37 scalar registers: 32 bytes of scratch a lane, none of it touched between the
+// first and the last MFMA, and two reads of a spilled scalar in three steps.
+//
+// K and V come in whole rows through LDS and dK and dV go out that way (RowStage).  Read a row a lane, 12 loads of 8
+// wavefronts hold the address path about 2.5 us of an item; the stores of a row a lane about as long.
 //
 // Tried here and slower or the same: V in LDS too (the LDS pipe, busy in half the clocks, costs power: +2 %); the two
 // groups half a step apart (+2 %); s_setprio around the MFMA chains; copies with a wait of their own in mid-step.
 //
 // DIRECT: the launch's item `block` and no other (see bwd_both_kernel).  n_resident: workgroups under way at a time.
 template <int DQK, int DV, bool DIRECT = false>
-__device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n_resident) {
+__device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
   static_assert(DQK == DV, "one set of lane offsets for Q and dO");
   constexpr int BN = 128, BQ = 64, SUB = 32, NBUF = 3;
   constexpr int QRB = DQK * 2;
   constexpr int TILE = SUB * QRB, PAIR = 2 * TILE;  // Q and dO of a step, one group
   constexpr int NC = DQK / 16, NDB = DQK / 32;
   constexpr bool kKLds = DQK > 64;  // K fragments read from LDS in every step
-  constexpr int K_AT = 2 * NBUF * PAIR, ROWS_AT = K_AT + (kKLds ? 4 * NC * 1024 : 0);
+  // K fragments, and in front of an item's first step the tile's rows of K; those of V where the third buffers are
+  constexpr int K_AT = 2 * NBUF * PAIR, ROWS_AT = K_AT + 4 * RowStage<DQK>::BYTES;
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // [group][buffer][Q | dO], [K fragments], [group][buffer][64 LSE2 | 64 D | 128 of no use]
@@ -921,16 +989,18 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
   for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(qtoff[0][db]), "+v"(qtoff[1][db]));
   const uint32_t tiles = lds0 + qs * (NBUF * PAIR) + kg * 1024, rows_lds = lds0 + ROWS_AT + qs * (NBUF * 1024) + kg * 256;
 
-  const uint32_t q_stride_b = (uint32_t)p.q_st * 2, o_stride_b = (uint32_t)p.o_st * 2;
+  const uint32_t q_stride_b = (uint32_t)bwd_args<false>()->q_st * 2, o_stride_b = (uint32_t)bwd_args<false>()->o_st * 2;
   FullTileLoader<DQK, SUB> q_loader, o_loader;
   q_loader.init(kg, lane, q_stride_b);
   o_loader.init(kg, lane, o_stride_b);
 
+  const bool profiled = !DIRECT && bwd_args<false>()->prof;
   ProfAcc pa;
-  const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
-  const int g_item = p.g / p.n_split;
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
+    const BwdArgs& p = *bwd_args<!DIRECT>();
+    const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
+    const int g_item = p.g / p.n_split;
     int tile_idx, vh;
     if constexpr (DIRECT) {
       const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
@@ -941,17 +1011,12 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
     }
     const int kh = vh / p.n_split, part = vh - kh * p.n_split;
     const int head0 = vh * g_item;
-    prof_begin(pa, p.prof, wave);
+    prof_begin(pa, profiled, wave);
 
-    hbp_tile tl = p.tiles[tile_idx];
-    tl.row_begin = __builtin_amdgcn_readfirstlane(tl.row_begin);
-    tl.row_end = __builtin_amdgcn_readfirstlane(tl.row_end);
-    tl.tile = __builtin_amdgcn_readfirstlane(tl.tile);
-    bool ok = tl.sample >= 0 && tl.sample < p.n_samples;
-    int s0 = 0, s1 = 0;
+    hbp_tile tl;
+    int s0, s1;
+    bool ok = load_tile(p.tiles, tile_idx, p.cu, p.n_samples, lane, tl, s0, s1);
     if (ok) {
-      s0 = __builtin_amdgcn_readfirstlane(p.cu[tl.sample]);
-      s1 = __builtin_amdgcn_readfirstlane(p.cu[tl.sample + 1]);
       ok = s0 >= 0 && s1 <= p.T && s0 <= tl.row_begin && tl.row_begin < tl.row_end &&
            tl.row_end <= s1 && tl.row_end - tl.row_begin <= BN;
     }
@@ -1033,27 +1098,29 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
         if constexpr (N_COPY > 4) issue_copy(std::integral_constant<int, 4>{}, buf_tag);
       };
       static_assert(N_COPY == 3 || N_COPY == 5, "32 rows of 128 or 256 bytes on four waves");
+      // K and V in whole rows (RowStage), half of a key group's by either of its waves
+      const uint32_t k_at = lds0 + K_AT + kg * RowStage<DQK>::BYTES;
+      const uint32_t v_at = lds0 + (kg >> 1) * (NBUF * PAIR) + 2 * PAIR + (kg & 1) * RowStage<DQK>::BYTES;
+      const int first_key = tl.row_begin + 32 * kg, keys_left = tl.row_end - first_key;
+      RowStage<DQK>::template copy_in<2>(p.k + (int64_t)first_key * p.k_st + (int64_t)kh * p.k_sh, (uint32_t)p.k_st * 2, keys_left, k_at, lane, qs);
+      RowStage<DQK>::template copy_in<2>(p.v + (int64_t)first_key * p.v_st + (int64_t)kh * p.v_sh, (uint32_t)p.v_st * 2, keys_left, v_at, lane, qs);
       issue_all(std::integral_constant<int, 0>{});
       advance(0);
       issue_all(std::integral_constant<int, 1>{});
       advance(1);
+      wait_async_but<2 * N_COPY>();
+      __syncthreads();
 
-      Frag knat[kKLds ? 1 : NC], vnat[NC];
+      Frag knat[NC], vnat[NC];
       {
-        const uint16_t* kp = p.k + (int64_t)my_key * p.k_st + (int64_t)kh * p.k_sh + 8 * hh;
-        const uint16_t* vp = p.v + (int64_t)my_key * p.v_st + (int64_t)kh * p.v_sh + 8 * hh;
-        if constexpr (kKLds) {  // the two waves of a key group write half of the fragments each
+        RowStage<DQK>::fragments(k_at, lane, knat);
+        RowStage<DQK>::fragments(v_at, lane, vnat);
+        if constexpr (kKLds) {  // the two waves of a key group write half of the fragments each, where the rows were
+          lds_barrier();
 #pragma unroll
-          for (int c = 0; c < NC / 2; ++c) {
-            const u32x4 x = key_valid ? *(const u32x4*)(kp + 16 * (2 * c + qs)) : u32x4{0, 0, 0, 0};
-            *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(kfoff + (2 * c + qs) * 1024) = x;
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < NC; ++c) knat[c].u = key_valid ? *(const u32x4*)(kp + 16 * c) : u32x4{0, 0, 0, 0};
+          for (int c = 0; c < NC / 2; ++c)
+            *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(kfoff + (2 * c + qs) * 1024) = qs ? knat[2 * c + 1].u : knat[2 * c].u;
         }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) vnat[c].u = key_valid ? *(const u32x4*)(vp + 16 * c) : u32x4{0, 0, 0, 0};
 #pragma unroll
         for (int c = 0; c < NC; ++c) vnat[c].u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
       }
@@ -1109,7 +1176,7 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < NC; ++i) {
-            const bf16x8 kb = kKLds ? rk[i % kPD].v : knat[kKLds ? 0 : i].v;
+            const bf16x8 kb = kKLds ? rk[i % kPD].v : knat[i].v;
             if (i == 0) s = mfma32_vgpr_first(rq[0].v, kb);
             else mfma32_vgpr(s, rq[i % kPD].v, kb);
             if (i + kPD < NC) {
@@ -1232,9 +1299,11 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
       };
       auto store = [&](const f32x16 (&acc)[NDB], uint16_t* out, int64_t st, int64_t sh, float* parts, float scale) {
         if (p.n_split == 1) {
-          uint16_t* row = out + (int64_t)my_key * st + (int64_t)kh * sh;
-#pragma unroll
-          for (int db = 0; db < NDB; ++db) store_block_bf16(row + 32 * db, acc[db], scale, hh, key_valid);
+          if (wave_active) {  // through what this wave alone has read
+            const uint32_t at = theirs - lane * 16;
+            RowStage<DQK>::put(at, lane, acc, scale);
+            RowStage<DQK>::copy_out(out + (int64_t)first_key * st + (int64_t)kh * sh, (uint32_t)st * 2, keys_left, at, lane);
+          }
         } else if (key_valid) {
           float* row = parts + (((int64_t)part * p.T + my_key) * p.Hkv + kh) * DQK + 4 * hh;
 #pragma unroll
@@ -1256,14 +1325,14 @@ __device__ __forceinline__ void dkdv8_items(const BwdParams& p, int block, int n
         store(dkt, p.dk, p.k_st, p.k_sh, p.dk_part, -p.scale);
       }
     }
-    prof_end(pa, p.prof, wave);
+    prof_end(pa, profiled, wave);
     if constexpr (DIRECT) break;
   }
-  prof_write(pa, p.prof, tid);
+  prof_write(pa, profiled, bwd_args<false>()->prof, tid);
 }
 template <int DQK, int DV>
-__global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdParams p) {
-  dkdv8_items<DQK, DV>(p, 0, (int)gridDim.x);
+__global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdParams) {
+  dkdv8_items<DQK, DV>(0, (int)gridDim.x);
 }
 
 // dK/dV and dQ in one launch, for packs of few rounds: neither needs the other, and with two launches the chip is partly
@@ -1274,7 +1343,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_dkdv8_kernel(const BwdPar
 // all of dQ.  Measured lines and gains: see one_launch().
 // Tried and dropped: dQ in pairs of heads in a launch of its own with queues (.86 to 1.02 of the present one's speed).
 template <int DQK, int DV, bool SHARED>
-__global__ __launch_bounds__(2 * kThreads, 2) void bwd_both_kernel(const BwdParams p, int n_dkdv, int n_dq, int n_resident,
+__global__ __launch_bounds__(2 * kThreads, 2) void bwd_both_kernel(const BwdParams, int n_dkdv, int n_dq, int n_resident,
                                                                    int interleave) {
   bool is_dkdv = (int)blockIdx.x < n_dkdv;
   int block = is_dkdv ? (int)blockIdx.x : (int)blockIdx.x - n_dkdv;
@@ -1286,8 +1355,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_both_kernel(const BwdPara
     block = (int)(kNumXcd * (is_dkdv ? in_front : k - in_front) + blockIdx.x % kNumXcd);
     if (block >= (is_dkdv ? n_dkdv : n_dq)) return;
   }
-  if (is_dkdv) dkdv8_items<DQK, DV, true>(p, block, n_resident);
-  else dq_items<DQK, DV, 2, SHARED>(p, block);
+  if (is_dkdv) dkdv8_items<DQK, DV, true>(block, n_resident);
+  else dq_items<DQK, DV, 2, SHARED>(block);
 }
 
 // dK, dV = sum over the parts of the partial sums of the key-tile kernel, in part order.  Workgroups (x, y):
@@ -1401,7 +1470,7 @@ __global__ __launch_bounds__(kThreads) void bwd_prepass_kernel(const BwdParams p
 
 template <int DQK, int DV>
 constexpr int dkdv8_lds() {
-  constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + (DQK > 64 ? 128 * DQK * 2 : 0) + 2 * 3 * 1024;
+  constexpr int tiles = 2 * 3 * 32 * (DQK * 2 + DV * 2) + 128 * DQK * 2 + 2 * 3 * 1024;
   constexpr int sums = 8 * DQK / 32 * 4096;
   return tiles > sums ? tiles : sums;
 }
@@ -1421,7 +1490,7 @@ static int launch_dkdv8(const BwdParams& p, int grid, hipStream_t s) {
 
 template <int DQK, int DV, bool SHARED>
 static int launch_both(BwdParams p, int n_resident, bool interleave, hipStream_t s) {
-  constexpr int lds_dq = (SHARED ? 2 : 4) * 64 * (DQK * 2 + DV * 2), lds_dkdv = dkdv8_lds<DQK, DV>();
+  constexpr int lds_dq = DqLds<DQK, DV, 2, SHARED>::BYTES, lds_dkdv = dkdv8_lds<DQK, DV>();
   constexpr int lds = lds_dq > lds_dkdv ? lds_dq : lds_dkdv;
   static bool attr_set = false;
   if (!attr_set) {
@@ -1441,7 +1510,8 @@ static int launch_both(BwdParams p, int n_resident, bool interleave, hipStream_t
 
 template <int DQK, int DV>
 static int launch_both4(const BwdParams& p, int n_resident, hipStream_t s) {
-  constexpr int lds = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);  // as dK/dV; dQ has no row sums there
+  constexpr int lds_dq = DqLds<DQK, DV, 1, false>::BYTES, lds_dkdv = DkdvLds<DQK, DV>::bytes();
+  constexpr int lds = lds_dq > lds_dkdv ? lds_dq : lds_dkdv;
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute((const void*)bwd_both4_kernel<DQK, DV>,
@@ -1456,8 +1526,7 @@ static int launch_both4(const BwdParams& p, int n_resident, hipStream_t s) {
 
 template <int DQK, int DV>
 static int launch_bwd_t(const BwdParams& p, int grid_dq, int grid_dkdv, hipStream_t s, hipEvent_t* ev) {
-  constexpr int lds_dq = 2 * 64 * (DQK * 2 + DV * 2);
-  constexpr int lds_dkdv = 2 * 64 * (DQK * 2 + DV * 2) + 4 * 64 * (int)sizeof(float);
+  constexpr int lds_dq = DqLds<DQK, DV, 1, false>::BYTES, lds_dkdv = DkdvLds<DQK, DV>::bytes();
   const BwdItems items{PackShape{DQK, p.T, p.n_samples, p.Hq, p.Hkv}, p.n_tiles, p.n_q_tiles, p.n_split};
   const BwdLaunch how = bwd_launch(items, p.prof || p.prof_dq || ev[0] || ev[2]);
   static bool attr_set = false;

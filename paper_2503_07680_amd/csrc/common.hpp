@@ -324,47 +324,77 @@ __device__ __forceinline__ void wait_async_loads() {
 // address path about 64 clocks a load instead of 16 (what counts is whether neighbouring lanes read the same line: 8 rows at
 // 128 bytes with neighbouring lanes in different rows gain nothing).  The same bytes read in whole rows, 8192 tokens, 32/8
 // heads of 128: from an item's identity to its first product 3.0 -> 1.9 us in the forward, 3.6 -> 2.0 in the dQ items of the
-// common launch.  The rows are swizzled like those of a tile.  Nobody else touches `lds`, so the wavefront waits for its
+// common launch.  Training step, us, the forward that way -> the backward too, with offsets of two instructions a copy: 1024
+// tokens, 4 heads of 64: 25.4 -> 24.2; 5497, 8 of 64: 69.3 -> 66.5; 8192, 32/8 of 128: 310 -> 300; 32768, 128 of 192:
+// 19750 -> 19500.  The rows are swizzled like those of a tile.  Nobody else touches `lds`, so the wavefront waits for its
 // copies and needs no barrier.
 template <int D>
 struct RowStage {
   static constexpr int RB = D * 2, BYTES = 32 * RB, N = BYTES / 1024;  // copies (or stores) of 1 KiB
-  // row and byte inside its row that LDS position i * 1024 + lane * 16 holds
-  static __device__ __forceinline__ void place(int i, int lane, int& row, int& byte) {
-    const int pos = i * 1024 + lane * 16;
-    row = pos / RB;
-    byte = swz<D>((pos % RB) / 16, row) * 16;
-  }
+  // LDS position i * 1024 + lane * 16 holds a chunk of row `row`, which a period of copies repeats so many rows further on,
+  // with its chunks' places moved by an exclusive or.
+  static constexpr int PERIOD = D == 192 ? 3 : 1, PERIOD_ROWS = PERIOD * 1024 / RB;
+  static constexpr int moved(int period) { return D == 128 ? (period & 3) * 16 : (period & 1) * 32; }
   // The lane again, opaque to the optimiser, for each of the functions below: their addresses are rebuilt for every item and
   // not held across its loops.
   static __device__ __forceinline__ int fresh(int lane) {
     asm volatile("" : "+v"(lane));
     return lane;
   }
-  // g: the first row (wave-uniform); rows >= rows_valid (at least 1) re-read the last valid one
-  static __device__ __forceinline__ void copy_in(const uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane) {
-    lane = fresh(lane);
+  // byte offset of that chunk in global memory: two instructions a copy
+  struct Places {
+    uint32_t row[PERIOD], byte[PERIOD], step;
+    __device__ __forceinline__ Places(int lane, uint32_t stride_bytes) : step(PERIOD_ROWS * stride_bytes) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      int row, byte;
-      place(i, lane, row, byte);
-      async_copy16(g, (uint32_t)min(row, rows_valid - 1) * stride_bytes + (uint32_t)byte, lds + i * 1024);
+      for (int b = 0; b < PERIOD; ++b) {
+        const int pos = b * 1024 + lane * 16, r = pos / RB;
+        row[b] = __umul24((uint32_t)r, stride_bytes);
+        byte[b] = swz<D>((pos % RB) / 16, r) * 16;
+      }
+    }
+    __device__ __forceinline__ uint32_t operator()(int i) const {
+      const int b = i % PERIOD, period = i / PERIOD;
+      return (byte[b] ^ (uint32_t)moved(period)) + (row[b] + (uint32_t)period * step);
+    }
+  };
+  // The rows' descriptor: g is the first one (wave-uniform); behind the first rows_valid (none: 0 or less) a copy writes zeros
+  // and a store nothing.
+  static __device__ __forceinline__ u32x4 desc(const uint16_t* g, uint32_t stride_bytes, int rows_valid) {
+    u32x4 d = buffer_desc(g, rows_span(rows_valid, 32, stride_bytes, RB));
+    // the compiler may have worked it out in vector registers, and does not see that the copies are memory instructions:
+    // these read a scalar register five wait states after a vector instruction wrote it at the earliest
+#pragma unroll
+    for (int i = 0; i < 3; ++i) d[i] = __builtin_amdgcn_readfirstlane(d[i]);
+    asm volatile("s_nop 4" : "+s"(d));
+    return d;
+  }
+  // PARTS: this wavefront's part of the rows only
+  template <int PARTS = 1>
+  static __device__ __forceinline__ void copy_in(const uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane, int part = 0) {
+    constexpr int MINE = N / PARTS;
+    static_assert(MINE % PERIOD == 0 && (PARTS == 1 || moved(MINE / PERIOD) == 0), "the parts' places are alike");
+    const u32x4 d = desc(g + (PARTS == 1 ? 0 : (int64_t)part * (32 / PARTS) * (stride_bytes / 2)), stride_bytes, rows_valid - part * (32 / PARTS));
+    const Places at(fresh(lane), stride_bytes);
+    const uint32_t to = lds + (PARTS == 1 ? 0 : part * MINE * 1024);
+    copies<0, MINE>(d, at, to);
+  }
+  template <int I, int TO>
+  static __device__ __forceinline__ void copies(const u32x4& d, const Places& at, uint32_t to) {
+    if constexpr (I < TO) {
+      buffer_copy16<I * 1024>(d, at(I), to);
+      copies<I + 1, TO>(d, at, to);
     }
   }
   // 16-byte chunk 2 * pair + lane / 32 of row lane % 32
   static __device__ __forceinline__ uint32_t at(uint32_t lds, int pair, int lane) {
     return lds + (lane & 31) * RB + swz<D>(2 * pair + (lane >> 5), lane & 31) * 16;
   }
-  // the D / 16 fragments of the rows as an MFMA operand: lane has row lane % 32, dims 16 c + 8 (lane / 32) .. + 7 in fragment
-  // c; zeros where the lane's row is not valid
+  // the D / 16 fragments of the rows as an MFMA operand: lane has row lane % 32, dims 16 c + 8 (lane / 32) .. + 7 in fragment c
   template <int NC>
-  static __device__ __forceinline__ void fragments(uint32_t lds, int lane, bool valid, Frag (&f)[NC]) {
+  static __device__ __forceinline__ void fragments(uint32_t lds, int lane, Frag (&f)[NC]) {
     lane = fresh(lane);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      f[c].u = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, c, lane);
-      if (!valid) f[c].u = u32x4{0, 0, 0, 0};
-    }
+    for (int c = 0; c < NC; ++c) f[c].u = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, c, lane);
   }
   // The other way: accumulator blocks of 32 dims (see store_block_bf16) into the rows, and the finished rows to global
   // memory, 1 KiB a store.
@@ -375,17 +405,21 @@ struct RowStage {
     for (int b = 0; b < 2 * NB; ++b)
       *(__attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, b, lane) = pack_block_half(acc[b / 2], scale, b % 2);
   }
-  static __device__ __forceinline__ void copy_out(uint16_t* g, int64_t stride, int rows_valid, uint32_t lds, int lane) {
+  static __device__ __forceinline__ void copy_out(uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane) {
     lane = fresh(lane);
+    const auto dst = __builtin_amdgcn_make_buffer_rsrc((void*)g, 0, (int)rows_span(rows_valid, 32, stride_bytes, RB), 0x00020000u);
+    const Places place(lane, stride_bytes);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      int row, byte;
-      place(i, lane, row, byte);
       const u32x4 x = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(lds + i * 1024 + lane * 16);
-      if (row < rows_valid) *(u32x4*)((char*)(g + row * stride) + byte) = x;
+      __builtin_amdgcn_raw_buffer_store_b128(x, dst, place(i), 0, 0);
     }
   }
 };
+// all of this wave's LDS reads have arrived
+__device__ __forceinline__ void wait_lds_reads() {
+  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+}
 // all but the last N of this wave's outstanding loads and copies have completed
 template <int N>
 __device__ __forceinline__ void wait_async_but() {

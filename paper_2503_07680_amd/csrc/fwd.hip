@@ -420,14 +420,14 @@ __device__ __forceinline__ void fwd_items() {
       // Q fragments (B operand of S^T = K Q^T): lane holds query l32, dims 16c+8hh..+7
       const uint32_t stage = Lds::stage(lds0, wave);
       int rows_left = r1 - (r0 + 32 * rw);
-      if (Lds::kStaged && wave_active)
+      if (Lds::kStaged)
         RowStage<DQK>::copy_in(p.q + (int64_t)(r0 + 32 * rw) * p.q_st + (int64_t)h * p.q_sh, (uint32_t)p.q_st * 2, rows_left, stage, lane);
       asm volatile("" : "+v"(rows_left));  // over the loops in a vector register: scalar ones are short there
       issue_k(0);
       issue_v(0);
       if constexpr (Lds::kStaged) {
         wait_async_but<decltype(k_loader)::PER_WAVE + decltype(v_loader)::PER_WAVE>();
-        RowStage<DQK>::fragments(stage, lane, row_valid, w.qf);
+        RowStage<DQK>::fragments(stage, lane, w.qf);
       } else {
         const uint16_t* qp = p.q + (int64_t)my_row * p.q_st + (int64_t)h * p.q_sh + 8 * hh;
 #pragma unroll
@@ -577,7 +577,7 @@ __device__ __forceinline__ void fwd_items() {
         const bool row_valid = l32 < rows_left;
         if constexpr (Lds::kOwn) {
           RowStage<DV>::put(stage, lane, w.oacc, inv);
-          RowStage<DV>::copy_out(p.o + (int64_t)__builtin_amdgcn_readfirstlane(my_row) * p.o_st + (int64_t)h * p.o_sh, p.o_st,
+          RowStage<DV>::copy_out(p.o + (int64_t)__builtin_amdgcn_readfirstlane(my_row) * p.o_st + (int64_t)h * p.o_sh, (uint32_t)p.o_st * 2,
                                  rows_left, stage, lane);
         } else {
           uint16_t* op = p.o + (int64_t)my_row * p.o_st + (int64_t)h * p.o_sh;
