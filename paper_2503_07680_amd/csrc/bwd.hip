@@ -115,7 +115,8 @@ __device__ __forceinline__ void dq_items(int block) {
   extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const int tid = threadIdx.x;
   const int wave_in_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave = HALVES == 1 ? wave_in_wg : wave_in_wg & 3, half = HALVES == 1 ? 0 : wave_in_wg >> 2;
+  const int half = HALVES == 1 ? 0 : wave_in_wg >> 2;
+  const int wave = (DQK > 64 ? mirrored(wave_in_wg) : wave_in_wg) & 3;  // its rows
   const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
   // a half's [K buf0][K buf1][V buf0][V buf1]
   char* const smem = smem_all + (SHARED ? 0 : half * (2 * K_TILE + 2 * V_TILE));
@@ -961,7 +962,7 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
   // (32 used of each 64: a copy by 64 lanes writes zeros behind its rows)
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave & 3, qs = wave >> 2;
+  const int qs = wave >> 2, share = DQK > 64 ? mirrored(wave) : wave, kg = share & 3;
   const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
 
   const uint32_t lds0 = lds_address(smem);
@@ -1278,7 +1279,7 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
 
       // The two waves of a pair: the upper rows' wave hands over its dK^T and finishes dV, the other the reverse.
       __syncthreads();  // the tile buffers are no longer read
-      const uint32_t mine = lds0 + wave * (NDB * 4096) + lane * 16, theirs = lds0 + (wave ^ 4) * (NDB * 4096) + lane * 16;
+      const uint32_t mine = lds0 + share * (NDB * 4096) + lane * 16, theirs = lds0 + (share ^ 4) * (NDB * 4096) + lane * 16;
       typedef __attribute__((address_space(3))) f32x4* lds_w4;
       auto send = [&](const f32x16 (&acc)[NDB]) {
 #pragma unroll

@@ -331,7 +331,7 @@ __device__ __forceinline__ void fwd_items() {
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rw = wave % (4 * TP);  // which 32 rows of the query tile
+  const int rw = (HP * TP == 2 ? mirrored(wave) : wave) % (4 * TP);  // which 32 rows of the query tile
   const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
 
   W w;
