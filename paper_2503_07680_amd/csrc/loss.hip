@@ -121,9 +121,9 @@ __global__ __launch_bounds__(kCeThreads) void ce_partition_kernel(const CeParams
 }
 
 // ---- what a workgroup of the main kernel works out for itself -----------------------------------
-// Every workgroup needs its range of rows and the weights of the samples in it, and both follow from which
+// Every workgroup needs its rows and the weights of their samples, and both follow from which
 // rows have a loss.  Up to kCePlanRows rows each workgroup reads all labels itself (from L2; 4 bytes a row
-// against the row's 2 V), keeps them as one bit a row with a running count per 64 rows, and finds its range
+// against the row's 2 V), keeps them as one bit a row with a running count per 64 rows, and finds its rows
 // and any sample's number of loss tokens in that.  The three kernels that did this before the main one
 // (count, weight, partition) each cost a launch: 22 us of 757 at T = 8192, V = 128256, and 12 us of 40 at
 // T = 1000, V = 32000.  They stay for longer packs, whose bits and counts would not fit beside the others'.
@@ -147,13 +147,29 @@ __device__ __forceinline__ int ce_live_before(const CeRows& c, int x, int T) {
 __device__ __forceinline__ int ce_sample_count(const CeRows& c, int a, int b, int T) {
   return max(ce_live_before(c, b, T) - ce_live_before(c, a, T), 0);
 }
-// Fills c, range[0..1] = this workgroup's rows (the cut of ce_partition_kernel: the first row whose preceding
-// rows cost at least k / n_ranges of the total) and slots[NW] = loss tokens in all samples.
-template <int NT>
+// Row number q (from 0) of those with a loss, or of those without.
+__device__ __forceinline__ int ce_nth_row(const CeRows& c, int n_words, int q, bool with_loss) {
+  auto in_front = [&](int w) { return with_loss ? c.before[w] : 64 * w - c.before[w]; };
+  int lo = 0, hi = n_words;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (in_front(mid) <= q) lo = mid;
+    else hi = mid;
+  }
+  const uint64_t bits = with_loss ? c.live[lo] : ~c.live[lo];
+  const int k = q - in_front(lo);
+  int i = 0;
+#pragma unroll
+  for (int step = 32; step >= 1; step >>= 1)
+    if (__popcll(bits & ((1ull << (i + step)) - 1)) <= k) i += step;
+  return 64 * lo + i;
+}
+// Fills c and slots[0] = loss tokens in all samples; RANGE: and range[0..1] = this workgroup's rows (the cut of
+// ce_partition_kernel: the first row whose preceding rows cost at least k / n_ranges of the total).
+template <int NT, bool RANGE>
 __device__ __forceinline__ void ce_plan_rows(const CeParams& p, const CeRows& c, int tid, int* range, int* slots) {
   constexpr int NW = NT / 64, kBatch = 4;
   const int wave = tid >> 6, lane = tid & 63, nw = ce_plan_words(p.T);
-  const bool with_grad = p.dlogits != nullptr;
   for (int w0 = wave; w0 < nw; w0 += NW * kBatch) {
     int lab[kBatch];
 #pragma unroll
@@ -189,11 +205,15 @@ __device__ __forceinline__ void ce_plan_rows(const CeParams& p, const CeRows& c,
     if (i < wave) base += slots[i];
     all += slots[i];
   }
-  const uint64_t row_c = (with_grad ? 8 : 0) + 1;  // row_cost(): 8 more for a row with a loss
+  const uint64_t row_c = (p.dlogits ? 8 : 0) + 1;  // row_cost(): 8 more for a row with a loss
   const uint64_t total = row_c * p.T + 8ull * all, n = gridDim.x;
   for (int w = w_begin; w < w_end; ++w) {
     c.before[w] = base;
     const uint64_t bits = c.live[w];
+    if (!RANGE) {
+      base += __popcll(bits);
+      continue;
+    }
     const uint64_t in_front = row_c * (64ull * w) + 8ull * base;
     base += __popcll(bits);
     const uint64_t behind = row_c * min(64 * (w + 1), p.T) + 8ull * base;
@@ -214,7 +234,7 @@ __device__ __forceinline__ void ce_plan_rows(const CeParams& p, const CeRows& c,
   if (tid == 0) {
     c.live[nw] = 0;
     c.before[nw] = all;
-    if (blockIdx.x == 0) range[0] = 0;
+    if (RANGE && blockIdx.x == 0) range[0] = 0;
   }
   __syncthreads();
   int in_samples = 0;
@@ -337,10 +357,27 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     sm = sm * __builtin_amdgcn_exp2f(__builtin_fmaf(finite_or_zero(mx), kLog2eF, -m2)) + a;
     mx = m_new;
   };
-  // Per-row scalars (label, weight, logit at the label) of the workgroup's next kRowBatch rows, staged
+  // The workgroup's rows.  With the gradient long rows are dealt in turn: of the rows with a loss every gridDim.x-th, and of
+  // those without as well, beginning with the workgroups that have one row with a loss less.  Those without come first: nothing
+  // is read for them, and the chip writes rows that lie next to each other, then reads and writes such rows.  (Consecutive
+  // rows a workgroup, cut by cost, lie all over the tensors, and a row without a loss between two with one leaves nothing to
+  // read behind its zeros.  Plain copies of 8192 rows of 128256: 5.13 TB/s that way, 5.28 in turn; zeros alone 5.70.)
+  // us, cut by cost -> in turn, T = 1000 to 8192, 0 to 70 % of the rows without a loss:
+  //   V = 4096 to 8192         .82 to 1.04        50304    1.01 to 1.13 (8192 rows, 30 %: 292 -> 272)
+  //       10240                .90 to 1.04        65536    1.00 to 1.16
+  //       12288               1.04 to 1.14        81928     .95 to 1.12
+  //       16384               1.04 to 1.20       128256    1.02 to 1.10; 8192 rows, 30 %: 738 -> 707, 707 -> 693 and 612 -> 646
+  //       16392                .96 to 1.11       151936    1.04 to 1.31; 8192 rows, 30 %: 886 -> 842, 763 -> 788
+  //       24576               1.05 to 1.12       (2.1 GB a tensor: with where in memory they lie)
+  //       32000               1.03 to 1.23
+  // Without the gradient consecutive rows, cut by cost, are as fast, and found sooner (300 of 128256: 14.9 against 16.0);
+  // packs too long for ce_plan_rows have them as well, by ce_partition_kernel, and so have streamed rows (not measured).
+  constexpr bool kDealt = WITH_GRAD && HOLD && NCH * kCeChunk > 10240;
+  //
+  // Per-row scalars (row, label, weight, logit at the label) of the workgroup's next kRowBatch rows, staged
   // in LDS by one thread per row.  Read from global memory inside the row loop they would have to be
   // waited for with every outstanding store and load of the chunk pipeline (the counter is in order).
-  __shared__ int row_label[kRowBatch];
+  __shared__ int row_index[kRowBatch], row_label[kRowBatch];
   __shared__ float row_weight[kRowBatch], row_zlabel[kRowBatch];
   extern __shared__ uint64_t plan_lds[];
   __shared__ int plan_range[2], plan_slots[NW];
@@ -348,43 +385,62 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   rows.live = plan_lds;
   rows.before = (int32_t*)(plan_lds + ce_plan_words(p.T) + 1);
   rows.cu = p.n_samples <= kCePlanCu ? rows.before + ce_plan_words(p.T) + 1 : nullptr;
-  if (!p.row_start) ce_plan_rows<NT>(p, rows, tid, plan_range, plan_slots);
-  // The range is the same in every thread and goes into scalar registers.  Chosen by ?: it came from a load through
+  if (!p.row_start) ce_plan_rows<NT, !kDealt>(p, rows, tid, plan_range, plan_slots);
+  // n rows, consecutive from `first`; or dealt: the first n_dead of them without a loss.  The same in every thread and in
+  // scalar registers.  Chosen by ?: it came from a load through
   // one pointer to either memory, whose result counts as different in every thread: a loop over rows by exec masks
   // and up to 10 more vector registers, of which the longest rows have none (20 chunks: a spill in the loop, whose
   // reload waits for the gradient stores; T = 8192, V = 160000: 933 -> 929 us).
-  int r, row_end;
+  const bool dealt = kDealt && !p.row_start && (int)gridDim.x < p.T;
+  int n, first, n_dead = 0, first_dead = 0;  // dealt: numbers of the first row of either kind among the rows of that kind
   if (p.row_start) {
-    r = p.row_start[blockIdx.x];
-    row_end = p.row_start[blockIdx.x + 1];
+    first = p.row_start[blockIdx.x];
+    n = p.row_start[blockIdx.x + 1] - first;
+  } else if (dealt) {
+    const int G = gridDim.x, all_live = __builtin_amdgcn_readfirstlane(rows.before[ce_plan_words(p.T)]), all_dead = p.T - all_live;
+    auto times = [G](int x) {  // x / G for x up to kCePlanRows: a division is 35 instructions
+      const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)G)), rest = x - q * G;
+      return __builtin_amdgcn_readfirstlane(q + (rest >= G) - (rest < 0));
+    };
+    const int live = times(all_live), more_live = all_live - live * G, dead = times(all_dead), more_dead = all_dead - dead * G;
+    first = blockIdx.x;
+    first_dead = first - more_live + (first < more_live ? G : 0);
+    n_dead = dead + (first_dead < more_dead);
+    n = n_dead + live + (first < more_live);
+  } else if constexpr (kDealt) {  // a workgroup a row
+    first = blockIdx.x;
+    n = 1;
   } else {
-    r = __builtin_amdgcn_readfirstlane(plan_range[0]);
-    row_end = __builtin_amdgcn_readfirstlane(plan_range[1]);
+    first = __builtin_amdgcn_readfirstlane(plan_range[0]);
+    n = __builtin_amdgcn_readfirstlane(plan_range[1]) - first;
   }
-  auto stage_rows = [&](int first_row) {  // rows first_row + i, i < kRowBatch
-    __syncthreads();                       // the entries of the batch before have all been read
+  auto stage_rows = [&](int i0) {  // entries i0 + i, i < kRowBatch
+    __syncthreads();                // the entries of the batch before have all been read
     if (tid < kRowBatch) {
-      const int64_t rr = (int64_t)first_row + tid;
-      int lab = -1;
+      const int i = i0 + tid;
+      int row = first + i, lab = -1;
       float wt = 0.f, zl = 0.f;
-      if (rr < row_end) {
-        lab = p.labels[rr];
+      if (i < n) {
+        if (dealt)
+          row = ce_nth_row(rows, ce_plan_words(p.T), i < n_dead ? first_dead + i * (int)gridDim.x : first + (i - n_dead) * (int)gridDim.x, i >= n_dead);
+        if (!dealt || i >= n_dead) lab = p.labels[row];
         if (has_loss(lab)) {
-          wt = p.row_start ? p.weighted[rr]  // the row's weight, put there by ce_weight_kernel
-                           : ce_row_weight(p, rows, (int)rr, plan_slots[0]);
-          zl = __uint_as_float((uint32_t)p.logits[rr * p.stride_t + lab] << 16);
+          wt = p.row_start ? p.weighted[row]  // the row's weight, put there by ce_weight_kernel
+                           : ce_row_weight(p, rows, row, plan_slots[0]);
+          zl = __uint_as_float((uint32_t)p.logits[(int64_t)row * p.stride_t + lab] << 16);
         } else {
           lab = -1;
-          if (HOLD && !WITH_GRAD) p.token_loss[rr] = p.weighted[rr] = 0.f;
+          if (HOLD && !WITH_GRAD) p.token_loss[row] = p.weighted[row] = 0.f;
         }
       }
+      row_index[tid] = row;
       row_label[tid] = lab;
       row_weight[tid] = wt;
       row_zlabel[tid] = zl;
     }
     __syncthreads();
   };
-  if (r >= row_end) return;
+  if (n <= 0) return;
   // log2-sum-exp2 of a row from every thread's statistics; one barrier.  parity: which set of the slots
   auto row_lse2 = [&](int parity) {
     const float m_wave = wave_max(mx);
@@ -417,20 +473,20 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
       const auto src = __builtin_amdgcn_make_buffer_rsrc((void*)(p.logits + (int64_t)row * p.stride_t), 0, 2 * p.V, 0x00020000);
       return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, fresh(byte_in_chunk), c * 2 * kCeChunk, 2 /* nt */));
     };
-    for (int base = r, parity = 0; base < row_end; base += kRowBatch) {
-      stage_rows(base);
-      const int n = min(row_end - base, kRowBatch);
-      auto next_live = [&](int i) {  // the first row from i on with a loss; n: none
-        while (i < n && row_label[i] < 0) ++i;
+    for (int i0 = 0, parity = 0; i0 < n; i0 += kRowBatch) {
+      stage_rows(i0);
+      const int base = first + i0, count = min(n - i0, kRowBatch);
+      auto next_live = [&](int i) {  // the first row from i on with a loss; count: none
+        while (i < count && row_label[i] < 0) ++i;
         return __builtin_amdgcn_readfirstlane(i);
       };
       int i = next_live(0);
-      if (i == n) continue;
+      if (i == count) continue;
 #pragma unroll
       for (int c = 0; c < NCH; ++c) held[c] = load_in_row(base + i, c);
-      while (i < n) {
+      while (i < count) {
         const int i_next = next_live(i + 1);
-        if (i_next < n) {
+        if (i_next < count) {
 #pragma unroll
           for (int c = 0; c < NCH; ++c) {
             add_to_stats(entries(held[c], c));
@@ -459,7 +515,8 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     }
     return;
   }
-  stage_rows(r);
+  stage_rows(0);
+  int r = __builtin_amdgcn_readfirstlane(row_index[0]);
   int label = row_label[0];  // -1: no loss
   float w = row_weight[0], z_label = row_zlabel[0];
   if (HOLD && label >= 0) {
@@ -471,10 +528,10 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
       __builtin_amdgcn_sched_barrier(0);  // one chunk at a time: bounds the temporaries
     }
   }
-  for (int parity = 0, i_next = 1; r < row_end; ++i_next) {
-    const int r_next = r + 1;
-    if (i_next % kRowBatch == 0 && r_next < row_end) stage_rows(r_next);
-    const int label_next = r_next < row_end ? row_label[i_next % kRowBatch] : -1;
+  for (int parity = 0, i_next = 1; i_next <= n; ++i_next) {
+    if (i_next % kRowBatch == 0 && i_next < n) stage_rows(i_next);
+    const int r_next = __builtin_amdgcn_readfirstlane(row_index[i_next % kRowBatch]);
+    const int label_next = i_next < n ? row_label[i_next % kRowBatch] : -1;
     const float w_next = row_weight[i_next % kRowBatch], z_label_next = row_zlabel[i_next % kRowBatch];
     const bool fetch_next = HOLD && label_next >= 0;
     const bool live = label >= 0;  // a row without a loss: zero loss, zero gradient, no arithmetic
