@@ -161,7 +161,7 @@ __device__ __forceinline__ void dq_items(int block) {
   int q_cur = xcc_id_reg() & (kNumXcd - 1), q_tried = 0;
   for (;;) {
     const BwdArgs& p = *bwd_args<!DIRECT>();
-    const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, p.g / (SHARED ? 2 : 1) / p.n_split_dq};
+    const WorkQueues wq{p.counter_dq, p.n_q_tiles, p.Hkv * p.n_split_dq, quotient(p.g / (SHARED ? 2 : 1), p.n_split_dq)};
     int tile_idx, h;
     if constexpr (!DIRECT) {
       if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, h)) break;
@@ -185,7 +185,7 @@ __device__ __forceinline__ void dq_items(int block) {
       const bool has_head = HALVES == 1 || SHARED || h < p.Hq;  // an odd number of heads: the last pair has one
       if (!has_head) h = p.Hq - 1;
       if (HALVES == 2) h = __builtin_amdgcn_readfirstlane(h);
-      const int kh = h / p.g;
+      const int kh = quotient(h, p.g);
       const int qw0 = r0 - s0 + 32 * wave;
       const int my_row = r0 + 32 * wave + l32;
       const bool row_valid = has_head && my_row < r1;
@@ -516,7 +516,7 @@ __device__ __forceinline__ void dkdv_items(int block, int n_resident) {
   for (;;) {
     const BwdArgs& p = *bwd_args<!DIRECT>();
     const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
-    const int g_item = p.g / p.n_split;
+    const int g_item = quotient(p.g, p.n_split);
     int tile_idx, vh;
     if constexpr (DIRECT) {
       const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
@@ -525,7 +525,7 @@ __device__ __forceinline__ void dkdv_items(int block, int n_resident) {
     } else {
       if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
     }
-    const int kh = vh / p.n_split, part = vh - kh * p.n_split;
+    const int kh = quotient(vh, p.n_split), part = vh - kh * p.n_split;
     const int head0 = vh * g_item;  // first query head of the item
     prof_begin(pa, profiled, tid);
 
@@ -562,8 +562,9 @@ __device__ __forceinline__ void dkdv_items(int block, int n_resident) {
       // the end; that set of w tiles ends together, the next one starts together, and so on in turns.  The
       // order is a function of the tile number alone, so the results do not depend on timing.
       // (With fewer than 8 workgroups per kv head there is little to share and the plain order is kept.)
-      const int w_share = n_resident / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);  // heads in work at a time
-      int skip = w_share >= 8 && ((tl.tile / w_share) & 1) ? (tl.tile % w_share) * (BN / BQ) : 0;
+      const int w_share = quotient(n_resident, min(p.Hkv * p.n_split, kNumXcd * kHeadGroup));  // heads in work at a time
+      const int set = quotient(tl.tile, max(w_share, 1));
+      int skip = w_share >= 8 && (set & 1) ? (tl.tile - set * w_share) * (BN / BQ) : 0;
       skip = max(0, min(skip, nqb - 1));
       const int first_blk = nqb - 1 - skip;
       // the blocks are taken in the order first_blk .. 0, then nqb-1 .. first_blk+1, g steps each
@@ -1001,7 +1002,7 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
   for (;;) {
     const BwdArgs& p = *bwd_args<!DIRECT>();
     const WorkQueues wq{p.counter, p.n_tiles, p.Hkv * p.n_split, 1};
-    const int g_item = p.g / p.n_split;
+    const int g_item = quotient(p.g, p.n_split);
     int tile_idx, vh;
     if constexpr (DIRECT) {
       const Taken tk = direct_item_inline(wq.n_tiles, wq.Hkv, 1, 0, 0, block);
@@ -1010,7 +1011,7 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
     } else {
       if (!next_item(wq, (int*)smem, tid, q_cur, q_tried, tile_idx, vh)) break;
     }
-    const int kh = vh / p.n_split, part = vh - kh * p.n_split;
+    const int kh = quotient(vh, p.n_split), part = vh - kh * p.n_split;
     const int head0 = vh * g_item;
     prof_begin(pa, profiled, wave);
 
@@ -1032,8 +1033,9 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
       const int qb_start = (k0_in / BQ) * BQ;
       const int nqb = (s_len - qb_start + BQ - 1) / BQ;
       const int n_steps = nqb * g_item;
-      const int w_share = n_resident / min(p.Hkv * p.n_split, kNumXcd * kHeadGroup);
-      int skip = w_share >= 8 && ((tl.tile / w_share) & 1) ? (tl.tile % w_share) * (BN / BQ) : 0;
+      const int w_share = quotient(n_resident, min(p.Hkv * p.n_split, kNumXcd * kHeadGroup));
+      const int set = quotient(tl.tile, max(w_share, 1));
+      int skip = w_share >= 8 && (set & 1) ? (tl.tile - set * w_share) * (BN / BQ) : 0;
       skip = max(0, min(skip, nqb - 1));
       // Step order as in the four-wave kernel.  The copies of a step's operands run two steps ahead, one by one behind the
       // updates: their address path takes 16 clocks of the compute unit a copy, and a burst of them holds the waves.  State of the copying side: the block and head of the next
@@ -1351,8 +1353,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void bwd_both_kernel(const BwdPara
   if (interleave) {  // of the first k groups of eight, ceil(k groups_dkdv / groups) are dK/dV
     const uint32_t groups_dkdv = (uint32_t)(n_dkdv + kNumXcd - 1) / kNumXcd;
     const uint32_t groups = groups_dkdv + (uint32_t)(n_dq + kNumXcd - 1) / kNumXcd, k = blockIdx.x / kNumXcd;
-    const uint32_t in_front = (k * groups_dkdv + groups - 1) / groups;
-    is_dkdv = ((k + 1) * groups_dkdv + groups - 1) / groups > in_front;
+    const uint32_t in_front = quotient(k * groups_dkdv + groups - 1, groups);
+    is_dkdv = quotient((k + 1) * groups_dkdv + groups - 1, groups) > (int)in_front;
     block = (int)(kNumXcd * (is_dkdv ? in_front : k - in_front) + blockIdx.x % kNumXcd);
     if (block >= (is_dkdv ? n_dkdv : n_dq)) return;
   }

@@ -515,20 +515,30 @@ struct Taken {
   int q_cur, q_tried;
 };
 
-// Item j of queue `queue`, which has nk kv heads.
+// x / d for 0 <= x < 2^22, d >= 1: the quotient in 32-bit floats is at most one off.  Ten instructions; an integer division
+// is 35, and an item of the backward had up to ten of them in front of its first load.  Training step, us: 1024 tokens, 4 heads
+// of 64: 24.16 -> 23.96; 5497, 8 of 64: 67.4 -> 67.2; eight drawn packs: .4 % faster in the mean.
+__device__ __forceinline__ int quotient(int x, int d) {
+  const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)d)), rest = x - q * d;
+  return __builtin_amdgcn_readfirstlane(q + (rest >= d) - (rest < 0));
+}
+
+// Item j of queue `queue`, which has nk kv heads.  SMALL: no more than 2^22 items, of the same number in all threads.
+template <bool SMALL>
 __device__ __forceinline__ void queue_item(int j, int queue, int nk, int n_tiles, int per_kv, int& tile_idx, int& head) {
+  auto div = [](int x, int d) { return SMALL ? quotient(x, d) : x / d; };
   const int per_group = n_tiles * kHeadGroup * per_kv;  // items of a full group of heads
   const int full = nk / kHeadGroup;
-  int grp = j / per_group, jj = j - grp * per_group, size = kHeadGroup;
+  int grp = div(j, per_group), jj = j - grp * per_group, size = kHeadGroup;
   if (grp >= full) {  // the last, smaller group
     grp = full;
     jj = j - full * per_group;
     size = nk - full * kHeadGroup;
   }
   const int per_tile = size * per_kv;
-  const int rem = jj % per_tile;
-  tile_idx = jj / per_tile;
-  head = (queue + kNumXcd * (grp * kHeadGroup + rem / per_kv)) * per_kv + rem % per_kv;
+  tile_idx = div(jj, per_tile);
+  const int rem = jj - tile_idx * per_tile, kv = div(rem, per_kv);
+  head = (queue + kNumXcd * (grp * kHeadGroup + kv)) * per_kv + rem - kv * per_kv;
 }
 
 // One thread takes the next item of the queues.  q_cur / q_tried: that thread's cursor over them.
@@ -543,7 +553,7 @@ __device__ __forceinline__ Taken queued_item_inline(int32_t* counters, int n_til
       const int j = atomicAdd(counters + q_cur * kCounterStride, 1);
       if (j < len) {
         Taken t{0, 0, q_cur, q_tried};
-        queue_item(j, q_cur, nk, n_tiles, per_kv, t.tile_idx, t.head);
+        queue_item<false>(j, q_cur, nk, n_tiles, per_kv, t.tile_idx, t.head);
         return t;
       }
     }
@@ -552,15 +562,16 @@ __device__ __forceinline__ Taken queued_item_inline(int32_t* counters, int n_til
   }
   return Taken{-1, 0, q_cur, q_tried};
 }
-// The one item of workgroup `block` in a launch without queues; workgroups are dealt to the dies in turn.
+// The one item of workgroup `block` in a launch without queues (few rounds: less than 2^22 items); workgroups are dealt to
+// the dies in turn.
 __device__ __forceinline__ Taken direct_item_inline(int n_tiles, int Hkv, int per_kv, int q_cur, int q_tried, int block) {
   Taken t{-1, 0, q_cur, kNumXcd};
   if (q_tried == 0) {
     if (Hkv % kNumXcd == 0) {
-      queue_item(block / kNumXcd, block % kNumXcd, Hkv / kNumXcd, n_tiles, per_kv, t.tile_idx, t.head);
+      queue_item<true>(block / kNumXcd, block % kNumXcd, Hkv / kNumXcd, n_tiles, per_kv, t.tile_idx, t.head);
     } else {
-      t.tile_idx = block / (Hkv * per_kv);
-      t.head = block % (Hkv * per_kv);
+      t.tile_idx = quotient(block, Hkv * per_kv);
+      t.head = block - t.tile_idx * (Hkv * per_kv);
     }
   }
   return t;
