@@ -358,11 +358,13 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     mx = m_new;
   };
   // The workgroup's rows.  With the gradient long rows are dealt in turn: of the rows with a loss every gridDim.x-th, and of
-  // those without as well, beginning with the workgroups that have one row with a loss less.  Those without come first: nothing
-  // is read for them, and the chip writes rows that lie next to each other, then reads and writes such rows.  (Consecutive
+  // those without as well, beginning with the workgroups that have one row with a loss less.  The zeros of the latter are written
+  // a share at a time in front of every other row's reduction, when nothing else is under way.  (Consecutive
   // rows a workgroup, cut by cost, lie all over the tensors, and a row without a loss between two with one leaves nothing to
   // read behind its zeros.  Plain copies of 8192 rows of 128256: 5.13 TB/s that way, 5.28 in turn; zeros alone 5.70.)
-  // us, cut by cost -> in turn, T = 1000 to 8192, 0 to 70 % of the rows without a loss:
+  // All zeros in front of the first row with a loss -> a share at a time, 30 % of the rows without, us: 8192 rows of 128256: 708
+  // -> 693; 4096: 363 -> 352; 2048: 187 -> 180; 1000 of 32000: 26.8 -> 26.6; 300 of 65536: 21.1 -> 18.6.  The first of these
+  // against rows cut by cost, us, T = 1000 to 8192, 0 to 70 % of the rows without a loss:
   //   V = 4096 to 8192         .82 to 1.04        50304    1.01 to 1.13 (8192 rows, 30 %: 292 -> 272)
   //       10240                .90 to 1.04        65536    1.00 to 1.16
   //       12288               1.04 to 1.14        81928     .95 to 1.12
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   rows.before = (int32_t*)(plan_lds + ce_plan_words(p.T) + 1);
   rows.cu = p.n_samples <= kCePlanCu ? rows.before + ce_plan_words(p.T) + 1 : nullptr;
   if (!p.row_start) ce_plan_rows<NT, !kDealt>(p, rows, tid, plan_range, plan_slots);
-  // n rows, consecutive from `first`; or dealt: the first n_dead of them without a loss.  The same in every thread and in
+  // n rows, consecutive from `first`; or dealt: n with a loss and n_dead without.  The same in every thread and in
   // scalar registers.  Chosen by ?: it came from a load through
   // one pointer to either memory, whose result counts as different in every thread: a loop over rows by exec masks
   // and up to 10 more vector registers, of which the longest rows have none (20 chunks: a spill in the loop, whose
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     first = blockIdx.x;
     first_dead = first - more_live + (first < more_live ? G : 0);
     n_dead = dead + (first_dead < more_dead);
-    n = n_dead + live + (first < more_live);
+    n = live + (first < more_live);
   } else if constexpr (kDealt) {  // a workgroup a row
     first = blockIdx.x;
     n = 1;
@@ -421,9 +423,8 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
       int row = first + i, lab = -1;
       float wt = 0.f, zl = 0.f;
       if (i < n) {
-        if (dealt)
-          row = ce_nth_row(rows, ce_plan_words(p.T), i < n_dead ? first_dead + i * (int)gridDim.x : first + (i - n_dead) * (int)gridDim.x, i >= n_dead);
-        if (!dealt || i >= n_dead) lab = p.labels[row];
+        if (dealt) row = ce_nth_row(rows, ce_plan_words(p.T), first + i * (int)gridDim.x, true);
+        lab = p.labels[row];
         if (has_loss(lab)) {
           wt = p.row_start ? p.weighted[row]  // the row's weight, put there by ce_weight_kernel
                            : ce_row_weight(p, rows, row, plan_slots[0]);
@@ -440,6 +441,42 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     }
     __syncthreads();
   };
+  // Dealt rows without a loss: their numbers, kRowBatch at a time, and their zeros, so many chunks at a time.
+  __shared__ int dead_index[kDealt ? kRowBatch : 1];
+  auto stage_dead = [&](int i0) {
+    if (tid < kRowBatch && i0 + tid < n_dead) {
+      const int row = ce_nth_row(rows, ce_plan_words(p.T), first_dead + (i0 + tid) * (int)gridDim.x, false);
+      dead_index[tid] = row;
+      p.token_loss[row] = p.weighted[row] = 0.f;
+    }
+    __syncthreads();
+  };
+  int zero_row = 0, zero_chunk = 0, zero_rows = 0;  // the next one to write, and how many rows there are
+  auto write_zeros = [&](int chunks) {
+    for (; chunks > 0 && zero_row < zero_rows; --chunks) {
+      uint16_t* row = p.dlogits + (int64_t)__builtin_amdgcn_readfirstlane(dead_index[zero_row]) * p.V;
+      if (zero_chunk < NCH - 1 || tail_valid) __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, chunk_ptr(row, zero_chunk));
+      if (++zero_chunk == NCH) {
+        zero_chunk = 0;
+        ++zero_row;
+      }
+    }
+  };
+  int zeros_a_row = 0;  // chunks of zeros beside every row with a loss
+  if constexpr (kDealt) {
+    if (dealt) {
+      for (int i0 = (n_dead - 1) / kRowBatch * kRowBatch; i0 >= 0 && n_dead > 0; i0 -= kRowBatch) {
+        stage_dead(i0);
+        zero_row = zero_chunk = 0;
+        zero_rows = min(n_dead - i0, kRowBatch);
+        if (i0 > 0 || n <= 0) {
+          write_zeros(kRowBatch * NCH);
+          __syncthreads();
+        }
+      }
+      zeros_a_row = n > 0 ? (zero_rows * NCH + n - 1) / n : 0;
+    }
+  }
   if (n <= 0) return;
   // log2-sum-exp2 of a row from every thread's statistics; one barrier.  parity: which set of the slots
   auto row_lse2 = [&](int parity) {
@@ -522,6 +559,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   if (HOLD && label >= 0) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) held[c] = load_chunk(p.logits + (int64_t)r * p.stride_t, c);
+    if constexpr (kDealt) write_zeros(zeros_a_row);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       add_to_stats(entries(held[c], c));
@@ -542,6 +580,9 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     if (live) {
       if (!HOLD) {
         for (int c = 0; c < my_chunks; ++c) add_to_stats(*chunk_ptr(row, c));
+      }
+      if constexpr (kDealt) {
+        if (i_next > 1) write_zeros(zeros_a_row);
       }
       const float lse2 = row_lse2(parity);
       const float ce = lse2 * kLn2F - z_label;
