@@ -937,11 +937,11 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_both4_kernel(const BwdParams,
 // of 64: 49.3 -> 42.5; 1024 tokens, 4 heads of 64: 14.8 -> 13.5.
 // The exchange at the end costs an item 1.9 us: see eight_waves() for where the line lies.
 //
-// At head size 128 it spills 7 vector and 37 scalar registers: 32 bytes of scratch a lane, none of it touched between the
+// At head size 128 it spills 5 vector and 35 scalar registers: 32 bytes of scratch a lane, none of it touched between the
 // first and the last MFMA, and two reads of a spilled scalar in three steps.
 //
-// K and V come in whole rows through LDS and dK and dV go out that way (RowStage).  Read a row a lane, 12 loads of 8
-// wavefronts hold the address path about 2.5 us of an item; the stores of a row a lane about as long.
+// K and V come in whole rows through LDS and dK and dV go out that way (RowStage).  A row a lane, the 12 loads of eight
+// wavefronts hold the address path 64 clocks each, 6144 of an item, and their 8 stores 4096; in whole rows a quarter of it.
 //
 // Tried here and slower or the same: V in LDS too (the LDS pipe, busy in half the clocks, costs power: +2 %); the two
 // groups half a step apart (+2 %); s_setprio around the MFMA chains; copies with a wait of their own in mid-step.
