@@ -127,18 +127,12 @@ __global__ __launch_bounds__(kCeThreads) void ce_partition_kernel(const CeParams
 // and any sample's number of loss tokens in that.  The three kernels that did this before the main one
 // (count, weight, partition) each cost a launch: 22 us of 757 at T = 8192, V = 128256, and 12 us of 40 at
 // T = 1000, V = 32000.  They stay for longer packs, whose bits and counts would not fit beside the others'.
-constexpr int kCePlanRows = 1 << 17;
-constexpr int kCePlanCu = 1024;  // samples whose bounds are kept in LDS too
 
 struct CeRows {
   uint64_t* live;  // bit i of word w: row 64 w + i has a loss; one word of zeros behind the last
   int32_t* before; // loss rows in front of word w; one entry behind the last
   int32_t* cu;     // bounds of the samples, null: too many, read them from global memory
 };
-__host__ __device__ inline int ce_plan_words(int T) { return (T + 63) / 64; }
-inline int ce_plan_lds(int T, int n) {
-  return (ce_plan_words(T) + 1) * (int)(sizeof(uint64_t) + sizeof(int32_t)) + (n <= kCePlanCu ? (n + 1) * (int)sizeof(int32_t) : 0);
-}
 // loss rows in front of row x; x is clamped to the pack (a malformed list of samples stays in bounds)
 __device__ __forceinline__ int ce_live_before(const CeRows& c, int x, int T) {
   x = min(max(x, 0), T);
@@ -293,7 +287,7 @@ __device__ __forceinline__ float ce_row_weight(const CeParams& p, const CeRows& 
 #define HBP_CE_LAG 2
 #endif
 constexpr int kLag = HBP_CE_LAG;
-constexpr int kRowBatch = 256;  // rows whose scalars are staged in LDS at a time
+constexpr int kRowBatch = kCeRowBatch;
 
 // NT threads, by the length of a row (see launch_packed_ce).
 template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
@@ -380,7 +374,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   //       32000               1.03 to 1.23
   // Without the gradient consecutive rows, cut by cost, are as fast, and found sooner (300 of 128256: 14.9 against 16.0);
   // packs too long for ce_plan_rows have them as well, by ce_partition_kernel, and so have streamed rows (not measured).
-  constexpr bool kDealt = WITH_GRAD && HOLD && NCH * kCeChunk > 10240;
+  constexpr bool kDealt = ce_dealt(NT, NCH, HOLD, WITH_GRAD);
   //
   // Per-row scalars (row, label, weight, logit at the label) of the workgroup's next kRowBatch rows, staged
   // in LDS by one thread per row.  Read from global memory inside the row loop they would have to be
@@ -670,17 +664,14 @@ __global__ __launch_bounds__(kCeThreads) void ce_reduce_kernel(const CeParams p)
 // Workgroups resident at once per compute unit.  The main kernel's grid is that times the compute
 // units: a persistent loop over rows; a second batch of workgroups would start with an empty pipeline.
 template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
-static int main_per_cu(int lds) {
-  static int per_cu = 0;  // without the planning's LDS; same on every device of this part
-  if (per_cu == 0) {
+static int main_per_cu(int plan_lds) {
+  static int by_registers = 0;  // without the planning's LDS; same on every device of this part
+  if (by_registers == 0) {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ce_main_kernel<NT, NCH, HOLD, WITH_GRAD>, NT, 0) != hipSuccess || n < 1) n = 1;
-    constexpr int kMost = ce_most_per_cu(NT, NCH, HOLD, WITH_GRAD);
-    per_cu = n < kMost ? n : kMost;
+    by_registers = n;
   }
-  constexpr int kLds = 160 * 1024, kStatic = 4 * 1024;  // LDS of a compute unit; the kernel's own arrays
-  const int by_lds = kLds / (lds + kStatic);
-  return per_cu < by_lds ? per_cu : by_lds;
+  return ce_per_cu(by_registers, NT, NCH, HOLD, WITH_GRAD, plan_lds);
 }
 template <int NT, int NCH, bool HOLD, bool WITH_GRAD>
 static void launch_main_g(CeParams p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {

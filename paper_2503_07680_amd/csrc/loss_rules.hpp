@@ -1,7 +1,25 @@
-// Launch shape of the packed cross-entropy: a plain host function, without HIP, so that a test without a GPU can ask it.
+// Launch shape of the packed cross-entropy: plain host functions, without HIP, so that a test without a GPU can ask them.
 #pragma once
+#include <stdint.h>
 
 namespace hbp {
+
+// Packs of up to kCePlanRows rows are planned in the main kernel, in LDS: one bit a row, a running count a word of 64 rows,
+// and the bounds of up to kCePlanCu samples.
+constexpr int kCePlanRows = 1 << 17;
+constexpr int kCePlanCu = 1024;
+constexpr int ce_plan_words(int T) { return (T + 63) / 64; }
+constexpr int ce_plan_lds(int T, int n_samples) {
+  return (ce_plan_words(T) + 1) * (int)(sizeof(uint64_t) + sizeof(int32_t)) + (n_samples <= kCePlanCu ? (n_samples + 1) * (int)sizeof(int32_t) : 0);
+}
+constexpr int kCeRowBatch = 256;  // rows whose scalars are staged in LDS at a time
+
+// Whether rows are dealt in turn to the workgroups (see ce_main_kernel, with what was measured).
+constexpr bool ce_dealt(int nt, int nch, bool hold, bool with_grad) { return with_grad && hold && nch * nt * 8 > 10240; }
+
+// The most LDS that the main kernel's own arrays take: statistics of the wavefronts, two sets, and the counts of the
+// planning; the rows' scalars; its range of rows.
+constexpr int ce_own_lds(int nt, bool dealt) { return 5 * 4 * (nt / 64) + (dealt ? 5 : 4) * 4 * kCeRowBatch + 16; }
 
 // The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
 // the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
@@ -24,6 +42,17 @@ constexpr int ce_most_per_cu(int nt, int nch, bool hold, bool with_grad) {
   if (nt == 256) return nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
   if (nt == 512) return nch <= 5 ? 4 : nch <= 7 ? 3 : 2;
   return 2;
+}
+// Workgroups a compute unit holds at once; the main kernel's grid is that times the compute units.  One more would have
+// its rows to itself, after the others: with the kernel's own arrays taken as 4 KiB and no pieces, a round of 256 workgroups
+// on its own, us, that -> what fits: T = 98000, V = 10248: 856 -> 804; 100000, 14336: 1055 -> 1030; 120000, 16384: 1443 -> 1388.
+constexpr int ce_per_cu(int by_registers, int nt, int nch, bool hold, bool with_grad, int plan_lds) {
+  constexpr int kLds = 160 * 1024, kPiece = 1280;  // of a compute unit; the unit it is handed out in
+  const int own = ce_own_lds(nt, ce_dealt(nt, nch, hold, with_grad));
+  const int by_lds = kLds / ((plan_lds + own + kPiece - 1) / kPiece * kPiece);
+  const int most = ce_most_per_cu(nt, nch, hold, with_grad);
+  const int n = by_registers < most ? by_registers : most;
+  return n < by_lds ? n : by_lds;
 }
 
 }  // namespace hbp

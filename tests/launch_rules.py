@@ -50,3 +50,13 @@ def backward(lengths, Hq, Hkv, d, records=False):
 def cross_entropy_per_cu(threads, chunks, hold, with_grad):
     """The most workgroups a compute unit gets."""
     return _load().ce_per_cu(threads, chunks, int(hold), int(with_grad))
+
+
+def cross_entropy_launched_per_cu(threads, chunks, hold, with_grad, T, n_samples):
+    """Workgroups a compute unit that a call launches, as far as the kernel's registers allow for that many."""
+    return _load().ce_launched_per_cu(threads, chunks, int(hold), int(with_grad), T, n_samples)
+
+
+def cross_entropy_plan_lds(T, n_samples):
+    """Bytes of LDS that a workgroup plans its rows in."""
+    return _load().ce_plan_lds(T, n_samples)

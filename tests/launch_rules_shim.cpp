@@ -16,3 +16,8 @@ extern "C" void bwd_route(int d_qk, int T, int n_samples, int Hq, int Hkv, int n
 extern "C" int ce_per_cu(int threads, int chunks, int hold, int with_grad) {
   return hbp::ce_most_per_cu(threads, chunks, hold != 0, with_grad != 0);
 }
+// workgroups a compute unit of the cross-entropy's main kernel, as far as the registers allow for that many
+extern "C" int ce_launched_per_cu(int threads, int chunks, int hold, int with_grad, int T, int n_samples) {
+  return hbp::ce_per_cu(1 << 20, threads, chunks, hold != 0, with_grad != 0, T > hbp::kCePlanRows ? 0 : hbp::ce_plan_lds(T, n_samples));
+}
+extern "C" int ce_plan_lds(int T, int n_samples) { return hbp::ce_plan_lds(T, n_samples); }
