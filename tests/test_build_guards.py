@@ -137,6 +137,25 @@ def test_the_forward_kernels_keep_their_registers():
         assert spills[name] <= (2 if "Li192ELi128ELi1ELi1E" in name else 0), (name, spills[name])
 
 
+@pytest.mark.parametrize("source,kernels", [("fwd.hip", 18), ("bwd.hip", 13)])
+def test_no_store_of_whole_rows_stands_in_a_loop_over_descriptors(source, kernels):
+    """A buffer store takes its descriptor from scalar registers.  Where the compiler has part of it in vector registers it
+    puts every such store into a loop over the values that the lanes might have, with a wait for the LDS read in each: all 4 to 12
+    stores at the end of an item of the forward and of dQ had one."""
+    text = device_asm(source)
+    names = [n for n in kernel_metadata(text) if re.search(r"fwd_kernel|fwd_direct_kernel|bwd_dq|bwd_dkdv|bwd_both", n)]
+    names = [n for n in names if "reduce" not in n]
+    assert len(names) == kernels, names
+    stores = 0
+    for name in names:
+        ins = kernel_instructions(text, name)
+        for i, l in enumerate(ins):
+            if l.startswith("buffer_store"):
+                stores += 1
+                assert not any(x.startswith("s_cbranch_execnz") for x in ins[i + 1:i + 5]), (name, ins[i:i + 5])
+    assert stores >= kernels
+
+
 @pytest.mark.parametrize("form", ["Li2ELi1E", "Li1ELi2E"])
 def test_the_forwards_hot_loop_reloads_few_spilled_scalars(form):
     """Head size 128, eight wavefronts: the loop over pairs of unmasked tiles (64 MFMAs, some 1300 instructions) had 14
