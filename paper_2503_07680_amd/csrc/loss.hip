@@ -376,10 +376,10 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   // packs too long for ce_plan_rows have them as well, by ce_partition_kernel, and so have streamed rows (not measured).
   constexpr bool kDealt = ce_dealt(NT, NCH, HOLD, WITH_GRAD);
   //
-  // Per-row scalars (row, label, weight, logit at the label) of the workgroup's next kRowBatch rows, staged
+  // Per-row scalars (label, weight, logit at the label; its number, where rows may be dealt) of the workgroup's next kRowBatch rows, staged
   // in LDS by one thread per row.  Read from global memory inside the row loop they would have to be
   // waited for with every outstanding store and load of the chunk pipeline (the counter is in order).
-  __shared__ int row_index[kRowBatch], row_label[kRowBatch];
+  __shared__ int row_index[kDealt ? kRowBatch : 1], row_label[kRowBatch];
   __shared__ float row_weight[kRowBatch], row_zlabel[kRowBatch];
   extern __shared__ uint64_t plan_lds[];
   __shared__ int plan_range[2], plan_slots[NW];
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
           if (HOLD && !WITH_GRAD) p.token_loss[row] = p.weighted[row] = 0.f;
         }
       }
-      row_index[tid] = row;
+      if (kDealt) row_index[tid] = row;
       row_label[tid] = lab;
       row_weight[tid] = wt;
       row_zlabel[tid] = zl;
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
     return;
   }
   stage_rows(0);
-  int r = __builtin_amdgcn_readfirstlane(row_index[0]);
+  int r = kDealt ? __builtin_amdgcn_readfirstlane(row_index[0]) : first;
   int label = row_label[0];  // -1: no loss
   float w = row_weight[0], z_label = row_zlabel[0];
   if (HOLD && label >= 0) {
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   }
   for (int parity = 0, i_next = 1; i_next <= n; ++i_next) {
     if (i_next % kRowBatch == 0 && i_next < n) stage_rows(i_next);
-    const int r_next = __builtin_amdgcn_readfirstlane(row_index[i_next % kRowBatch]);
+    const int r_next = kDealt ? __builtin_amdgcn_readfirstlane(row_index[i_next % kRowBatch]) : r + 1;
     const int label_next = i_next < n ? row_label[i_next % kRowBatch] : -1;
     const float w_next = row_weight[i_next % kRowBatch], z_label_next = row_zlabel[i_next % kRowBatch];
     const bool fetch_next = HOLD && label_next >= 0;

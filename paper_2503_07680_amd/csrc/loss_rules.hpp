@@ -19,7 +19,7 @@ constexpr bool ce_dealt(int nt, int nch, bool hold, bool with_grad) { return wit
 
 // The most LDS that the main kernel's own arrays take: statistics of the wavefronts, two sets, and the counts of the
 // planning; the rows' scalars; its range of rows.
-constexpr int ce_own_lds(int nt, bool dealt) { return 5 * 4 * (nt / 64) + (dealt ? 5 : 4) * 4 * kCeRowBatch + 16; }
+constexpr int ce_own_lds(int nt, bool dealt) { return 5 * 4 * (nt / 64) + (dealt ? 5 : 3) * 4 * kCeRowBatch + 16; }
 
 // The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
 // the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this

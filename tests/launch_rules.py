@@ -60,3 +60,8 @@ def cross_entropy_launched_per_cu(threads, chunks, hold, with_grad, T, n_samples
 def cross_entropy_plan_lds(T, n_samples):
     """Bytes of LDS that a workgroup plans its rows in."""
     return _load().ce_plan_lds(T, n_samples)
+
+
+def cross_entropy_own_lds(threads, chunks, hold, with_grad):
+    """The most bytes of LDS that the main kernel's own arrays take."""
+    return _load().ce_own_lds(threads, chunks, int(hold), int(with_grad))

@@ -21,3 +21,7 @@ extern "C" int ce_launched_per_cu(int threads, int chunks, int hold, int with_gr
   return hbp::ce_per_cu(1 << 20, threads, chunks, hold != 0, with_grad != 0, T > hbp::kCePlanRows ? 0 : hbp::ce_plan_lds(T, n_samples));
 }
 extern "C" int ce_plan_lds(int T, int n_samples) { return hbp::ce_plan_lds(T, n_samples); }
+// the most LDS that the main kernel's own arrays take
+extern "C" int ce_own_lds(int threads, int chunks, int hold, int with_grad) {
+  return hbp::ce_own_lds(threads, hbp::ce_dealt(threads, chunks, hold != 0, with_grad != 0));
+}

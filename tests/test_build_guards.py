@@ -186,13 +186,15 @@ def test_the_loss_kernels_keep_a_row_in_registers_without_spills():
 def test_no_loss_workgroup_is_launched_beyond_those_that_fit():
     """The main kernel's grid is what the chip holds at once: a workgroup more than a compute unit's LDS has room for (given
     out in pieces of 1280 bytes of its 160 KB) would begin with its share of the rows when the others have ended.  The
-    kernel's own arrays are taken from what the compiler gave them."""
+    kernel's own arrays are taken from what the compiler gave them; where no rows are dealt, the rows' numbers are not among
+    them (an LDS read a row instead of an addition: 1 % of 2500 rows of 4096)."""
     import launch_rules as rules
     kernels = [(tuple(int(x) for x in m.group(2, 3, 4, 5)), int(m.group(1))) for m in
                re.finditer(r"\.group_segment_fixed_size: (\d+)\n(?:(?!\s+\.name:).*\n)*\s+\.name:\s+\S+ce_main_kernelILi(\d+)ELi(\d+)ELb(\d)ELb(\d)E",
                            device_asm("loss.hip"))]
     assert len({k for k, _ in kernels}) == len(kernels) == 76
     for (threads, chunks, hold, grad), own in kernels:
+        assert own <= rules.cross_entropy_own_lds(threads, chunks, hold, grad) <= own + 64, (threads, chunks, hold, grad, own)
         for n_samples in (1, 63, 1023):
             for T in list(range(512, 131073, 512)) + [131073]:
                 plan = rules.cross_entropy_plan_lds(T, n_samples) if T <= 131072 else 0
