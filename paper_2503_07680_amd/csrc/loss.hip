@@ -363,15 +363,16 @@ __global__ __launch_bounds__(NT) void ce_main_kernel(const CeParams p) {
   // rows a workgroup, cut by cost, lie all over the tensors, and a row without a loss between two with one leaves nothing to
   // read behind its zeros.  Plain copies of 8192 rows of 128256: 5.13 TB/s that way, 5.28 in turn; zeros alone 5.70.)
   // All zeros in front of the first row with a loss -> a share at a time, 30 % of the rows without, us: 8192 rows of 128256: 708
-  // -> 693; 4096: 363 -> 352; 2048: 187 -> 180; 1000 of 32000: 26.8 -> 26.6; 300 of 65536: 21.1 -> 18.6.  The first of these
-  // against rows cut by cost, us, T = 1000 to 8192, 0 to 70 % of the rows without a loss:
-  //   V = 4096 to 8192         .82 to 1.04        50304    1.01 to 1.13 (8192 rows, 30 %: 292 -> 272)
-  //       10240                .90 to 1.04        65536    1.00 to 1.16
-  //       12288               1.04 to 1.14        81928     .95 to 1.12
-  //       16384               1.04 to 1.20       128256    1.02 to 1.10; 8192 rows, 30 %: 738 -> 707, 707 -> 693 and 612 -> 646
-  //       16392                .96 to 1.11       151936    1.04 to 1.31; 8192 rows, 30 %: 886 -> 842, 763 -> 788
-  //       24576               1.05 to 1.12       (2.1 GB a tensor: with where in memory they lie)
-  //       32000               1.03 to 1.23
+  // -> 693; 4096: 363 -> 352; 2048: 187 -> 180; 1000 of 32000: 26.8 -> 26.6; 300 of 65536: 21.1 -> 18.6.
+  // Time of rows cut by cost / of dealt ones, T = 1000, 2500 and 8192, 0, 30 and 70 % of the rows without a loss:
+  //   V = 1024, 2048        1.00 to 1.16       24576             1.06 to 1.18
+  //       4096 to 8192       .81 to 1.10       32000              .99 to 1.24
+  //       10240              .97 to 1.09       61440, 65536      1.00 to 1.23
+  //       10248              .99 to 1.18       81920, 81928      1.02 to 1.28
+  //       12288, 16384      1.04 to 1.26       90112 to 128256   1.03 to 1.16
+  //       16392, 20480       .99 to 1.20       151936            1.04 to 1.29
+  // (2.1 GB a tensor: with where in memory they lie.  8192 rows of 128256, 30 %, on four cards, us: 738 -> 707, 707 -> 693, 612
+  // -> 646, 738 -> 696.)
   // Without the gradient consecutive rows, cut by cost, are as fast, and found sooner (300 of 128256: 14.9 against 16.0);
   // packs too long for ce_plan_rows have them as well, by ce_partition_kernel, and so have streamed rows (not measured).
   constexpr bool kDealt = ce_dealt(NT, NCH, HOLD, WITH_GRAD);
@@ -712,22 +713,28 @@ static bool launch_held(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t e
 
 // Threads a row.  A row costs its workgroup one reduction and one barrier whatever its length, with nothing
 // else to run on the compute unit if the workgroup fills it; several smaller workgroups overlap theirs.  A
-// longer row has to be spread over more threads to be held.  us at T = 8192 with the gradient / without:
+// longer row has to be spread over more threads to be held.  us at T = 8192 with the gradient, 30 % of the rows without a
+// loss / without the gradient:
 //   V        1024 threads   512          256
-//   4096      65 /  41       41 /  27     37 /  22
-//   16384    111 /  50      104 /  42    104 /  43
-//   32000    192 /  70      192 /  68    195 /  72
-//   65536    381 / 130      375 / 130
-//   81920    476 / 156      473 / 157
+//   4096      62 /  41       43 /  27     36 /  22
+//   16384    113 /  50       90 /  42     93 /  43
+//   20480    132            114          117
+//   32000    178 /  70      172 /  68    182 /  72
+//   65536    349 / 130      356 / 130
+//   81920    437 / 156      446 / 157
 // With few rows, T = 64 / 1000 with the gradient:
-//   4096      9.5 / 17.4     8.3 / 12.5     8.3 / 10.5
-//   16384    10.8 / 23.0    10.0 / 20.3    10.3 / 19.9
-//   32000    13.0 / 33.0    12.3 / 30.5    14.2 / 31.5
-// A call whose workgroups have a row each (two of 512 threads a compute unit) is as long as the compute units with
-// two rows; 1024 threads have half the chain a row and, with one workgroup a compute unit, ranges cut by cost.
-// T = 280 / 512 with the gradient, 1024 threads and 512: V = 81920: 24.0 / 40.1 and 27.1 / 42.1; 65536: 21.2 / 33.6 and
-// 26.2 / 34.7; T = 256, 57352: 18.3 and 17.3.  Without it both have one workgroup a compute unit and are alike (81920:
-// 14.0 / 21.8 and 14.3 / 21.3; 65536: 12.8 / 19.2 and 13.0 / 19.4); the line is the same, so the losses are the same bits.
+//   4096      9.1 / 15.9     8.3 / 12.0     8.3 / 9.9
+//   16384     9.6 / 24.0     9.0 / 17.7     8.9 / 16.3
+//   20480    10.3 / 26.8     9.2 / 19.5     9.7 / 19.6
+//   32000    10.7 / 29.5    10.0 / 24.8    10.9 / 28.7
+// Few (up to two rows a compute unit, so that workgroups of 512 threads have a row each): 1024 threads have half the chain
+// a row, as long as no more rows than compute units have a loss; with more of them some units have two rows after one
+// another.  T = 280 / 512 with the gradient, 30 % of the rows without a loss, 1024 threads and 512: V = 65536: 18.2 / 27.6
+// and 20.2 / 28.5; 81920: 21.2 / 33.7 and 25.8 / 34.6.  All with a loss: 25.7 / 29.5 and 18.8 / 24.1; 29.8 / 35.0 and 21.8 /
+// 30.3.  The host does not know how many have one.  Up to 256 rows, V = 65536 to 81920, 512 threads are 0 to 3 % faster;
+// V = 45056 to 61440: 1024 threads 3 to 7 % slower, T = 280: 5 % faster with 30 % without a loss, 27 % slower with none.
+// Without the gradient both have one workgroup a compute unit and 512 threads are 0 to 3 % faster; the line is the same, so
+// the losses are the same bits.
 constexpr int kCeRow256 = 16384, kCeRow512 = 81920, kCeRow512Few = 61440;  // Few: a row a workgroup at most
 
 int launch_packed_ce(const CeParams& p, int n_cu, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {

@@ -21,11 +21,18 @@ constexpr bool ce_dealt(int nt, int nch, bool hold, bool with_grad) { return wit
 // planning; the rows' scalars; its range of rows.
 constexpr int ce_own_lds(int nt, bool dealt) { return 5 * 4 * (nt / 64) + (dealt ? 5 : 3) * 4 * kCeRowBatch + 16; }
 
-// The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows,
-// the cut between them is coarser and they store into more rows at a time.  us at T = 1000 / 2500 / 8192 with this
-// many and with one more.  With the gradient: V = 32000: 30.5 / 65.5 / 190 and 34.1 / 65.8 / 193; 45056: 41.1 / 86.8 /
-// 267 and 44.3 / 87.1 / 270; 28672: 30.4 / 57.2 / 174 and 28.0 / 60.0 / 174; 16384: 19.2 / 35.7 / 103 and 19.3 / 38.5 /
-// 104.
+// The most workgroups a compute unit gets, if the registers allow for more: with more of them each has fewer rows, and
+// they store into more rows at a time.  With the gradient, time with this many / with one fewer, T = 1000, 2500, 8192, all
+// rows with a loss; 30 % without:
+//   256 threads, V = 10248    .99, 1.02, 1.00; 1.00, 1.01, 1.01       512, V = 24576    .98,  .96, 1.00; 1.00, 1.02, 1.02
+//                    12288   1.00,  .99, 1.00; 1.00, 1.03, 1.01                28672   1.00,  .98, 1.01; 1.04, 1.03, 1.02
+//                    16384   1.00,  .99, 1.01; 1.00, 1.02, 1.01                32000    .84,  .88,  .91;  .82,  .92,  .95
+//                                                                              45056    .88,  .90,  .95;  .84,  .97, 1.00
+// The registers allow for one more at V = 16392 to 20480 and 32000 alone.  With this many / with one more:
+//   512 threads, V = 16392    .95,  .88,  .96;  .93,  .93,  .95; 70 % without:  .94, 1.11,  .94
+//                    20480    .98,  .86,  .94;  .96,  .92,  .96;                .92, 1.11,  .97
+//                    32000   1.00, 1.00,  .98;  .94,  .97,  .98
+// (with one more, rows of 16392 to 20480 were up to 6 % slower than cut by cost; with this many they are not.)
 // Without it a workgroup has a row under way whatever its work is, so fewer are enough.  With 1 / 2 / 4 of 256 threads,
 // V = 4096: 9.9 / 9.7 / 8.9, 16.0 / 13.4 / 11.8 and 37 / 28 / 23; 8000: 10.6 / 10.5 / 9.8, 17 / 15 / 14, 41 / 32 / 29 (8:
 // 13.3 and 14.7 at T = 2500); with 1 / 2 of 512, V = 32000: 16.0 / 18.1, 26.6 / 29.3, 68 / 70; 65536: 24.6 / 29.7, 43.5 /
@@ -40,7 +47,7 @@ constexpr int ce_most_per_cu(int nt, int nch, bool hold, bool with_grad) {
   if (!hold) return 2;
   if (!with_grad) return nt == 256 ? 4 : 1;
   if (nt == 256) return nch <= 5 ? 8 : nch <= 7 ? 7 : 6;
-  if (nt == 512) return nch <= 5 ? 4 : nch <= 7 ? 3 : 2;
+  if (nt == 512) return nch <= 7 ? 3 : 2;
   return 2;
 }
 // Workgroups a compute unit holds at once; the main kernel's grid is that times the compute units.  One more would have
