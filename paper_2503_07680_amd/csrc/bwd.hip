@@ -236,6 +236,7 @@ __device__ __forceinline__ void dq_items(int block) {
           wait_async_loads();
         }
         RowStage<DV>::fragments(do_at, lane, dof);
+        race_fence();
       }
       // the dP^T accumulator of every block starts at -D of the lane's query (one value per lane): the
       // subtraction in dS = P (dP - D) then comes out of the MFMAs
@@ -415,6 +416,7 @@ __device__ __forceinline__ void dq_items(int block) {
       if (cur_buf) point_offsets_at(0);
 
       __syncthreads();  // the tiles are no longer read
+      race_fence();
       if (wave_active) {
         const uint32_t at = lds_all + wave_in_wg * Lds::UNIT;
         RowStage<DQK>::put(at, lane, dqacc, p.scale);
@@ -637,6 +639,7 @@ __device__ __forceinline__ void dkdv_items(int block, int n_resident) {
       {
         RowStage<DQK>::fragments(k_at, lane, knat);
         RowStage<DV>::fragments(v_at, lane, vnat);
+        race_fence();
 #pragma unroll
         for (int c = 0; c < NCV; ++c) vnat[c].u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
       }
@@ -1112,12 +1115,14 @@ __device__ __forceinline__ void dkdv8_items(int block, int n_resident) {
       issue_all(std::integral_constant<int, 1>{});
       advance(1);
       wait_async_but<2 * N_COPY>();
+      race_fence();
       __syncthreads();
 
       Frag knat[NC], vnat[NC];
       {
         RowStage<DQK>::fragments(k_at, lane, knat);
         RowStage<DQK>::fragments(v_at, lane, vnat);
+        race_fence();
         if constexpr (kKLds) {  // the two waves of a key group write half of the fragments each, where the rows were
           lds_barrier();
 #pragma unroll

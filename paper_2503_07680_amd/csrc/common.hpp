@@ -319,6 +319,38 @@ __device__ __forceinline__ void wait_async_loads() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt left at their maxima
 }
 
+// all of this wave's LDS operations have completed
+__device__ __forceinline__ void wait_lds_reads() {
+  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+}
+// all but the last N of this wave's outstanding loads and copies have completed
+template <int N>
+__device__ __forceinline__ void wait_async_but() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "i"(N) : "memory");
+}
+
+// Race-hunting build (-DHBP_RACE_HUNT, a second library next to the release one): a full fence of the
+// workgroup - this wave's tile copies and LDS operations complete, then a barrier - at the end of every
+// phase of the forward and of every tile or step of the backward kernels, and around an item's rows: when the
+// wavefronts have them from LDS and before they go out that way.  The release build gets by with
+// one barrier per tile and relies on which buffer each phase still reads; if that reasoning were wrong
+// somewhere, the two builds would differ.  The arithmetic and its order are the same, so they must agree
+// bit for bit.  Every call site is reached by all wavefronts of the workgroup equally often.
+__device__ __forceinline__ void race_fence() {
+#ifdef HBP_RACE_HUNT
+  wait_async_loads();
+  __syncthreads();
+#endif
+}
+// The same for what a wavefront hands to itself, without the barrier: the rows that it copies, reads, writes and stores by
+// itself (RowStage).  The release build waits for a count of copies, or for nothing where LDS operations are in order.
+__device__ __forceinline__ void race_fence_of_wave() {
+#ifdef HBP_RACE_HUNT
+  wait_async_loads();
+  wait_lds_reads();
+#endif
+}
+
 // A wavefront's own 32 rows of a [rows][D] operand, taken through LDS in whole rows: the fragments of an MFMA operand have a
 // row a lane, and read from global memory that way a load touches 32 rows at 32 bytes each, which holds the compute unit's
 // address path about 64 clocks a load instead of 16 (what counts is whether neighbouring lanes read the same line: 8 rows at
@@ -371,6 +403,7 @@ struct RowStage {
   // PARTS: this wavefront's part of the rows only
   template <int PARTS = 1>
   static __device__ __forceinline__ void copy_in(const uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane, int part = 0) {
+    race_fence_of_wave();
     constexpr int MINE = N / PARTS;
     static_assert(MINE % PERIOD == 0 && (PARTS == 1 || moved(MINE / PERIOD) == 0), "the parts' places are alike");
     const u32x4 d = desc(g + (PARTS == 1 ? 0 : (int64_t)part * (32 / PARTS) * (stride_bytes / 2)), stride_bytes, rows_valid - part * (32 / PARTS));
@@ -392,6 +425,7 @@ struct RowStage {
   // the D / 16 fragments of the rows as an MFMA operand: lane has row lane % 32, dims 16 c + 8 (lane / 32) .. + 7 in fragment c
   template <int NC>
   static __device__ __forceinline__ void fragments(uint32_t lds, int lane, Frag (&f)[NC]) {
+    race_fence_of_wave();
     lane = fresh(lane);
 #pragma unroll
     for (int c = 0; c < NC; ++c) f[c].u = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, c, lane);
@@ -400,12 +434,14 @@ struct RowStage {
   // memory, 1 KiB a store.
   template <int NB>
   static __device__ __forceinline__ void put(uint32_t lds, int lane, const f32x16 (&acc)[NB], float scale) {
+    race_fence_of_wave();
     lane = fresh(lane);
 #pragma unroll
     for (int b = 0; b < 2 * NB; ++b)
       *(__attribute__((address_space(3))) u32x4*)(uintptr_t)at(lds, b, lane) = pack_block_half(acc[b / 2], scale, b % 2);
   }
   static __device__ __forceinline__ void copy_out(uint16_t* g, uint32_t stride_bytes, int rows_valid, uint32_t lds, int lane) {
+    race_fence_of_wave();
     lane = fresh(lane);
     // one descriptor for the wavefront, in scalar registers: with the span or the base worked out in vector registers every store
     // stood in a loop of its own over the descriptors that the lanes might have (training step, us: 1024 tokens, 4 heads of 64:
@@ -421,15 +457,6 @@ struct RowStage {
     }
   }
 };
-// all of this wave's LDS reads have arrived
-__device__ __forceinline__ void wait_lds_reads() {
-  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-}
-// all but the last N of this wave's outstanding loads and copies have completed
-template <int N>
-__device__ __forceinline__ void wait_async_but() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "i"(N) : "memory");
-}
 
 // ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives element i%4 of the 8-byte
 // words addressed by lanes i/4, i/4+4, i/4+8, i/4+12 of the group.
@@ -606,19 +633,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Race-hunting build (-DHBP_RACE_HUNT, a second library next to the release one): a full fence of the
-// workgroup - this wave's tile copies and LDS operations complete, then a barrier - at the end of every
-// phase of the forward and of every tile or step of the backward kernels.  The release build gets by with
-// one barrier per tile and relies on which buffer each phase still reads; if that reasoning were wrong
-// somewhere, the two builds would differ.  The arithmetic and its order are the same, so they must agree
-// bit for bit.  Every call site is reached by all wavefronts of the workgroup equally often.
-__device__ __forceinline__ void race_fence() {
-#ifdef HBP_RACE_HUNT
-  wait_async_loads();
-  __syncthreads();
-#endif
 }
 
 // Workgroup-wide fetch of the next item: thread 0 takes it, everybody reads it back as scalars.

@@ -428,6 +428,7 @@ __device__ __forceinline__ void fwd_items() {
       if constexpr (Lds::kStaged) {
         wait_async_but<decltype(k_loader)::PER_WAVE + decltype(v_loader)::PER_WAVE>();
         RowStage<DQK>::fragments(stage, lane, w.qf);
+        race_fence();
       } else {
         const uint16_t* qp = p.q + (int64_t)my_row * p.q_st + (int64_t)h * p.q_sh + 8 * hh;
 #pragma unroll

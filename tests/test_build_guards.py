@@ -25,14 +25,15 @@ def kernel_metadata(asm_text):
 _ASM_CACHE = {}
 
 
-def device_asm(source):
-    if source not in _ASM_CACHE:
+def device_asm(source, flags=()):
+    key = (source, *flags)
+    if key not in _ASM_CACHE:
         with tempfile.TemporaryDirectory() as tmp:
             out = os.path.join(tmp, "out.s")
-            cmd = [B._hipcc()] + B.HIP_FLAGS + ["-S", "--cuda-device-only", os.path.join(B.CSRC, source), "-o", out]
+            cmd = [B._hipcc()] + B.HIP_FLAGS + [*flags, "-S", "--cuda-device-only", os.path.join(B.CSRC, source), "-o", out]
             subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-            _ASM_CACHE[source] = open(out).read()
-    return _ASM_CACHE[source]
+            _ASM_CACHE[key] = open(out).read()
+    return _ASM_CACHE[key]
 
 
 def backward_asm():
@@ -201,3 +202,24 @@ def test_no_loss_workgroup_is_launched_beyond_those_that_fit():
                 fit = 160 * 1024 // (-(-(plan + own) // 1280) * 1280)
                 launched = rules.cross_entropy_launched_per_cu(threads, chunks, hold, grad, T, n_samples)
                 assert launched <= fit, (threads, chunks, hold, grad, T, n_samples, launched, fit)
+
+
+@pytest.mark.parametrize("source,least", [("fwd.hip", 16), ("bwd.hip", 11)])
+def test_the_race_hunting_build_waits_for_all_copies_of_an_items_rows(source, least):
+    """The release build waits for an item's rows by a count of copies.  Were a count too high, the build that it is compared
+    with would have to differ: it waits for all of them in front of the first LDS read behind every such count."""
+    def counted_waits(text):
+        out = []
+        for name in kernel_metadata(text):
+            ins = kernel_instructions(text, name)
+            for i, l in enumerate(ins):
+                m = re.match(r"s_waitcnt vmcnt\((\d+)\)$", l)
+                copies = [k for k in range(max(0, i - 400), i) if re.match(r"buffer_load_dwordx4 .*lds", ins[k])]
+                read = next((k for k in range(i, min(i + 120, len(ins))) if ins[k].startswith("ds_read_b128")), None)
+                in_a_step = any(x.startswith("v_mfma") for x in ins[max(0, i - 300):i])
+                if m and int(m.group(1)) and copies and read is not None and not in_a_step:
+                    out.append((name, i, any("vmcnt(0)" in x for x in ins[copies[-1]:read])))
+        return out
+    release, hunting = counted_waits(device_asm(source)), counted_waits(device_asm(source, ["-DHBP_RACE_HUNT"]))
+    assert sum(not full for _, _, full in release) >= least, release
+    assert len(hunting) >= least and all(full for _, _, full in hunting), hunting
