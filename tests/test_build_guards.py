@@ -138,6 +138,18 @@ def test_the_forward_kernels_keep_their_registers():
         assert spills[name] <= (2 if "Li192ELi128ELi1ELi1E" in name else 0), (name, spills[name])
 
 
+def test_the_forward_kernels_of_one_item_keep_their_registers():
+    """The kernels that packs of few rounds run: no spills, registers for eight wavefronts a compute unit, and at head size 64
+    for three workgroups of four wavefronts (512 registers a lane in a SIMD, given out by eight)."""
+    text = device_asm("fwd.hip")
+    regs = {m.group(1): int(m.group(2)) for m in
+            re.finditer(r"\.name:\s+(\S+fwd_direct_kernel\S+)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)", text)}
+    spills = {k: v for k, v in kernel_metadata(text).items() if "fwd_direct_kernel" in k}
+    assert len(regs) == len(spills) == 9 and not any(spills.values()), (regs, spills)
+    for name in regs:
+        assert regs[name] <= (168 if "Li64ELi64ELi1ELi1E" in name else 256), (name, regs[name])
+
+
 @pytest.mark.parametrize("source,kernels", [("fwd.hip", 18), ("bwd.hip", 13)])
 def test_no_store_of_whole_rows_stands_in_a_loop_over_descriptors(source, kernels):
     """A buffer store takes its descriptor from scalar registers.  Where the compiler has part of it in vector registers it
