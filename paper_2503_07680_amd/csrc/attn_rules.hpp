@@ -34,33 +34,46 @@ struct PackShape {
 // also one head a workgroup of four wavefronts, two workgroups a compute unit, instead of a pair of heads on one K/V
 // stream (kSingles): a workgroup's prologue and end are then covered by the other one, and the last round is finer.  With
 // more rounds the queues balance better, and long samples need the shared stream.  `rounds`: items (pairs of heads, or
-// 256-row tiles) to a compute unit; `len`: tokens a sample.  Forward, time with queues and pairs / this way, T = 2048 to
-// 32768, 3 to 64 heads:
-//   even, d = 64     singles, to 7: 1.03 to 1.37; to 10, samples of 100 to 250: 1.10 to 1.14
-//   even, d >= 128   singles, to 2: 1.03 to 1.34; samples to 100, to 8: 1.04 to 1.23
-//     kv heads dealt evenly to the dies: pairs, 2 to 4.8: 1.00 to 1.12 (samples of 1600: .98), 5.3: .99; singles there
-//                    gain up to .03 more, but .96 to .99 with a sample of half the pack
-//     else           pairs, 2 to 2.7: 1.00 to 1.10; 3.1: .98; singles, 2.5: .98 to 1.03
-//   odd              256-row tiles, to 3.5: 1.00 to 1.52; 3.6: .99; 4.2 to 4.7: .97 to 1.03; samples to 128, 4.0 to 5.5:
-//                    1.04 to 1.14
-//   odd, kHalves     a workgroup of four wavefronts takes half of a 256-row tile: the longest item's chain of key tiles runs
-//                    without a second wavefront on its SIMD.  Against 256-row tiles, mixed samples and one of .4 or .5:
-//     d = 64         to 4.2: 1.00 to 1.31; 4.5: .97 to 1.09; len to 320, to 7.5: 1.01 to 1.24
-//     d = 128        to .75: 1.02 to 1.23; .8 to 2: .93 to 1.17; len to 350, to 9: 1.02 to 1.42; 11 to 22: .95 to 1.10
-//     d = 192        to 2.3: 1.01 to 1.21; 3 to 4.5: .97 to 1.13; len to 350, to 6: 1.01 to 1.20; 7.4: .99
-//     len to 100     from 1.05 on: 1.10 to 1.45, and packs of that mean with a long sample .97 to 1.02 to T = 16384; with a
-//                    round or less: .97 to 1.03
-// The host knows the samples' mean length alone, and beyond two rounds a very long sample beside short ones loses by every
-// way but the queues: 9500 tokens with a sample of 7125, 16/8 heads of 128: .96.  kDirect and kSingles therefore end at
-// T = 8192 or 16384.  kHalves does not: beyond 2.5 rounds, T = 18000 to 48000, against 256-row tiles with queues, without a
-// long sample / with one of .3 / of .4 or .5 / of .65 or .7 of the pack
-//   d = 64, 8 heads          1.05 to 1.31 / 1.04 to 1.28 / .96 to 1.23 / .95 to 1.06
-//           4                1.14 to 1.33 / 1.17 to 1.28 / 1.03 to 1.26 / .95 to 1.19
-//           6/2              1.06 to 1.37 / 1.02 to 1.28 / .92 to 1.23 / .93 to 1.20
-//   d = 128, 8, 12, 16 heads 1.03 to 1.23 / .95 to 1.13 / .95 to 1.06 / .96 to .98 (the losses from 4.5 rounds on)
-//            9/3             1.13 to 1.23 / 1.09 to 1.15 / 1.08 to 1.21 / not measured
-//   d = 192, 12/4            1.11 and 1.12 / 1.05 / 1.03 / not measured
-// A bound on T there would lose the first two columns for what the last two lose.
+// 256-row tiles) to a compute unit; `len`: tokens a sample.  Forward, time with queues and pairs or 256-row tiles / this way,
+// T = 512 to 60000, 4 to 64 heads, samples of 60 to 1500 tokens (log-normal) alone / with one of .4 of the pack / of .7:
+//   even, d = 64, singles           to 7, T to 16384           1.08 to 2.03 / 1.13 to 1.67 / 1.03 to 1.54
+//                                   2 to 12, longer packs      1.10 to 1.66 / 1.05 to 1.18 / 1.02 to 1.10
+//   even, d >= 128, singles         to 2                       1.03 to 1.91 / 1.00 to 1.72 / 1.05 to 1.55
+//                                   2 to 2.7, len > 100        1.00 to 1.34 /  .99 to 1.35 /  .93 to 1.25
+//                     len to 100    2 to 8, T to 8192          1.20 to 1.48 / 1.06 to 1.32 / -
+//                                   2 to 12, longer packs      1.10 to 1.30 /  .95 to 1.29 / -
+//     kv heads dealt evenly, pairs  2 to 4.8, T to 8192        1.00 to 1.41 / 1.04 to 1.31 / 1.02 to 1.29
+//                                   4.8 to 7, T to 8192        1.01 to 1.29 / 1.03 to 1.17 / 1.00 to 1.06
+//                                   2 to 4.8, longer packs     1.00 to 1.20 /  .99 to 1.08 / 1.00 to 1.05
+//                                   4.8 to 12, longer packs     .96 to 1.21 /  .98 to 1.06 /  .98 to 1.02
+//       singles there against pairs, 2 to 4.8                   .93 to 1.08 /  .92 to 1.12 /  .95 to 1.04
+//     else, pairs                   2 to 2.7, T to 8192        1.28 to 1.34 / 1.13         / -
+//                                   2 to 4.8, longer packs      .99 to 1.28 /  .96 to 1.18 /  .97 to 1.10
+//                                   4.8 to 12                   .94 to 1.20 /  .96 to 1.07 /  .97 to 1.03
+//   odd, 256-row tiles              to 3.5, T to 16384         1.00 to 1.88 / 1.00 to 1.59 / 1.00 to 1.36
+//                                   3.5 to 5.5, T to 16384     1.01 to 1.53 /  .99 to 1.51 / 1.01 to 1.35
+//                                   2 to 5.5, longer packs      .97 to 1.43 /  .95 to 1.20 /  .97 to 1.29
+//                                   5.5 to 12                   .95 to 1.42 /  .95 to 1.42 /  .97 to 1.26
+//   odd, kHalves: a workgroup of four wavefronts takes half of a 256-row tile: the longest item's chain of key tiles runs
+//   without a second wavefront on its SIMD.  Against the better of 256-row tiles with queues and without:
+//     d = 64          to 4.2                                    .99 to 1.45 / 1.02 to 1.27 /  .97 to 1.27
+//                     4.2 to 7.5, len to 320                   1.34 to 1.53 / 1.04 to 1.24 /  .99 to 1.09
+//                     beyond, to 12                            1.09 to 1.62 / 1.02 to 1.18 / 1.02 to 1.08
+//     d = 128         to .75                                   1.03 to 1.22 /  .98 to 1.20 / 1.07 to 1.17
+//                     .75 to 9, len to 350                     1.00 to 1.31 /  .98 to 1.22 /  .95 to 1.19
+//                     .75 to 9, len > 350                       .91 to 1.20 /  .88 to 1.15 /  .92 to 1.15
+//                     9 to 12, len to 350                      1.12 to 1.32 /  .97 to 1.13 /  .95 to  .98
+//     d = 192         to 2.3                                    .93 to 1.21 /  .98 to 1.17 / 1.00 to 1.17
+//                     2.3 to 6, len to 350                     1.02 to 1.27 /  .98 to 1.14 /  .96 to 1.09
+//                     2.3 to 6, len > 350                       .93 to 1.10 /  .93 to 1.08 /  .96 to 1.05
+//                     6 to 12, len to 350                      1.04 to 1.27 /  .96 to 1.07 /  .96 to  .99
+//     len to 100      to 1.05                                  1.08 to 1.20 / 1.04 to 1.25 / -
+//                     more, T to 16384                          .92 to 1.69 / 1.02 to 1.27 / -
+//                     more, longer packs                       1.38 to 1.75 /  .99 to 1.25 / -
+// The lines were drawn with an item's rows read a row a lane and two of a die's heads at a time without queues, where a way lost
+// just behind its line.  The table is of the kernels as they are: no way loses within its lines but as shown, and several gain
+// beyond them too; the lines have stayed.  The host knows the samples' mean length alone, so a line has to hold for packs with
+// a very long sample beside short ones as well.
 enum FwdWay { kQueues, kDirect, kSingles, kHalves };
 inline FwdWay fwd_way(const PackShape& p, int64_t n_items, bool records) {
   if (records) return kQueues;  // records are one per resident workgroup
@@ -110,16 +123,20 @@ struct BwdItems {
 
 // Eight or four wavefronts a key tile (dK/dV kernel).  Eight pay per step and cost per item, so the line is the mean
 // number of steps an item has: heads of the item x blocks of 64 rows from the tile to its sample's end.  Time of the
-// backward, four / eight, T = 512 to 32768, samples of one size and mixed ones:
-//   d = 128, one head an item    samples of 60: .81 to .97; 250: .90 to .96; 600: .95 to .99; 1000: .98 to 1.01;
-//                                1200: 1.00 to 1.01; 1500: 1.00 to 1.02; 2500: 1.02 to 1.03
-//            two                 60: .92; 150: .98; 290: 1.02; 580: 1.03; 1000: 1.03
-//            three and more      25: 1.01 (four) and 1.11 (eight); 60: 1.00 and 1.10; 250: 1.08; 1000: 1.06
-//   d = 64, one                  25: 1.01; 60: 1.00; 126: .94 to .99; 240: 1.00 to 1.07; 800: 1.03 to 1.08
-//            nine and more, no more items than compute units, d = 64 and 128: samples of 30 to 90: 1.12 to 1.25
+// backward in two launches, four / eight, T = 512 to 60000, more items than compute units, len tokens a sample (log-normal)
+// alone / with a sample of .4 of the pack / of .7:
+//                          len to 100                        200 to 400                        above 800
+//   d = 64, one head        .98 to 1.07 / 1.05 to 1.11 / -    1.03 to 1.10 / 1.06 / 1.05        1.07 to 1.12 / 1.06 / 1.05
+//           two            1.02 to 1.07 / 1.08 / -            1.10 to 1.13 / 1.08 / 1.06        1.11 / 1.07 / 1.06
+//           four           1.12 to 1.16 / 1.09 / -            1.14 to 1.18 / 1.07 / 1.07        1.09 / 1.07 / 1.06
+//   d = 128, one            .93 to 1.02 /  .99 to 1.07 / -     .96 to 1.07 / 1.00 / 1.02        1.01 to 1.06 / 1.00 / 1.02
+//            two           1.03 to 1.10 / 1.03 / -            1.05 to 1.08 / 1.04 / 1.04        1.05 / 1.04 / 1.03
+//            four, eight   1.10 to 1.19 / 1.04 / -            1.08 to 1.16 / 1.05 / 1.04        1.05 / 1.04 / 1.04
+// (single figures: the least.)  In between, one head of 128: 100 to 200: .94 to 1.06 / .99 / 1.01; 400 to 800: .99 to 1.08 / 1.01
+// / 1.01.  The lines were drawn with K and V read a row a lane, which cost eight wavefronts more; they have stayed.
 // One or two heads with no more items than compute units: the launch is as long as its longest item, so eight from 100
-// tokens a sample on (.995 to 1.39; of 60: .96 to .99).  Only a call without query tiles comes there: with them such a pack
-// has one launch for dK/dV and dQ, always of eight (see one_launch).
+// tokens a sample on.  Only a call without query tiles comes there: with them such a pack has one launch for dK/dV and dQ,
+// always of eight (see one_launch).
 inline bool eight_waves(const BwdItems& p) {
   const double len = p.pack.mean_len();
   const int heads = p.heads(), d = p.pack.d_qk;
@@ -130,17 +147,23 @@ inline bool eight_waves(const BwdItems& p) {
 }
 // dK/dV and dQ in one launch (bwd_both_kernel), and with their items interleaved?  `rounds`: dK/dV items to a compute
 // unit; heads: query heads an item loops over; len: tokens a sample.  Time of the backward, two launches / one, T = 512 to
-// 50000; samples of 60, 250, 800, 3000 (log-normal) and one sample of .4 or .5 of the pack among short ones:
-//   one head     interleaved.  To 1 round 1.3 to 1.75; to 3: 1.1 to 1.8.  Dispatched dK/dV first .94 to 1.6.
-//     d = 64     to 5.5: 1.01 to 1.36; 5.9 to 12.9, len >= 900: .97 to 1.06; len <= 320, to 19: 1.01 to 1.08
-//     d = 128    to 6.5: 1.02 to 1.20; 8.5 to 12: .97 (a sample of .5 to .7, len 1400 to 3000) to 1.08
-//                len 150 to 350, to 15: 1.02 to 1.12; 18 to 25: .99 to 1.04; shorter, to 8: 1.02 to 1.18; to 12.7: .95 to 1.01
-//   more heads   dK/dV first.  To 1 round 1.16 to 1.9.  Interleaved, two heads: .84 to 1.5 (as many dQ items as dK/dV, so
+// 60000, samples of 60 to 1500 tokens (log-normal) alone / with one of .4 of the pack / of .7; beyond a line, from there on:
+//   one head     interleaved (dK/dV first, measured before an item's rows went through LDS: .94 to 1.6)
+//     to 3       d = 64: 1.25 to 1.76 / 1.21 to 1.87 / 1.21 to 1.77; d = 128: 1.14 to 1.62 / 1.16 to 1.73 / 1.15 to 1.53
+//     d = 64     3 to 5.5: 1.08 to 1.83 / 1.10 to 1.83 / 1.00 to 1.45; len to 320, to 19: 1.05 to 1.22 / .99 to 1.37 / .94 to 1.12
+//                beyond 5.5, len > 320: .95 to 1.17 / .92 to 1.18 / .91 to 1.02
+//     d = 128    3 to 6.5: 1.02 to 1.35 / 1.01 to 1.64 / .97 to 1.27; len 150 to 320, to 15: 1.01 to 1.15 / .98 to 1.20 /
+//                .95 to 1.15; len to 150, 6.5 to 8.5: 1.08 to 1.19 / 1.16 to 1.20 / -; to 19: .97 to 1.14 / .99 to 1.19 / -
+//                beyond 6.5, len > 320: .95 to 1.13 / .93 to 1.15 / .92 to 1.12
+//   more heads   dK/dV first.  Interleaved, measured before, two heads: .84 to 1.5 (as many dQ items as dK/dV, so
 //                every second group of a die, and these go to the same of its shader engines); from four: .90 to 1.1
-//     two        to 4: 1.03 to 1.63; 4.2: .99 to 1.04; len <= 320, to 5: 1.05 to 1.08
-//     to five    to 4: 1.01 to 1.38 (d = 64, 3.1: .99, so to 2.9 there); 4.2 to 5.3: .98 to 1.02; len <= 100, to 12:
-//                1.01 to 1.13
-//     to eight   to 2.7: 1.00 to 1.29; 3.1 to 3.6: .97 to 1.03; len <= 100, to 12: 1.00 to 1.07.  Not measured beyond.
+//     two        to 4: 1.02 to 1.79 / 1.00 to 1.71 / 1.01 to 1.62; 4 to 5.5, len to 320: 1.07 to 1.26 / 1.02 to 1.37 / 1.02
+//                to 1.04; longer: 1.01 to 1.05 / .95 to 1.09 / .97 to 1.05
+//     four       to 2.9: 1.04 to 1.78 / 1.03 to 1.45 / 1.01 to 1.39; 3 to 4, d = 64: .99 to 1.18 / .99 to 1.42 / .98 to 1.08;
+//                d = 128: 1.00 to 1.14 / .98 to 1.35 / .99 to 1.07; 4 to 5.5: .99 to 1.15 / .98 to 1.19 / .98 to 1.03; len to 150,
+//                to 12: 1.01 to 1.13 / .99 to 1.13 / -
+//     eight      to 2.7: 1.03 to 1.55 / 1.01 to 1.31 / .99 to 1.21; 3 to 4: .98 to 1.17 / .99 to 1.30 / .98 to 1.06; len to 150, to
+//                12: 1.00 to 1.07 / .96 to 1.17 / -.  Not measured beyond eight.
 enum Launches { kTwo, kOne, kOneInterleaved };
 inline Launches one_launch(const BwdItems& p) {
   if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 49 * 512) return kTwo;  // measured to 49 rounds of dQ
@@ -154,9 +177,8 @@ inline Launches one_launch(const BwdItems& p) {
   const double most = heads <= 5 ? (d == 64 ? 2.9 : 4) : 2.7;
   return heads <= 8 && (rounds <= most || (len <= 100 && rounds <= 12)) ? kOne : kTwo;
 }
-// The same at head size 192 (bwd_both4_kernel): two launches / one, T = 512 to 16384, 8, 16 and 128 heads and 12/4:  to 1
-// round 1.2 to 1.7; to 3: 1.04 to 1.77; to 4: 1.02 to 1.2; 4.2 to 5: .99 to 1.13; 6 to 10: .96 to 1.1; more: .95 to 1.0.
-// Items of several heads were not measured.
+// The same at head size 192 (bwd_both4_kernel), 16 heads: to 1 round 1.45 to 1.61; to 3: 1.07 to 1.75; to 4: 1.01 to 1.38; 4 to
+// 5.5: .99 to 1.27; to 8.5: .99 to 1.17; to 12: .99 to 1.09; more: .98 to 1.06.  Items of several heads were not measured.
 inline bool one_launch4(const BwdItems& p) {
   if (p.n_tiles <= 0 || p.n_q_tiles <= 0 || p.dq() > 49 * 512) return false;
   return p.heads() == 1 && (double)p.dkdv() / kNumCU <= 4;

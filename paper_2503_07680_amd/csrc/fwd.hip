@@ -1,6 +1,7 @@
 // Forward kernel: causal attention inside each sample of a packed buffer, gfx950.
 //
-// One work item = (query tile, one or two query heads of a kv head).  A persistent grid takes items
+// One work item = (query tile, one or two query heads of a kv head).  Launches of few rounds have a workgroup for
+// every item, which is its place in the grid (fwd_direct_kernel); else a persistent grid takes items
 // from per-die queues in worklist order (longest first).  Per item the workgroup (eight
 // wavefronts of 32 query rows each: two heads x 128 rows, or one head x 256 rows; four for one head x
 // 128 rows) walks the sample's keys from the sample start to the diagonal.
